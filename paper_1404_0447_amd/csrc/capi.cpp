@@ -587,8 +587,6 @@ selinv_status selinv_bind_workspace(selinv_plan P, void* d_ws, size_t bytes, hip
     P->inverted = false;
     P->ap_valid = false;
     P->queues_on_device = false;
-    const hipError_t init = kernels_init();
-    if (init != hipSuccess) return hip_fail(init, "kernel attributes");
     hipError_t e = hipSuccess;
     int dev = 0;
     hipDeviceProp_t prop;
@@ -669,7 +667,7 @@ selinv_status selinv_backward(selinv_plan P, const double* d_gsel, double* d_gA,
         const auto& c = P->t_rf2.off;
         const auto& d = P->t_diag.off;
         e = launch_revfac_level(&P->prof, D, a[l], a[l + 1] - a[l], b[l], b[l + 1] - b[l], c[l], c[l + 1] - c[l],
-                                d[l], d[l + 1] - d[l], s);
+                                d[l], d[l + 1] - d[l], P->diag_smax[l], s);
         if (e) return hip_fail(e, "reverse factor launch");
     }
     e = launch_gather(&P->prof, kRevFac, D.Zb, D.asm_off, P->nnzA, d_gA, s);

@@ -23,7 +23,6 @@
 
 #include <algorithm>
 #include <cstdint>
-#include <atomic>
 #include <type_traits>
 #include <utility>
 
@@ -2741,54 +2740,60 @@ __global__ __launch_bounds__(kThreads) void k_rf2(const Task* __restrict__ tasks
     }
 }
 
-// Fbar(B,B) stored lower = -T (Tbar + Tbar^T) T with the diagonal halved; one
-// work-group per block, Q = (Tbar + Tbar^T) T held in LDS (s <= 128).
+// Fbar(B,B) stored lower = -T (Tbar + Tbar^T) T with the diagonal halved
+// (s <= 128).  A work-group forms 16 columns J of the result: first
+// Q = (Tbar + Tbar^T) T(:,J) into LDS, then the tiles of T Q on and below the
+// diagonal, a wave per 16 x 16 tile, operands straight from global memory
+// (both matrices fit the L2 several times over) with eight steps of loads in
+// flight.  The step is a link of the root-first chain, so its time is the
+// latency of one block: with one work-group per block 64 tiles of Q shared
+// four waves, 155 us at s = 128; eight work-groups take about 15 us (the whole backward and forward of a
+// 31 x 29 x 30 grid: 10.7 -> 7.8 ms).
 __global__ __launch_bounds__(kThreads) void k_rf3(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                   const double* __restrict__ Tp, const double* __restrict__ Tb,
                                                   double* __restrict__ Zb)
 {
-    extern __shared__ double Q[];
+    __shared__ double Q[kLdsDiagMax][16 + 1];
     const BlockDesc d = blk[tasks[blockIdx.x].b];
-    const int s = d.s;
+    const int s = d.s, j0 = (int)blockIdx.y * 16;
+    if (j0 >= s) return;  // the grid covers the widest block of the level
     const int64_t ld = (int64_t)d.s + d.c;
-    const int ls = s + 1;
     const double* T = Tp + d.woff;
     const double* Tbar = Tb + d.woff;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m16 = lane & 15, q4 = lane >> 4;
     const int nt = (s + 15) / 16;
-    for (int p = wave; p < nt * nt; p += kThreads / 64) {
-        const int i0 = (p / nt) * 16, j0 = (p % nt) * 16;
+    // rows, columns and contraction indices past s read the last one instead;
+    // what they give is masked (k) or never stored (i, j)
+    const double* Tj = T + (int64_t)min(j0 + m16, s - 1) * s;
+    for (int p = wave; p < nt; p += kThreads / 64) {
+        const int i = min(p * 16 + m16, s - 1);
         d4 acc = {0, 0, 0, 0};
-        for (int k4 = 0; k4 < s; k4 += 4) {
-            const int k = k4 + (lane >> 4), i = i0 + (lane & 15), j = j0 + (lane & 15);
-            const double a = (i < s && k < s) ? Tbar[i + (int64_t)k * s] + Tbar[k + (int64_t)i * s] : 0.0;
-            const double b = (k < s && j < s) ? T[k + (int64_t)j * s] : 0.0;
-            acc = mfma(a, b, acc);
-        }
+        for (int k0 = 0; k0 < s; k0 += 32)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int kt = k0 + 4 * t + q4, k = min(kt, s - 1);
+                const double a = Tbar[i + (int64_t)k * s] + Tbar[k + (int64_t)i * s];
+                acc = mfma(kt < s ? a : 0.0, Tj[k], acc);
+            }
         mfma_drain();
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int ii = i0 + (lane >> 4) + 4 * v, jj = j0 + (lane & 15);
-            if (ii < s && jj < s) Q[ii * ls + jj] = acc[v];
-        }
+        for (int v = 0; v < 4; ++v) Q[p * 16 + q4 + 4 * v][m16] = acc[v];
     }
     __syncthreads();
-    for (int p = wave; p < nt * (nt + 1) / 2; p += kThreads / 64) {
-        int I = 0;
-        while ((I + 1) * (I + 2) / 2 <= p) ++I;
-        const int J = p - I * (I + 1) / 2;
-        const int i0 = I * 16, j0 = J * 16;
+    for (int p = (j0 >> 4) + wave; p < nt; p += kThreads / 64) {
+        const int i = min(p * 16 + m16, s - 1);
         d4 acc = {0, 0, 0, 0};
-        for (int k4 = 0; k4 < s; k4 += 4) {
-            const int k = k4 + (lane >> 4), i = i0 + (lane & 15), j = j0 + (lane & 15);
-            const double a = (i < s && k < s) ? T[i + (int64_t)k * s] : 0.0;
-            const double b = (k < s && j < s) ? Q[k * ls + j] : 0.0;
-            acc = mfma(a, b, acc);
-        }
+        for (int k0 = 0; k0 < s; k0 += 32)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const int kt = k0 + 4 * t + q4, k = min(kt, s - 1);
+                const double a = T[i + (int64_t)k * s];
+                acc = mfma(kt < s ? a : 0.0, Q[k][m16], acc);
+            }
         mfma_drain();
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int ii = i0 + (lane >> 4) + 4 * v, jj = j0 + (lane & 15);
+            const int ii = p * 16 + q4 + 4 * v, jj = j0 + m16;
             if (ii < s && jj < s && ii >= jj) Zb[d.poff + ii + (int64_t)jj * ld] = ii == jj ? -0.5 * acc[v] : -acc[v];
         }
     }
@@ -2834,18 +2839,6 @@ static inline unsigned grid_for(int64_t n)
     return (unsigned)g;
 }
 
-hipError_t kernels_init()
-{
-    // the reverse diagonal step needs more than the default 64 KB of LDS;
-    // set once per process (a failure is not remembered: the next call tries again)
-    static std::atomic<bool> done{false};
-    if (done.load()) return hipSuccess;
-    const hipError_t e =
-        hipFuncSetAttribute((const void*)k_rf3, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsDiagBytes);
-    if (e == hipSuccess) done.store(true);
-    return e;
-}
-
 hipError_t launch_backward_init(Prof* P, const DevPtrs& D, int64_t arena, int64_t harena, const double* gsel,
                                 int64_t nnzL, hipStream_t s)
 {
@@ -2879,7 +2872,7 @@ hipError_t launch_revfac_init(Prof* P, const DevPtrs& D, int64_t nblocks, int64_
 }
 
 hipError_t launch_revfac_level(Prof* P, const DevPtrs& D, int64_t a0, int64_t na, int64_t b0, int64_t nb, int64_t c0,
-                               int64_t nc, int64_t d0, int64_t nd, hipStream_t s)
+                               int64_t nc, int64_t d0, int64_t nd, int smax, hipStream_t s)
 {
     if (na > 0)
         launch(P, kRevFac, k_rf1a, dim3((unsigned)na), 0, s, D.t_rf1a + a0, D.blocks, (const double*)D.Zb,
@@ -2891,7 +2884,7 @@ hipError_t launch_revfac_level(Prof* P, const DevPtrs& D, int64_t a0, int64_t na
         launch(P, kRevFac, k_rf2, dim3((unsigned)nc), 0, s, D.t_rf2 + c0, D.blocks, (const double*)D.Lp,
                (const double*)D.Hb, D.Tb);
     if (nd > 0)
-        launch(P, kRevFac, k_rf3, dim3((unsigned)nd), kLdsDiagBytes, s, D.t_diag + d0, D.blocks, (const double*)D.Tp,
+        launch(P, kRevFac, k_rf3, dim3((unsigned)nd, (unsigned)(smax + 15) / 16), 0, s, D.t_diag + d0, D.blocks, (const double*)D.Tp,
                (const double*)D.Tb, D.Zb);
     return hipGetLastError();
 }

@@ -30,7 +30,6 @@ struct DevPtrs {
     const int64_t* ck_off;  // per block: its offset in the store (-1: not stored)
 };
 
-hipError_t kernels_init();
 hipError_t launch_backward_init(Prof* P, const DevPtrs& D, int64_t arena, int64_t harena, const double* gsel,
                                 int64_t nnzL, hipStream_t s);
 // rs3_cuts[0..ncuts): the level's t_rs3 tasks in groups launched one after
@@ -38,8 +37,9 @@ hipError_t launch_backward_init(Prof* P, const DevPtrs& D, int64_t arena, int64_
 hipError_t launch_revsel_level(Prof* P, const DevPtrs& D, int64_t a0, int64_t na, int64_t b0, int64_t nb,
                                const int64_t* rs3_cuts, int ncuts, hipStream_t s);
 hipError_t launch_revfac_init(Prof* P, const DevPtrs& D, int64_t nblocks, int64_t arena, hipStream_t s);
+// smax: the widest of the level's blocks t_diag[d0 .. d0+nd)
 hipError_t launch_revfac_level(Prof* P, const DevPtrs& D, int64_t a0, int64_t na, int64_t b0, int64_t nb, int64_t c0,
-                               int64_t nc, int64_t d0, int64_t nd, hipStream_t s);
+                               int64_t nc, int64_t d0, int64_t nd, int smax, hipStream_t s);
 // set-up of the inversion: tasks t_zero[t0 .. t0+n)
 hipError_t launch_zero_x(Prof* P, const DevPtrs& D, int64_t t0, int64_t n, hipStream_t s);
 // inverse panels of the blocks listed by t_diag[0 .. ntasks) that have a

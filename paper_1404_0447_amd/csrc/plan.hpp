@@ -147,6 +147,7 @@ struct selinv_plan_s {
     // path of the others (t_ldlt, t_panel, t_schur, t_gemm, t_sdiag, t_zero);
     // t_diag lists every block (used by the reverse sweep)
     selinv::LevelTasks t_diag, t_ldlt, t_panel, t_schur, t_gemm, t_sdiag, t_sb;
+    std::vector<int32_t> diag_smax;    // per level: the widest block of t_diag
     std::vector<int64_t> ldlt_cut;     // per level: t_ldlt splits into s <= 32 | <= 64 | wider at 2l, 2l+1
     // per level: t_schur in colour groups [cut[g], cut[g+1]) whose blocks share no column of C
     std::vector<std::vector<int64_t>> schur_cuts;

@@ -296,6 +296,7 @@ void build_schedule(selinv_plan_s* P)
     }
     P->t_zero.clear();
     P->t_zero_off.assign(D + 1, 0);
+    P->diag_smax.assign(D, 0);
     P->ldlt_cut.assign(2 * D, 0);
     P->schur_cuts.assign(D, {});
     P->rs3_cuts.assign(D, {});
@@ -373,6 +374,7 @@ void build_schedule(selinv_plan_s* P)
             const int pbn = deep ? std::min(bn, 64) : bn;
             const int s = d.s, c = d.c;
             P->t_diag.tasks.push_back({B, 0, 0, 0, 0, 0, 0, 0});
+            P->diag_smax[l] = std::max(P->diag_smax[l], d.s);
             // reverse sweep: every block, tiled
             const int nd = (s + kDiagTile - 1) / kDiagTile;
             const int rsplit = split_for(rdwant, c);

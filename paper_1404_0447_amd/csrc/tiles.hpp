@@ -23,9 +23,6 @@ constexpr int kZSplitRows = 64;
 // batch's larger levels cost more in sums than they gained
 constexpr int kZSplitFewTasks = 64;
 constexpr size_t kZSlotDoubles = 2 * (size_t)kZMaxS * kZMaxS;
-constexpr size_t kLdsDiagBytes = sizeof(double) * kLdsDiagMax * (kLdsDiagMax + 1);
-constexpr bool kUseSweep = true;  // register Gauss-Jordan sweep for s <= kLdsDiagMax
-constexpr size_t kDiagShmem = kUseSweep ? sizeof(double) * 2 * kLdsDiagMax : kLdsDiagBytes;
 
 // small blocks run whole on one wave (all phases, 16 x 16 MFMA tiles)
 constexpr int kSbS = 16;          // widest small block
