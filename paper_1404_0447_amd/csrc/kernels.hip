@@ -33,6 +33,7 @@
 namespace selinv {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 // two doubles read with one load from an 8-byte aligned address
 typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 // (cbase, rbase) of one position, one 16-byte load
@@ -1206,14 +1207,14 @@ __device__ void ldlt_global(const BlockDesc d, double* __restrict__ Lp, double* 
     double* F = Lp + d.poff;
     double* W = Wp + d.woff;
     double* T = Tp + d.woff;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, nthr = blockDim.x;
     for (int j = 0; j < s; ++j) {
         __syncthreads();
         const double dj = F[j + j * ld];
         const bool ok = isfinite(dj) && dj != 0.0 && (!require_spd || dj > 0.0);
         if (!ok && tid == 0) atomicMin(status, (unsigned long long)(d.first + j));
         const int m = s - j - 1;
-        for (int e = tid; e < m * m; e += kThreads) {
+        for (int e = tid; e < m * m; e += nthr) {
             const int ii = e % m, kk = e / m;
             if (ii >= kk) {
                 const int i = j + 1 + ii, k = j + 1 + kk;
@@ -1221,10 +1222,10 @@ __device__ void ldlt_global(const BlockDesc d, double* __restrict__ Lp, double* 
             }
         }
         __syncthreads();
-        for (int i = j + 1 + tid; i < s; i += kThreads) F[i + j * ld] /= dj;
+        for (int i = j + 1 + tid; i < s; i += nthr) F[i + j * ld] /= dj;
     }
     __syncthreads();
-    for (int j = tid; j < s; j += kThreads) {
+    for (int j = tid; j < s; j += nthr) {
         for (int i = 0; i < j; ++i) W[i + j * s] = 0.0;
         W[j + j * s] = 1.0;
         for (int i = j + 1; i < s; ++i) {
@@ -1234,164 +1235,13 @@ __device__ void ldlt_global(const BlockDesc d, double* __restrict__ Lp, double* 
         }
     }
     __syncthreads();
-    for (int e = tid; e < s * s; e += kThreads) {
+    for (int e = tid; e < s * s; e += nthr) {
         const int i = e % s, j = e / s;
         const int m = i > j ? i : j;
         double v = 0.0;
         for (int k = m; k < s; ++k) v += W[k + i * s] * W[k + j * s] / F[k + k * ld];
         T[e] = v;
     }
-}
-
-// Diagonal block, s <= 16 NB (NB = 2, 4, 8), by symmetric Gauss-Jordan
-// sweeps held in registers.  Sweeping pivot j (M(j,j) = d_j, c = M(:,j)):
-//   M(i,k) -= c_i c_k / d_j  (i, k != j),  M(i,j) = M(j,i) = c_i / d_j,
-//   M(j,j) = -1 / d_j.
-// After all pivots M = -F_BB^{-1} = -T.  Before its own sweep, column j
-// below the diagonal holds the Schur-complement column, so the multipliers
-// c_i / d_j (i > j) are L_BB(i,j) and d_j is D's entry: both are written
-// out as they appear.
-//
-// M stays symmetric, so only its lower 16 x 16 sub-blocks are held: thread
-// (tx, ty) = (tid % 16, tid / 16) owns M(tx + 16a, ty + 16b) for a >= b
-// (a diagonal sub-block whole).  Column j is then spread over two groups of
-// threads: ty == j % 16 holds rows >= 16 (j / 16) in sub-blocks (a, j / 16),
-// tx == j % 16 holds the rows above as row j of sub-blocks (j / 16, b).
-// The sweep is latency-bound (one pivot after the other), so each pivot
-// first forms the next pivot's column and publishes it in LDS (two
-// alternating slots, one barrier per pivot), then issues the LDS reads of
-// that column, and only then updates the rest of its registers while the
-// reads are in flight.
-template <int NB>
-__device__ __forceinline__ void ldlt_sweep(const BlockDesc d, double* __restrict__ Lp, double* __restrict__ Tp,
-                           unsigned long long* __restrict__ status, int require_spd, double (*colbuf)[kLdsDiagMax])
-{
-    constexpr int NS = NB * (NB + 1) / 2;
-    const int s = d.s;
-    const int64_t ld = (int64_t)d.s + d.c;
-    double* F = Lp + d.poff;
-    double* T = Tp + d.woff;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    auto slot = [](int a, int b) { return a * (a + 1) / 2 + b; };
-    auto read_col = [&](const double* col, double (&v)[NB], int r0) {
-#pragma unroll
-        for (int a = 0; a < NB; ++a) v[a] = col[r0 + 16 * a];
-    };
-    double M[NS];
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = 0; b <= a; ++b) {
-            const int i = tx + 16 * a, k = ty + 16 * b;
-            double v = 0.0;
-            if (i < s && k < s) v = i >= k ? F[i + k * ld] : F[k + i * ld];
-            M[slot(a, b)] = v;
-        }
-    // column 0 to slot 0; its reads
-    if (ty == 0) {
-#pragma unroll
-        for (int a = 0; a < NB; ++a) colbuf[0][tx + 16 * a] = M[slot(a, 0)];
-    }
-    __syncthreads();
-    double ri_[NB], rk_[NB], rd;  // the pivot column as read: rows tx + 16a, ty + 16b, and d_j
-    read_col(colbuf[0], ri_, tx);
-    read_col(colbuf[0], rk_, ty);
-    rd = colbuf[0][0];
-    // A thread records the column of L_BB (and D's entry) of the one pivot
-    // per group of 16 that it owns, and stores them when the group ends:
-    // a store inside the pivot loop would make every later write of its
-    // data register wait for the store to complete, a full memory round
-    // trip per pivot.
-    double lc[NB], dd = 0.0;
-#pragma unroll
-    for (int a = 0; a < NB; ++a) lc[a] = 0.0;
-#pragma unroll
-    for (int jb = 0; jb < NB; ++jb) {
-        const int jt_end = min(16, s - 16 * jb);
-        for (int jt = 0; jt < jt_end; ++jt) {
-            const int j = 16 * jb + jt;
-            const double dj = rd;
-            // 1 / d_j: hardware reciprocal and two Newton steps (each squares
-            // the relative error; the first estimate is good to about 2^-26)
-            double inv = __builtin_amdgcn_rcp(dj);
-            inv = fma(inv, fma(-dj, inv, 1.0), inv);
-            inv = fma(inv, fma(-dj, inv, 1.0), inv);
-            double ci[NB], ck[NB];
-#pragma unroll
-            for (int a = 0; a < NB; ++a) ci[a] = ri_[a] * inv;  // c_i / d_j
-#pragma unroll
-            for (int b = 0; b < NB; ++b) ck[b] = rk_[b];
-            if (tid == 0) {
-                const bool ok = isfinite(dj) && dj != 0.0 && (!require_spd || dj > 0.0);
-                if (!ok) atomicMin(status, (unsigned long long)(d.first + j));
-            }
-            if (ty == jt) {  // column j of L_BB and D, stored after this group of 16 pivots
-#pragma unroll
-                for (int a = jb; a < NB; ++a) lc[a] = ci[a];
-                dd = dj;
-            }
-            // M(tx + 16a, ty + 16b) after this pivot (a, b known at compile time)
-            auto after = [&](int a, int b) {
-                const bool ri = a == jb && tx == jt, rk = b == jb && ty == jt;
-                const double upd = M[slot(a, b)] - ci[a] * ck[b];
-                return (ri && rk) ? -inv : (ri ? ck[b] * inv : (rk ? ci[a] : upd));
-            };
-            // the next pivot's column, published before the bulk update
-            const bool more = j + 1 < s;
-            double* nb = colbuf[(j + 1) & 1];
-            if (more) {
-                if (jt + 1 < 16) {
-                    if (ty == jt + 1) {
-#pragma unroll
-                        for (int a = jb; a < NB; ++a) nb[tx + 16 * a] = after(a, jb);
-                    }
-                    if (tx == jt + 1) {
-#pragma unroll
-                        for (int b = 0; b < jb; ++b) nb[ty + 16 * b] = after(jb, b);
-                    }
-                } else if (jb + 1 < NB) {
-                    if (ty == 0) {
-#pragma unroll
-                        for (int a = jb + 1; a < NB; ++a) nb[tx + 16 * a] = after(a, jb + 1);
-                    }
-                    if (tx == 0) {
-#pragma unroll
-                        for (int b = 0; b < jb + 1; ++b) nb[ty + 16 * b] = after(jb + 1, b);
-                    }
-                }
-            }
-            __syncthreads();
-            if (more) {
-                read_col(nb, ri_, tx);
-                read_col(nb, rk_, ty);
-                rd = nb[j + 1];
-            }
-#pragma unroll
-            for (int a = 0; a < NB; ++a)
-#pragma unroll
-                for (int b = 0; b <= a; ++b) M[slot(a, b)] = after(a, b);
-        }
-        const int jo = 16 * jb + ty;  // the pivot this thread recorded
-        if (jo < s) {
-#pragma unroll
-            for (int a = jb; a < NB; ++a) {
-                const int i = tx + 16 * a;
-                if (i > jo && i < s) F[i + (int64_t)jo * ld] = lc[a];
-            }
-            if (tx == 0) F[jo + (int64_t)jo * ld] = dd;
-        }
-    }
-    // T = -M, made exactly symmetric from the lower triangle
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = 0; b <= a; ++b) {
-            const int i = tx + 16 * a, k = ty + 16 * b;
-            if (i < s && k < s && i >= k) {
-                T[i + (int64_t)k * s] = -M[slot(a, b)];
-                T[k + (int64_t)i * s] = -M[slot(a, b)];
-            }
-        }
 }
 
 // f(integral_constant<int, I>) for I = I0 .. N - 1, each call with its own
@@ -1423,216 +1273,387 @@ __device__ __forceinline__ double recip(double d)
     return inv;
 }
 
-// The same sweep (same thread ownership of M, same arithmetic per entry) for
-// a work-group that has the LDS to itself: every pivot's column is kept,
-// lds[j W + i] = M(i, j) when pivot j is swept (W = 16 NB), and 1 / d_j in
-// invd[j].  Rows below j of that column are the Schur-complement column, so
-// L_BB and D are written from LDS after the sweep (coalesced, no store inside
-// the pivot loop); T then goes through the same LDS, as a (W + 1)-strided
-// square, to be stored column by column.  Per pivot, the entries of the next
-// pivot's column are updated first and published, then, while the reads of
-// that column are in flight, the rest; the two register sets of the pivot
-// column alternate between pivots, so no copies are made.
+// ---------------------------------------------------------------------------
+// Diagonal block, s <= 16 NB (NB = 2, 4, 8): L_BB, D and T = F_BB^{-1} by
+// symmetric Gauss-Jordan sweeps over pivot blocks of 16 columns.  Sweeping
+// block p, with C(R) = M(R, p) (16 x 16 for every block row R) and
+// Q = M(p, p)^{-1}:
+//   M(I, J) -= (C(I) Q) C(J)^T  (I, J != p),  M(R, p) = C(R) Q,  M(p, p) = -Q;
+// after the last block M = -F_BB^{-1} = -T.  M's lower 16 x 16 tiles live in
+// LDS; the products run on MFMA.
+//
+// What bounds it is the chain of s dependent pivots.  So wave 0 does nothing
+// but that chain: it updates the next pivot block, inverts it in its own
+// registers (gj16: the pivot column and row go between lanes by row
+// broadcasts and row swaps, no LDS and no barrier; about 220 cycles a pivot,
+// against about 1,000 when each pivot's column went through LDS behind a
+// barrier) and stores -Q, while the other waves update the other tiles and
+// form L_BB.  A block step has two barriers: first all waves form
+// N(R) = -C(R) Q from the published tiles, then the updates run.
+// One block of 128 columns: 61 -> 33 us, of 64: 20 -> 14 us (launch
+// included); 32 columns take about 8 us either way.
+//
+// L_BB(R, p) = C(R) Q L_pp = C(R) L_pp^{-T} D_p^{-1} needs one more product a
+// tile and is off the pivot chain.  Rows and columns past s hold the
+// identity: their pivots are 1 and they touch nothing else.
+// ---------------------------------------------------------------------------
+constexpr int kDiagPad = 18;  // 16 doubles a row and 16 bytes: every row 16-byte aligned, operand reads conflict-free
 template <int NB>
-__device__ __forceinline__ void ldlt_sweep_cols(const BlockDesc d, double* __restrict__ Lp, double* __restrict__ Tp,
-                                                unsigned long long* __restrict__ status, int require_spd,
-                                                double* lds, double* invd)
+struct alignas(16) DiagLds {
+    double M[NB * (NB + 1) / 2][16][kDiagPad];  // tile (I, J), I >= J, at I (I + 1) / 2 + J
+    double C[16 * NB][kDiagPad];
+    double N[16 * NB][kDiagPad];
+    double Lb[2][16][kDiagPad];  // -L_pp
+    double D[2][16];
+};
+
+// x of lane J of each row of 16 lanes, in every lane of the row
+template <int J>
+__device__ __forceinline__ double row_lane(double x)
 {
-    constexpr int NS = NB * (NB + 1) / 2;
-    constexpr int W = 16 * NB;
-    const int s = d.s;
+    return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + J, 0xF, 0xF, true));
+}
+// row G (of the wave's four rows of 16 lanes) in every row: halves, then
+// neighbouring rows swapped between two copies
+template <int G>
+__device__ __forceinline__ unsigned row_copy32(unsigned x)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    const unsigned y = (G & 2) ? a[1] : a[0];
+    const auto b = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+    return (G & 1) ? b[1] : b[0];
+}
+template <int G>
+__device__ __forceinline__ double row_copy(double x)
+{
+    return __hiloint2double((int)row_copy32<G>((unsigned)__double2hiint(x)),
+                            (int)row_copy32<G>((unsigned)__double2loint(x)));
+}
+
+// Gauss-Jordan inversion of a symmetric 16 x 16 block, lane (m, g) holding
+// row m, columns g + 4 v.  Pivot j: l = column j / d_j; every row m != j
+// loses l_m times row j, and column j becomes -l (1 in row j).  Row j itself
+// is scaled by 1 / d_j once, at the end: until then the recurrence is linear
+// in it.  L: the multipliers l (rows below the diagonal: L_pp); dm: d_m.
+__device__ __forceinline__ void gj16(double (&P)[4], double (&L)[4], double& dm, const int m, const int g)
+{
+    double im = 0.0;  // 1 / d_m
+    StaticFor<0, 16>::run([&](auto jc) {
+        constexpr int j = decltype(jc)::value, gj = j & 3, vj = j >> 2;
+        const double c = row_copy<gj>(P[vj]);  // column j
+        const double dj = row_lane<j>(c);
+        const double inv = recip(dj);
+        const double l = c * inv;
+        const double lz = m == j ? 0.0 : l;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) P[v] = fma(-lz, row_lane<j>(P[v]), P[v]);
+        if (g == gj) {
+            P[vj] = m == j ? 1.0 : -l;
+            L[vj] = l;
+        }
+        if (m == j) {
+            im = inv;
+            dm = dj;
+        }
+    });
+#pragma unroll
+    for (int v = 0; v < 4; ++v) P[v] *= im;
+}
+
+// NW waves work on the block.  Lane (m, g) = (l % 16, l / 16) holds entry (m, g + 4 v) of a 16 x 16 block in
+// register v: the form of both MFMA operands (k = g + 4 v in step v) and,
+// with the product formed transposed, of its result.
+template <int NB, int NW>
+__device__ __forceinline__ void ldlt_blocks(const BlockDesc d, double* __restrict__ Lp, double* __restrict__ Tp,
+                                            unsigned long long* __restrict__ status, int require_spd, DiagLds<NB>& S)
+{
+    // tile waves: all but wave 0, and but wave 4 of 8, which shares its SIMD
+    // and forms L_BB
+    constexpr int NK = NW == 8 ? 6 : NW - 1;
+    constexpr int NT = NB * (NB + 1) / 2, NL = (NT + NK - 1) / NK;
+    constexpr int kGroup = NB < 8 ? 1 : 3;  // tiles updated together: independent MFMA chains
+    constexpr int kRows = NB == 8 && NK < 6 ? 2 : 1;      // rows of N a tile wave forms together
+    const int s = d.s, nb = (s + 15) >> 4;
     const int64_t ld = (int64_t)d.s + d.c;
     double* F = Lp + d.poff;
     double* T = Tp + d.woff;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    auto slot = [](int a, int b) { return a * (a + 1) / 2 + b; };
-    double M[NS];
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const bool chain = wave == 0, tiles = wave > 0 && (NW < 8 || wave != 4);
+    const int wk = wave - 1 - (NW == 8 && wave > 4);
+    const bool lower = NW == 8 ? wave == 4 : tiles;
+    const int l0 = NW == 8 ? 0 : wk, lstep = NW == 8 ? 1 : NK;
+    auto tile = [](int I, int J) { return (int)((unsigned)(I * (I + 1)) >> 1) + J; };
+    // tile (I, J) of index t, row by row: rows 1 .. 7 start at the bits set
+    auto tile_of = [&](int t, int& I, int& J) {
+        constexpr unsigned long long kStarts = 1ull << 1 | 1ull << 3 | 1ull << 6 | 1ull << 10 | 1ull << 15 |
+                                               1ull << 21 | 1ull << 28;
+        I = __builtin_popcountll(kStarts & ((2ull << t) - 1));
+        J = t - tile(I, 0);
+    };
+    double Q[4];
+    // invert the pivot block P of step p; -Q, -L_pp and D to LDS
+    auto pivots = [&](int p, const d4& P) {
+        double L[4] = {0.0, 0.0, 0.0, 0.0}, dm = 1.0;
 #pragma unroll
-    for (int a = 0; a < NB; ++a)
+        for (int v = 0; v < 4; ++v) Q[v] = P[v];
+        gj16(Q, L, dm, m, g);
 #pragma unroll
-        for (int b = 0; b <= a; ++b) {
-            const int i = tx + 16 * a, k = ty + 16 * b;
-            double v = 0.0;
-            if (i < s && k < s) v = i >= k ? F[i + k * ld] : F[k + i * ld];
-            M[slot(a, b)] = v;
+        for (int v = 0; v < 4; ++v) {
+            const int k = g + 4 * v;
+            S.M[tile(p, p)][m][k] = -Q[v];
+            S.Lb[p & 1][m][k] = m > k ? -L[v] : (m == k ? -1.0 : 0.0);
         }
-    if (ty == 0) {
+        if (g == 0) S.D[p & 1][m] = dm;
+    };
+    // F(i, j) of tile (I, J), the identity past s
+    auto load_tile = [&](int I, int J) {
+        d4 x;
 #pragma unroll
-        for (int a = 0; a < NB; ++a) lds[tx + 16 * a] = M[slot(a, 0)];
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * I + m, j = 16 * J + g + 4 * v;
+            const int a = min(max(i, j), s - 1), b = min(min(i, j), s - 1);
+            const double f = F[a + (int64_t)b * ld];
+            x[v] = i < s && j < s ? f : (i == j ? 1.0 : 0.0);
+        }
+        return x;
+    };
+    if (tiles) {
+        d4 x[NL];
+        const int nt = nb * (nb + 1) / 2;
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            int I, J;
+            tile_of(min(1 + u * NK + wk, nt - 1), I, J);
+            x[u] = load_tile(I, J);
+        }
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int t = 1 + u * NK + wk;
+            if (t < nt) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) S.M[t][m][g + 4 * v] = x[u][v];
+            }
+        }
     }
+    if (chain) pivots(0, load_tile(0, 0));
     __syncthreads();
-    // Column j of the LDS array.  Its offset is made opaque to the compiler:
-    // folded into the instruction it would exceed the 16-bit immediate offset
-    // of LDS instructions past 64 KiB, and every access would need an add.
-    auto col_at = [&](int j) {
-        int o = j * W;
-        asm volatile("" : "+s"(o));
-        return lds + o;
-    };
-    // the pivot column as read (rows tx + 16a, rows ty + 16b, d_j), in two sets
-    double riA[NB], rkA[NB], rdA, riB[NB], rkB[NB], rdB;
-    auto read_col = [&](int j, double (&ri)[NB], double (&rk)[NB], double& rd) {
-        const double* col = col_at(j);
+    for (int p = 0; p < nb; ++p) {
+        const int buf = p & 1;
+        const bool more = p + 1 < nb;
+        // C(R), N(R)^T = -Q C(R)^T and M(R, p) = -N(R), rows R[0 .. n)
+        auto rows_of = [&](const double (&nQ)[4], const int* R, const bool* live, auto n, d4* acc, double (*c)[4]) {
+            constexpr int kN = decltype(n)::value;
 #pragma unroll
-        for (int a = 0; a < NB; ++a) ri[a] = col[tx + 16 * a];
+            for (int e = 0; e < kN; ++e) {
+                const double* src = S.M[tile(max(R[e], p), min(R[e], p))][0];
+                if (R[e] > p) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) rk[b] = col[ty + 16 * b];
-        rd = col[j];
-    };
-    read_col(0, riA, rkA, rdA);
-
-    // Pivot j = 16 jb + jt.  `last`: jt = 15 with a next group, whose first
-    // column lies in sub-block column jb + 1.
-    auto pivot = [&](const int jb, const int jt, const bool last, const double (&ri)[NB], const double (&rk)[NB],
-                     const double rd, double (&rin)[NB], double (&rkn)[NB], double& rdn) {
-        const int j = 16 * jb + jt;
-        const double dj = rd;
-        const double inv = recip(dj);
-        double ci[NB];
+                    for (int v = 0; v < 4; ++v) c[e][v] = src[m * kDiagPad + g + 4 * v];
+                } else {
 #pragma unroll
-        for (int a = 0; a < NB; ++a) ci[a] = ri[a] * inv;  // c_i / d_j
-        // the slots that hold the next pivot's column
-        const int nb = last ? jb + 1 : jb;
-        auto in_next = [&](int a, int b) { return (b == nb && a >= nb) || (a == nb && b < nb); };
-        // M(i, k) -= c_i c_k / d_j for every slot of one phase, then row and
-        // column j overwritten by the lanes that hold them (a, b known at
-        // compile time; jb too, so only the slots of sub-block row / column
-        // jb take part)
-        auto update = [&](bool first) {
-#pragma unroll
-            for (int a = 0; a < NB; ++a)
-#pragma unroll
-                for (int b = 0; b <= a; ++b)
-                    if (in_next(a, b) == first) M[slot(a, b)] = fma(-ci[a], rk[b], M[slot(a, b)]);
-            if (ty == jt) {  // column j: c_i / d_j, and -1 / d_j on the diagonal
-#pragma unroll
-                for (int a = jb; a < NB; ++a)
-                    if (in_next(a, jb) == first) M[slot(a, jb)] = (a == jb && tx == jt) ? -inv : ci[a];
+                    for (int v = 0; v < 4; ++v) c[e][v] = src[(g + 4 * v) * kDiagPad + m];
+                }
             }
-            if (tx == jt) {  // row j
 #pragma unroll
-                for (int b = 0; b <= jb; ++b)
-                    if (in_next(jb, b) == first) M[slot(jb, b)] = (b == jb && ty == jt) ? -inv : rk[b] * inv;
-            }
+            for (int e = 0; e < kN; ++e) acc[e] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int e = 0; e < kN; ++e) acc[e] = mfma(nQ[v], c[e][v], acc[e]);
+#pragma unroll
+            for (int e = 0; e < kN; ++e)
+                if (live[e]) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) S.C[16 * R[e] + m][g + 4 * v] = c[e][v];
+                }
+            mfma_drain();
+#pragma unroll
+            for (int e = 0; e < kN; ++e)
+                if (live[e]) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) S.N[16 * R[e] + m][g + 4 * v] = acc[e][v];
+                    double* dst = S.M[tile(max(R[e], p), min(R[e], p))][0];
+                    if (R[e] > p) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) dst[m * kDiagPad + g + 4 * v] = -acc[e][v];
+                    } else {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) dst[(g + 4 * v) * kDiagPad + m] = -acc[e][v];
+                    }
+                }
         };
-        update(true);
-        const bool more = j + 1 < s;
-        const int nt = last ? 0 : jt + 1;  // the next pivot within sub-block nb
-        if (more) {
-            double* col = col_at(j + 1);
-            if (ty == nt) {
+        d4 P = {0, 0, 0, 0};
+        if (chain && more) {
+            // row p + 1, and the next pivot block with it: its update needs
+            // nothing from the other waves
+            const double nQ[4] = {-Q[0], -Q[1], -Q[2], -Q[3]};
+            const int R[1] = {p + 1};
+            const bool live[1] = {true};
+            d4 acc[1];
+            double c[1][4];
 #pragma unroll
-                for (int a = nb; a < NB; ++a) col[tx + 16 * a] = M[slot(a, nb)];
-            }
-            if (tx == nt) {
+            for (int v = 0; v < 4; ++v) P[v] = S.M[tile(p + 1, p + 1)][m][g + 4 * v];
+            rows_of(nQ, R, live, std::integral_constant<int, 1>{}, acc, c);
 #pragma unroll
-                for (int b = 0; b < nb; ++b) col[ty + 16 * b] = M[slot(nb, b)];
+            for (int v = 0; v < 4; ++v) P = mfma(c[0][v], acc[0][v], P);
+            mfma_drain();
+        }
+        if (tiles) {
+            double nQ[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) nQ[v] = S.M[tile(p, p)][m][g + 4 * v];
+            // p + 2, p + 3, .. cyclically, without p
+            for (int r0 = 1 + wk; r0 < nb - 1; r0 += kRows * NK) {
+                int R[kRows];
+                bool live[kRows];
+                d4 acc[kRows];
+                double c[kRows][4];
+#pragma unroll
+                for (int e = 0; e < kRows; ++e) {
+                    const int r = min(r0 + e * NK, nb - 2);
+                    live[e] = r0 + e * NK < nb - 1;
+                    R[e] = p + 1 + r < nb ? p + 1 + r : p + 1 + r - nb;
+                }
+                rows_of(nQ, R, live, std::integral_constant<int, kRows>{}, acc, c);
             }
+        }
+        if (chain && !more && nb > 1) {
+            // the last step has no row p + 1: wave 0 takes the first of the others
+            const double nQ[4] = {-Q[0], -Q[1], -Q[2], -Q[3]};
+            const int R[1] = {0};
+            const bool live[1] = {true};
+            d4 acc[1];
+            double c[1][4];
+            rows_of(nQ, R, live, std::integral_constant<int, 1>{}, acc, c);
         }
         __syncthreads();
-        if (more) read_col(j + 1, rin, rkn, rdn);
-        update(false);
-        // keeps this pivot's updates inside it, where they hide the latency
-        // of the column reads (the compiler would sink them past the next
-        // pivot's barrier)
+        if (tiles) {
+            // M(I, J) += N(I) C(J)^T over the tiles outside row and column p
+            // and the next pivot block
+            const int nt = nb * (nb - 1) / 2;
+            for (int t0 = wk; t0 < nt; t0 += kGroup * NK) {
+                d4 x[kGroup];
+                d2 a[kGroup][2], b[kGroup][2];  // contraction index 4 g + t in step t
+                double(*tp[kGroup])[kDiagPad];
+                bool live[kGroup];
 #pragma unroll
-        for (int a = 0; a < NB; ++a)
+                for (int e = 0; e < kGroup; ++e) {
+                    int I, J;
+                    const int t = t0 + e * NK;
+                    tile_of(min(t, nt - 1), I, J);
+                    I += I >= p;
+                    J += J >= p;
+                    live[e] = t < nt && !(I == p + 1 && J == p + 1);
+                    tp[e] = S.M[tile(I, J)];
 #pragma unroll
-            for (int b = 0; b <= a; ++b)
-                if (!in_next(a, b)) asm volatile("" : "+v"(M[slot(a, b)]));
-    };
-    auto copy_BA = [&]() {
+                    for (int v = 0; v < 4; ++v) x[e][v] = tp[e][m][g + 4 * v];
 #pragma unroll
-        for (int a = 0; a < NB; ++a) riA[a] = riB[a], rkA[a] = rkB[a];
-        rdA = rdB;
-    };
-    StaticFor<0, NB>::run([&](auto jbc) {
-        constexpr int jb = decltype(jbc)::value;
-        const int jt_end = min(16, s - 16 * jb);
-        const bool handover = jt_end == 16 && 16 * (jb + 1) < s;
-        const int nplain = handover ? 15 : jt_end;
-        int jt = 0;
-        for (; jt + 1 < nplain; jt += 2) {
-            pivot(jb, jt, false, riA, rkA, rdA, riB, rkB, rdB);
-            pivot(jb, jt + 1, false, riB, rkB, rdB, riA, rkA, rdA);
-        }
-        if (jt < nplain) {
-            pivot(jb, jt, false, riA, rkA, rdA, riB, rkB, rdB);
-            copy_BA();
-        }
-        if (handover) {
-            pivot(jb, 15, true, riA, rkA, rdA, riB, rkB, rdB);
-            copy_BA();
-        }
-    });
-    // d_j is column j's diagonal entry: the pivot check (the first failing
-    // pivot wins the atomic minimum) and 1 / d_j as the sweep formed it
-    if (tid < s) {
-        const double dj = lds[tid * W + tid];
-        const bool ok = isfinite(dj) && dj != 0.0 && (!require_spd || dj > 0.0);
-        if (!ok) atomicMin(status, (unsigned long long)(d.first + tid));
-        invd[tid] = recip(dj);
-    }
-    __syncthreads();
-    // L_BB(i, j) = c_i / d_j below the diagonal, D on it; eight columns per
-    // thread at a time, their LDS reads issued together
-    constexpr int kCols = kThreads / W;  // columns per pass
-    constexpr int kU = 8;
-    const int i = tid % W;
-    for (int j0 = tid / W; j0 < s; j0 += kCols * kU) {
-        double v[kU], r[kU];
+                    for (int h = 0; h < 2; ++h) {
+                        a[e][h] = *reinterpret_cast<const d2*>(&S.C[16 * J + m][4 * g + 2 * h]);
+                        b[e][h] = *reinterpret_cast<const d2*>(&S.N[16 * I + m][4 * g + 2 * h]);
+                    }
+                }
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int j = min(j0 + u * kCols, W - 1);
-            v[u] = lds[j * W + i];
-            r[u] = invd[j];
-        }
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int j = j0 + u * kCols;
-            if (j < s && i >= j && i < s) F[i + (int64_t)j * ld] = i == j ? v[u] : v[u] * r[u];
-        }
-    }
-    __syncthreads();  // column history read
-    // T = -M, made exactly symmetric from the lower triangle
+                    for (int w = 0; w < 2; ++w)
 #pragma unroll
-    for (int a = 0; a < NB; ++a)
+                        for (int e = 0; e < kGroup; ++e) x[e] = mfma(a[e][h][w], b[e][h][w], x[e]);
+                mfma_drain();
 #pragma unroll
-        for (int b = 0; b <= a; ++b) {
-            const int r = tx + 16 * a, k = ty + 16 * b;
-            if (r >= k) {
-                lds[r + k * (W + 1)] = -M[slot(a, b)];
-                lds[k + r * (W + 1)] = -M[slot(a, b)];
+                for (int e = 0; e < kGroup; ++e)
+                    if (live[e]) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) tp[e][m][g + 4 * v] = x[e][v];
+                    }
             }
         }
-    __syncthreads();
-    for (int k0 = tid / W; k0 < s; k0 += kCols * kU) {
-        double v[kU];
+        if (lower) {
+            // L_BB(R, p) = N(R) (-L_pp) below the pivot block, L_pp and D in it
+            const double* lb = &S.Lb[buf][0][0];
+            double a[4];
 #pragma unroll
-        for (int u = 0; u < kU; ++u) v[u] = lds[i + min(k0 + u * kCols, W - 1) * (W + 1)];
+            for (int v = 0; v < 4; ++v) a[v] = lb[(g + 4 * v) * kDiagPad + m];
+            double* Fp = F + m + (int64_t)(16 * p + g) * ld;
+            if (l0 == 0) {
+                const double dm = S.D[buf][m];
+                const int row = 16 * p + m;
+                if (g == 0 && row < s && !(isfinite(dm) && dm != 0.0 && (!require_spd || dm > 0.0)))
+                    atomicMin(status, (unsigned long long)(d.first + row));
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int k = k0 + u * kCols;
-            if (k < s && i < s) T[i + (int64_t)k * s] = v[u];
+                for (int v = 0; v < 4; ++v) {
+                    const double x = m == g + 4 * v ? dm : -lb[m * kDiagPad + g + 4 * v];
+                    if (row < s && m >= g + 4 * v) Fp[16 * p + (int64_t)(4 * v) * ld] = x;
+                }
+            }
+            for (int R = p + 1 + l0; R < nb; R += 2 * lstep) {
+                const int R2 = min(R + lstep, nb - 1);
+                d4 x = {0, 0, 0, 0}, y = {0, 0, 0, 0};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    x = mfma(a[v], S.N[16 * R + m][g + 4 * v], x);
+                    y = mfma(a[v], S.N[16 * R2 + m][g + 4 * v], y);
+                }
+                mfma_drain();
+                // a repeated last row writes the same values twice
+                if (16 * R + m < s) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Fp[16 * R + (int64_t)(4 * v) * ld] = x[v];
+                }
+                if (16 * R2 + m < s) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Fp[16 * R2 + (int64_t)(4 * v) * ld] = y[v];
+                }
+            }
+        }
+        if (chain && more) pivots(p + 1, P);
+        __syncthreads();
+    }
+    // T = -M, made exactly symmetric from the lower triangle
+    for (int t = wave; t < nb * (nb + 1) / 2; t += NW) {
+        int I, J;
+        tile_of(t, I, J);
+        double lo[4], up[4];  // entries (m, k) and (k, m), k = g + 4 v
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            lo[v] = -S.M[t][m][g + 4 * v];
+            up[v] = -S.M[t][g + 4 * v][m];
+        }
+        double* Tl = T + 16 * I + m + (int64_t)(16 * J + g) * s;
+        double* Tu = T + 16 * J + m + (int64_t)(16 * I + g) * s;
+        if (I != J && 16 * I + 16 <= s) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                Tl[(int64_t)(4 * v) * s] = lo[v];
+                Tu[(int64_t)(4 * v) * s] = up[v];
+            }
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = g + 4 * v;
+                if (16 * I + m < s && (I != J || k <= m)) Tl[(int64_t)(4 * v) * s] = lo[v];
+                if (16 * I + k < s && (I != J || m < k)) Tu[(int64_t)(4 * v) * s] = up[v];
+            }
         }
     }
 }
 
-// one launch per width class: NB = 2, 4, 8 for s <= 32, 64, 128; wider
-// blocks take ldlt_global
+// One launch per width class, a work-group per block: two waves for s <= 32,
+// four for s <= 64, eight wider; blocks wider than 128 take ldlt_global.
+constexpr int diag_waves(int NB) { return NB == 2 ? 2 : NB == 4 ? 4 : 8; }
 template <int NB>
-__global__ __launch_bounds__(kThreads) void k_ldlt_diag(const Task* __restrict__ tasks,
-                                                        const BlockDesc* __restrict__ blk, double* __restrict__ Lp,
-                                                        double* __restrict__ Wp, double* __restrict__ Tp,
-                                                        unsigned long long* __restrict__ status, int require_spd)
+__global__ __launch_bounds__(64 * diag_waves(NB)) void k_ldlt_diag(const Task* __restrict__ tasks,
+                                                                   const BlockDesc* __restrict__ blk,
+                                                                   double* __restrict__ Lp, double* __restrict__ Wp,
+                                                                   double* __restrict__ Tp,
+                                                                   unsigned long long* __restrict__ status,
+                                                                   int require_spd)
 {
-    static_assert(kThreads % (16 * NB) == 0, "rows of a column split evenly over the work-group");
-    __shared__ __align__(16) double lds[16 * NB * (16 * NB + 1)];
-    __shared__ double invd[16 * NB];
-    const Task t = tasks[blockIdx.x];
-    const BlockDesc d = blk[t.b];
-    if (d.s > 16 * NB) ldlt_global(d, Lp, Wp, Tp, status, require_spd);
-    else ldlt_sweep_cols<NB>(d, Lp, Tp, status, require_spd, lds, invd);
+    __shared__ DiagLds<NB> S;
+    const BlockDesc d = blk[tasks[blockIdx.x].b];
+    if (NB == 8 && d.s > 16 * NB) ldlt_global(d, Lp, Wp, Tp, status, require_spd);
+    else ldlt_blocks<NB, diag_waves(NB)>(d, Lp, Tp, status, require_spd, S);
 }
 
 // ---------------------------------------------------------------------------
@@ -2149,14 +2170,14 @@ __global__ __launch_bounds__(kThreads) void k_sb_invert(const Task* __restrict__
 // every wait ends; a wait that exceeds spin_limit polls latches status[1]
 // and the task proceeds, so the kernel always drains.
 // ===========================================================================
+template <int NB>  // the widest diagonal block (16 NB; inversion kernels: none, NB = 1)
 union PersistLds {
     TileLds tile;
     GemmLds gemm;
     SdiagLds sd;
-    alignas(16) double colbuf[2][kLdsDiagMax];
+    DiagLds<NB> diag;
     SbLds sb[kThreads / 64];
 };
-
 
 struct QueueArgs {
     const Task* q;
@@ -2227,7 +2248,7 @@ __device__ __forceinline__ void signal_done(const QueueArgs& a, const Task& t)
 // diagonal block of a tiled level: the host keeps s <= 16 NB, or NB = 8
 template <int NB>
 __device__ __forceinline__ void diag_block(const BlockDesc& d, double* Lp, double* Wp, double* Tp,
-                                           unsigned long long* status, int require_spd, double (*colbuf)[kLdsDiagMax])
+                                           unsigned long long* status, int require_spd, DiagLds<NB>& S)
 {
     if constexpr (NB == 8) {
         if (d.s > kLdsDiagMax) {
@@ -2235,7 +2256,7 @@ __device__ __forceinline__ void diag_block(const BlockDesc& d, double* Lp, doubl
             return;
         }
     }
-    ldlt_sweep<NB>(d, Lp, Tp, status, require_spd, colbuf);
+    ldlt_blocks<NB, kThreads / 64>(d, Lp, Tp, status, require_spd, S);
 }
 
 // L_hat tile; tiles are at most as wide as the level's widest block
@@ -2279,7 +2300,7 @@ __global__ __launch_bounds__(kThreads, NB < 8 ? 2 : 1) void k_persist_factor(con
                                                              const int64_t* __restrict__ rbase,
                                                              const int32_t* __restrict__ rel)
 {
-    __shared__ PersistLds sm;
+    __shared__ PersistLds<NB> sm;
     __shared__ int s_idx;
     // a work-group cannot claim more than ntasks entries: the bound only
     // makes termination evident
@@ -2322,7 +2343,7 @@ __global__ __launch_bounds__(kThreads, NB < 8 ? 2 : 1) void k_persist_factor(con
             }
             switch (o) {
                 case qLdlt:
-                    diag_block<NB>(d, Lp, Wp, Tp, a.status, a.require_spd, sm.colbuf);
+                    diag_block<NB>(d, Lp, Wp, Tp, a.status, a.require_spd, sm.diag);
                     break;
                 case qPanel:
                     panel_bounded<NB>(sm.gemm, u, d, Lp, Hp, Tp);
@@ -2349,7 +2370,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_persist_invert(const QueueArgs 
                                                                 const int32_t* __restrict__ rel,
                                                                 const int64_t* __restrict__ cr2)
 {
-    __shared__ PersistLds sm;
+    __shared__ PersistLds<1> sm;
     __shared__ int s_idx;
     for (int64_t it = 0; it < a.ntasks; ++it) {
         const int idx = claim(a, &s_idx);
@@ -2818,17 +2839,23 @@ Prof::~Prof()
 }
 
 template <class Kern, class... Args>
-static void launch(Prof* P, int kind, Kern kern, dim3 grid, size_t shmem, hipStream_t s, Args... args)
+static void launch_wg(Prof* P, int kind, Kern kern, dim3 grid, int threads, size_t shmem, hipStream_t s, Args... args)
 {
     if (P && P->on) {
         hipEvent_t a = P->next(), z = P->next();
         if (a && z) {
-            hipExtLaunchKernelGGL(kern, grid, dim3(kThreads), (uint32_t)shmem, s, a, z, 0, args...);
+            hipExtLaunchKernelGGL(kern, grid, dim3((unsigned)threads), (uint32_t)shmem, s, a, z, 0, args...);
             P->kinds.push_back(kind);
             return;
         }
     }
-    hipLaunchKernelGGL(kern, grid, dim3(kThreads), shmem, s, args...);
+    hipLaunchKernelGGL(kern, grid, dim3((unsigned)threads), shmem, s, args...);
+}
+
+template <class Kern, class... Args>
+static void launch(Prof* P, int kind, Kern kern, dim3 grid, size_t shmem, hipStream_t s, Args... args)
+{
+    launch_wg(P, kind, kern, grid, kThreads, shmem, s, args...);
 }
 
 static inline unsigned grid_for(int64_t n)
@@ -2976,14 +3003,14 @@ hipError_t launch_ldlt_level(Prof* P, const DevPtrs& D, const int64_t diag[4], i
     // diagonal blocks by width class: [diag[0], diag[1]) s <= 32, then <= 64,
     // then wider
     if (diag[1] > diag[0])
-        launch(P, kLdlt, k_ldlt_diag<2>, dim3((unsigned)(diag[1] - diag[0])), 0, s, D.t_ldlt + diag[0], D.blocks,
-               D.Lp, D.Wp, D.Tp, D.status, require_spd);
+        launch_wg(P, kLdlt, k_ldlt_diag<2>, dim3((unsigned)(diag[1] - diag[0])), 64 * diag_waves(2), 0, s, D.t_ldlt + diag[0],
+                  D.blocks, D.Lp, D.Wp, D.Tp, D.status, require_spd);
     if (diag[2] > diag[1])
-        launch(P, kLdlt, k_ldlt_diag<4>, dim3((unsigned)(diag[2] - diag[1])), 0, s, D.t_ldlt + diag[1], D.blocks,
-               D.Lp, D.Wp, D.Tp, D.status, require_spd);
+        launch_wg(P, kLdlt, k_ldlt_diag<4>, dim3((unsigned)(diag[2] - diag[1])), 64 * diag_waves(4), 0, s, D.t_ldlt + diag[1],
+                  D.blocks, D.Lp, D.Wp, D.Tp, D.status, require_spd);
     if (diag[3] > diag[2])
-        launch(P, kLdlt, k_ldlt_diag<8>, dim3((unsigned)(diag[3] - diag[2])), 0, s, D.t_ldlt + diag[2], D.blocks,
-               D.Lp, D.Wp, D.Tp, D.status, require_spd);
+        launch_wg(P, kLdlt, k_ldlt_diag<8>, dim3((unsigned)(diag[3] - diag[2])), 64 * diag_waves(8), 0, s, D.t_ldlt + diag[2],
+                  D.blocks, D.Lp, D.Wp, D.Tp, D.status, require_spd);
     return hipGetLastError();
 }
 

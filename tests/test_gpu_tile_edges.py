@@ -54,3 +54,32 @@ def test_dense_gradient(n, cap, det):
     acols, arows = np.triu_indices(n)
     ref = np.where(arows == acols, 0.5, 1.0) * d[arows, acols]
     assert np.abs(g - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("run", ["levels", "persistent"])
+@pytest.mark.parametrize("n,cap", [(1, 128), (2, 128), (15, 128), (16, 128), (17, 128), (31, 128), (32, 128),
+                                   (33, 128), (48, 128), (63, 128), (64, 128), (65, 128), (112, 128), (113, 128),
+                                   (127, 128), (128, 128), (129, 128), (90, 17), (135, 64), (250, 49), (385, 128)])
+def test_dense_forward(n, cap, run):
+    """Selected inverse and factor of chains of blocks of `cap` columns."""
+    import torch
+    a, m = _dense(n, n)
+    p = _plan(m, max_super=cap, exec_cap=min(cap, 128))
+    v = torch.as_tensor(m.vals, device="cuda")
+    if run == "levels":
+        p.factor(v)
+        sel = p.invert()
+    else:
+        p.set_schedule(mb_tiles=0, small_s=0)
+        sel = p.run(v)
+    p.sync_status()
+    cp, ri, perm = p.pattern()
+    cols = np.repeat(np.arange(n), np.diff(cp))
+    ap = a[np.ix_(perm, perm)]
+    assert np.abs(sel.cpu().numpy() - np.linalg.inv(ap)[ri, cols]).max() <= 1e-12
+    lv = p.factor_values().cpu().numpy()
+    ld = np.zeros((n, n))
+    ld[ri, cols] = lv
+    d = np.diag(ld).copy()
+    np.fill_diagonal(ld, 1.0)
+    assert np.abs(ld @ np.diag(d) @ ld.T - ap).max() <= 1e-12
