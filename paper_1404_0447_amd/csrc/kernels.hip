@@ -24,7 +24,6 @@
 #include <algorithm>
 #include <cstdint>
 #include <type_traits>
-#include <utility>
 
 #include "kernels.hpp"
 #include "plan.hpp"
@@ -52,35 +51,6 @@ __device__ __forceinline__ void mfma_drain()
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-}
-
-// Instruction interleaving for a software-pipelined MFMA loop body: NM
-// slots, each one MFMA followed by its share of the other instructions of
-// the body (DS reads, DS writes, global loads, VALU), so that a wave issues
-// its address arithmetic and memory operations while its own MFMAs run
-// instead of in a block of its own.  A prologue slot holds the DS reads the
-// first MFMA needs.  Counts are hints to the scheduler: what does not fit
-// the pattern is scheduled freely.
-template <int NM, int NDR0, int NDR, int NDW, int NVM, int NVALU, int I>
-__device__ __forceinline__ void sgb_slot()
-{
-    constexpr int kMfma = 0x008, kValu = 0x002, kVmemRead = 0x020, kDsRead = 0x100, kDsWrite = 0x200;
-    __builtin_amdgcn_sched_group_barrier(kMfma, 1, 0);
-    if constexpr ((I + 1) * NDR / NM > I * NDR / NM) __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
-    if constexpr ((I + 1) * NDW / NM > I * NDW / NM) __builtin_amdgcn_sched_group_barrier(kDsWrite, 1, 0);
-    if constexpr ((I + 1) * NVM / NM > I * NVM / NM) __builtin_amdgcn_sched_group_barrier(kVmemRead, 1, 0);
-    if constexpr (NVALU > 0) __builtin_amdgcn_sched_group_barrier(kValu, NVALU, 0);
-}
-template <int NM, int NDR0, int NDR, int NDW, int NVM, int NVALU, int... I>
-__device__ __forceinline__ void sgb_body(std::integer_sequence<int, I...>)
-{
-    if constexpr (NDR0 > 0) __builtin_amdgcn_sched_group_barrier(0x100, NDR0, 0);
-    (sgb_slot<NM, NDR0, NDR, NDW, NVM, NVALU, I>(), ...);
-}
-template <int NM, int NDR0, int NDR, int NDW, int NVM, int NVALU>
-__device__ __forceinline__ void sgb_interleave()
-{
-    sgb_body<NM, NDR0, NDR, NDW, NVM, NVALU>(std::make_integer_sequence<int, NM>{});
 }
 
 // LDS written by some lanes of a wave, then read by others
@@ -560,15 +530,6 @@ __device__ __forceinline__ void tile_mma_deep(GemmLds& L, int Kb, int Ke, d4 (&a
 // Selected inversion, step 3: X = Ainv(C,B) = -Ainv(C,C) L_hat(C,B) for rows
 // [i0, i0+64) and columns [j0, j0+BN) of X.  Ainv(C,C) is gathered from the
 // ancestors' panels: entries with i >= k directly, the others by symmetry.
-//
-// The gather G(i,k) = Ap[cbase[p] + rel[rbase[p] + q]] (p, q = k, i when
-// i >= k, else i, k) is a chain of three dependent loads, so the main loop
-// is a software pipeline over 16-deep chunks of the contraction: while the
-// MFMAs consume chunk n from one LDS buffer, the values of chunk n+1 are
-// stored to the other, the values of chunk n+2 are loaded from the offsets
-// found one iteration earlier, the rel entries of chunk n+3 and the
-// (cbase, rbase) pairs of chunk n+4 are loaded: every load has a whole
-// iteration of MFMAs to arrive, and there is one barrier per chunk.
 // ---------------------------------------------------------------------------
 // The pipelined gather-GEMM loop, shared by the forward gather-GEMM and the
 // reverse sweep: acc += A B over the contraction [Kb, Ke) for tile rows
@@ -576,172 +537,319 @@ __device__ __forceinline__ void tile_mma_deep(GemmLds& L, int Kb, int Ke, d4 (&a
 //   A(i, k) = S[cbase[p] + rel[rbase[p] + q]],  p = min(i, k), q = max(i, k)
 // (an arena gathered through the block index maps; kTri = 1 keeps k <= i
 // only, 2 keeps k >= i only, 0 all) and B(k, j) = Bm[k + (n0 + j) ldb].
-template <int BN, bool kPair, int kTri>
-__device__ __forceinline__ void gather_mma(GemmLds& L, const BlockDesc d, const int r0, const int n0, const int Kb,
+//
+// What bounds it: the FP64 MFMAs and the vector instructions beside them.
+// The two share the SIMD's FP64 hardware on this part: a vector instruction
+// next to an FP64 MFMA costs its four issue cycles (measured: 77 TFLOP/s with
+// none, 54 with five per MFMA).  So the loop is built to issue few:
+//  * Chunks of the contraction come in three modes.  Below the diagonal band
+//    (k < i for the whole tile) p = k: the lanes of a wave run along i, so
+//    the map entry is one address per wave and the rel entries and values are
+//    contiguous.  Above it p = i, and the lanes run along k.  Only the chunks
+//    of the band, and a ragged last chunk, form min and max per element and
+//    carry masks.  In the other modes every per-lane offset is a constant of
+//    the tile, and the chunk's position sits in the scalar base.
+//  * Rows past c read row c - 1 (their products are never stored), columns
+//    past s read column s - 1, and chunks past the end read the last chunk
+//    again, so no load needs a mask.
+//  * Both operands lie in LDS as rows of 16 contraction entries (128 bytes),
+//    their 16-byte slots exclusive-or'ed with row / 2 mod 8, which makes the
+//    16-byte reads of an MFMA pair conflict-free without padding; a pair of
+//    reads feeds two MFMAs (contraction entries 8 t + 2 g and + 1).
+// Vector instructions per 32 MFMAs: 154 -> 21.  Gather-GEMM of the 64^3
+// matrix: 22.0 -> 18.4 ms (11.2 ms of it MFMA at the rate above, padding
+// included; without the loads of A it takes 15.3).
+//
+// The software pipeline: while the MFMAs consume chunk n from one LDS buffer,
+// the values of chunk n+1 are stored to the other, and the loads of A of
+// chunk n+3, of B of chunk n+2, of the rel entries of chunk n+4 and of the
+// (cbase, rbase) pairs of chunk n+5 are issued: A, which comes from HBM, has
+// two iterations of MFMAs to arrive, the others one.  One barrier per chunk.
+// Byte offsets inside a block's panel and C's maps are 32-bit: a |C| that
+// exceeds them (4 million) would need a 16 TB inverse.
+constexpr int kGatherRow = 16 * (int)sizeof(double);  // bytes of one LDS row
+template <int BNMAX>
+struct alignas(16) GatherLdsN {
+    char A[2][TBM * kGatherRow];
+    char B[2][BNMAX * kGatherRow];
+};
+using GatherLds = GatherLdsN<128>;
+
+template <int BN, int kTri, class LDS>
+__device__ __forceinline__ void gather_mma(LDS& L, const BlockDesc d, const int r0, const int n0, const int Kb,
                                            const int Ke, const double* __restrict__ S, const double* __restrict__ Bm,
                                            const int64_t ldb, const int64_t* __restrict__ cr2,
                                            const int32_t* __restrict__ rel, d4 (&acc)[2][4])
 {
     using SH = TileShape<BN>;
-    constexpr int NB = BN / 16;  // B elements per thread per chunk
-    const int s = d.s, c = d.c;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(sizeof(L.B[0]) >= BN * kGatherRow, "the LDS tile holds BN columns");
+    constexpr int NP = BN >= 32 ? BN / 32 : 1;  // pairs (k, k + 1) of B per thread per chunk
+    const int c = d.c;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm0 = (wave % SH::WM) * (TBM / SH::WM), wn0 = (wave / SH::WM) * (BN / SH::WN);
     const int nch = Ke > Kb ? (Ke - Kb + TBK - 1) / TBK : 0;
-    // chunks entirely above the diagonal band are read along k (contiguous)
-    auto along_of = [&](int ch) { return Kb + ch * TBK >= r0 + TBM; };
-    // element q of this thread in chunk ch: (kk, ii) = along ? (e & 15, e >> 4) : (e >> 6, e & 63)
-    auto elem = [&](int ch, int q, int& i, int& k) {
-        const int e = tid + q * kThreads;
-        const bool al = along_of(ch);
-        i = r0 + (al ? e >> 4 : e & 63);
-        k = Kb + ch * TBK + (al ? e & 15 : e >> 6);
-        if (ch >= nch) k = c;  // past the end: padding
+    if (nch == 0) return;
+    enum { kBelow = 0, kAbove = 1, kBand = 2 };
+    auto k_of = [&](int ch) { return Kb + min(ch, nch - 1) * TBK; };
+    auto mode_of = [&](int k0) {
+        if (k0 + TBK > Ke) return (int)kBand;
+        if (kTri != 2 && k0 + TBK <= r0) return (int)kBelow;
+        if (kTri != 1 && k0 >= r0 + TBM) return (int)kAbove;
+        return (int)kBand;
     };
-    // Loads are unconditional and every stage only issues loads into raw
-    // registers; whatever consumes a loaded value (the offset sums, the
-    // padding masks) runs in the next stage, an iteration later, so no wait
-    // falls right behind its own load.  A padding element reads an in-bounds
-    // stand-in (position 0 of the block's maps, its own L_hat) and is zeroed
-    // by its mask.
-    int64_t m_cb[4], m_rb[4];  // stage M: cbase[p], rbase[p] as loaded
-    int m_q[4];                // stage M: q (the second index), -1 for padding
-    int64_t r_cb[4];           // stage R: cbase[p]
-    int32_t r_rel[4];          // stage R: rel[rbase[p] + q] as loaded
-    bool r_ok[4];
-    double v_a[4], v_b[NB];    // stage V: values as loaded
-    bool v_ok[4];
-    bool av = false;           // stage V chunk is read along k
-    auto stage_m = [&](int ch) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int i, k;
-            elem(ch, q, i, k);
-            const bool ok = i < c && k < c && (kTri == 0 || (kTri == 1 ? k <= i : k >= i));
-            const int64_t p = d.coff + (ok ? (i >= k ? k : i) : 0);
-            const i64x2 cr = *reinterpret_cast<const i64x2*>(cr2 + 2 * p);  // (cbase[p], rbase[p])
-            m_cb[q] = cr.x;
-            m_rb[q] = cr.y;
-            m_q[q] = ok ? (i >= k ? i : k) : -1;
-        }
+    // element q of this thread: below the band (kk, ii) = (4 q + wave, lane),
+    // else (tid & 15, tid / 16 + 16 q)
+    const int ak = tid & 15, ai = tid >> 4;
+    const int iBelow = min(r0 + lane, c - 1);
+    const int64_t* map = cr2 + 2 * d.coff;
+    // Stages, each for one chunk; M: the chunk's mode where it is known, -1
+    // in the general form (which finds the mode out, a uniform branch).
+    i64x2 m_cr[4];          // stage MAP: (cbase[p], rbase[p])
+    const double* r_at[4];  // stage REL: S + cbase[p]
+    uint32_t r_rel[4];      //            rel entry
+    double v_a[2][4];       // stage VAL: A of two chunks (by the chunk's parity), B of one
+    d2u v_b[NP];
+    // the band's (i, k) of element q, clamped into C and the contraction
+    auto band_ik = [&](int k0, int q, int& i, int& k) {
+        i = min(r0 + ai + 16 * q, c - 1);
+        k = min(k0 + ak, Ke - 1);
     };
-    auto stage_r = [&]() {
+    auto load_map = [&](auto M, int ch) {
+        constexpr int kM = decltype(M)::value;
+        const int k0 = k_of(ch), md = kM >= 0 ? kM : mode_of(k0);
+        uint32_t off[4];
+        const int64_t* base = map;
+        if (md == kBelow) {
+            base += 2 * k0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            r_ok[q] = m_q[q] >= 0;
-            r_rel[q] = rel[m_rb[q] + (r_ok[q] ? m_q[q] : 0)];
-            r_cb[q] = m_cb[q];
-        }
-    };
-    auto stage_v = [&](int ch) {
-        av = along_of(ch);
+            for (int q = 0; q < 4; ++q) off[q] = (uint32_t)(4 * q + wave) * 16u;
+        } else if (md == kAbove) {
+            // row ai + 16 q of the tile (all rows are inside C here)
+            base += 2 * r0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v_a[q] = S[r_cb[q] + r_rel[q]];
-            v_ok[q] = r_ok[q];
-        }
-        // L_hat needs no mask: where k >= c the gathered A is zero, and
-        // columns past s are never written; a stand-in keeps the read in bounds
-        const int k0 = Kb + ch * TBK;
-        if constexpr (kPair) {
-            // rows k, k+1 of one column per load (c even: a pair never
-            // crosses the column's end)
-#pragma unroll
-            for (int q = 0; q < NB / 2; ++q) {
-                const int e = tid + q * kThreads;
-                const int k = k0 + 2 * (e & 7), jj = n0 + (e >> 3);
-                const bool ok = k < c && jj < s;
-                const d2u pr = *reinterpret_cast<const d2u*>(Bm + (ok ? k + (int64_t)jj * ldb : 0));
-                v_b[2 * q] = pr.x;
-                v_b[2 * q + 1] = pr.y;
-            }
+            for (int q = 0; q < 4; ++q) off[q] = (uint32_t)(ai + 16 * q) * 16u;
         } else {
 #pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                const int e = tid + q * kThreads;
-                const int k = k0 + (e & 15), jj = n0 + (e >> 4);
-                v_b[q] = Bm[(k < c && jj < s) ? k + (int64_t)jj * ldb : 0];
+            for (int q = 0; q < 4; ++q) {
+                int i, k;
+                band_ik(k0, q, i, k);
+                off[q] = (uint32_t)min(i, k) * 16u;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            m_cr[q] = *reinterpret_cast<const i64x2*>(reinterpret_cast<const char*>(base) + off[q]);
+    };
+    auto load_rel = [&](auto M, int ch) {
+        constexpr int kM = decltype(M)::value;
+        const int k0 = k_of(ch), md = kM >= 0 ? kM : mode_of(k0);
+        if (md == kBand) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                int i, k;
+                band_ik(k0, q, i, k);
+                r_rel[q] = (uint32_t)rel[m_cr[q].y + max(i, k)];
+            }
+        } else {  // one second index for all four elements
+            const int32_t* rq = rel + (md == kBelow ? iBelow : k0 + ak);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) r_rel[q] = (uint32_t)rq[m_cr[q].y];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r_at[q] = S + m_cr[q].x;
+    };
+    // B: pair bk of columns bj + 32 q, through a buffer descriptor (the
+    // chunk's offset is scalar; columns past s are out of its range and read 0)
+    const int bk = tid & 7, bj = tid >> 3;
+    const int64_t bytes = ((int64_t)(d.s - 1 - n0) * ldb + c) * (int64_t)sizeof(double);
+    const double* Bt = Bm + (int64_t)n0 * ldb;
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)Bt, 0, (int)(uint32_t)bytes, 0x00020000);
+    uint32_t boff[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+        boff[q] = (uint32_t)(((int64_t)(bj + 32 * q) * ldb + 2 * bk) * (int64_t)sizeof(double));
+    auto load_b = [&](auto M, int ch) {
+        constexpr int kM = decltype(M)::value;
+        const int k0 = k_of(ch);
+        if (kM >= 0 || k0 + TBK <= Ke) {
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+                v_b[q] = __builtin_bit_cast(
+                    d2u, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)boff[q], k0 * (int)sizeof(double), 0));
+        } else {  // ragged end: rows past Ke - 1 read that row (A is zero there)
+#pragma unroll
+            for (int q = 0; q < NP; ++q) {
+                const double* col = Bm + (int64_t)min(n0 + bj + 32 * q, d.s - 1) * ldb;
+                v_b[q].x = col[min(k0 + 2 * bk, Ke - 1)];
+                v_b[q].y = col[min(k0 + 2 * bk + 1, Ke - 1)];
             }
         }
     };
-    auto stage_store = [&](int buf) {
+    // LDS byte offsets: row * 128 + ((k / 2) ^ (row / 2 mod 8)) * 16 + (k mod 2) * 8
+    auto at = [](int row, int k) { return row * kGatherRow + (((k >> 1) ^ ((row >> 1) & 7)) << 4) + (k & 1) * 8; };
+    const int wAbove = at(ai, ak), wB = at(bj, 2 * bk);
+    int wBelow[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + q * kThreads;
-            const double x = v_ok[q] ? v_a[q] : 0.0;
-            const int row = av ? (e & 15) : (e >> 6), col = av ? (e >> 4) : (e & 63);
-            L.A[buf][row][col] = x;
-        }
-        if constexpr (kPair) {
+    for (int q = 0; q < 4; ++q) wBelow[q] = at(lane, 4 * q + wave);
+    auto store = [&](auto M, const double (&va)[4], int ch, int buf) {
+        constexpr int kM = decltype(M)::value;
+        const int k0 = k_of(ch), md = kM >= 0 ? kM : mode_of(k0);
+        char* A = L.A[buf];
+        if (md == kBelow) {
 #pragma unroll
-            for (int q = 0; q < NB / 2; ++q) {
-                const int e = tid + q * kThreads;
-                L.B[buf][2 * (e & 7)][e >> 3] = v_b[2 * q];
-                L.B[buf][2 * (e & 7) + 1][e >> 3] = v_b[2 * q + 1];
-            }
+            for (int q = 0; q < 4; ++q) *reinterpret_cast<double*>(A + wBelow[q]) = va[q];
+        } else if (md == kAbove) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *reinterpret_cast<double*>(A + wAbove + q * 16 * kGatherRow) = va[q];
         } else {
+            const int kr = k0 + ak;
 #pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                const int e = tid + q * kThreads;
-                L.B[buf][e & 15][e >> 4] = v_b[q];
+            for (int q = 0; q < 4; ++q) {
+                const int ir = r0 + ai + 16 * q;
+                const bool ok = kr < Ke && (kTri == 0 || (kTri == 1 ? kr <= ir : kr >= ir));
+                *reinterpret_cast<double*>(A + wAbove + q * 16 * kGatherRow) = ok ? va[q] : 0.0;
             }
         }
+        char* B = L.B[buf];
+        if (BN >= 32 || wave < 2) {
+#pragma unroll
+            for (int q = 0; q < NP; ++q) *reinterpret_cast<d2*>(B + wB + q * 32 * kGatherRow) = d2{v_b[q].x, v_b[q].y};
+        }
     };
-    // prologue: chunk 0 in LDS, chunk 1 values, chunk 2 offsets, chunk 3
-    // (cbase, rbase).  Chunks past the end are all padding: the stages run
-    // for them anyway, so the loop body has no branches.
-    stage_m(0);
-    stage_r();
-    stage_v(0);
-    stage_store(0);
-    stage_m(1);
-    stage_r();
-    stage_v(1);
-    stage_m(2);
-    stage_r();
-    stage_m(3);
-    __syncthreads();
-    for (int ch = 0; ch < nch; ++ch) {
-        const int buf = ch & 1;
+    // fragment rows: wm0, wn0 and 16 mt are multiples of 16, so one slot per
+    // lane and half chunk serves every fragment
+    const int fr = lane & 15, fg = lane >> 4;
+    const int f0 = at(fr, 2 * fg), f1 = at(fr, 8 + 2 * fg);
+    auto body = [&](auto M, auto X, int ch) {  // X: the parity of ch
+        constexpr int buf = decltype(X)::value;
+        const char *A = L.A[buf] + wm0 * kGatherRow, *B = L.B[buf] + wn0 * kGatherRow;
+        d2 a[SH::MT], b[SH::NT];
+        auto frags = [&](int f) {
 #pragma unroll
-        for (int ks = 0; ks < TBK / 4; ++ks) {
-            const int kr = ks * 4 + (lane >> 4);
-            double a[SH::MT], b[SH::NT];
+            for (int mt = 0; mt < SH::MT; ++mt) a[mt] = *reinterpret_cast<const d2*>(A + f + mt * 16 * kGatherRow);
 #pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt) a[mt] = L.A[buf][kr][wm0 + mt * 16 + (lane & 15)];
+            for (int nt = 0; nt < SH::NT; ++nt) b[nt] = *reinterpret_cast<const d2*>(B + f + nt * 16 * kGatherRow);
+        };
+        auto products = [&]() {
 #pragma unroll
-            for (int nt = 0; nt < SH::NT; ++nt) b[nt] = L.B[buf][kr][wn0 + nt * 16 + (lane & 15)];
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt)
+                for (int mt = 0; mt < SH::MT; ++mt)
 #pragma unroll
-                for (int nt = 0; nt < SH::NT; ++nt) acc[mt][nt] = mfma(b[nt], a[mt], acc[mt][nt]);
-        }
-        stage_store(buf ^ 1);
-        stage_v(ch + 2);
-        stage_r();
-        stage_m(ch + 4);
-        {
-            // one MFMA, then about five VALU and a share of the DS and
-            // global-memory operations (swept 3, 5, 8: 5 fastest, 22.85 ->
-            // 22.3 ms of gather-GEMM at 64^3)
-            constexpr int nm = (TBK / 4) * SH::MT * SH::NT, nr = (TBK / 4) * (SH::MT + SH::NT) / 2;
-            constexpr int nw = 4 + NB, nv = 12 + (kPair ? NB / 2 : NB);
-            sgb_interleave<nm, (SH::MT + SH::NT) / 2, nr - (SH::MT + SH::NT) / 2, nw, nv, 5>();
-        }
+                    for (int nt = 0; nt < SH::NT; ++nt) acc[mt][nt] = mfma(b[nt][h], a[mt][h], acc[mt][nt]);
+        };
+        frags(f0);
+        store(M, v_a[buf ^ 1], ch + 1, buf ^ 1);
+        // The loads stay ahead of the products (the scheduler would sink them
+        // to the end, in front of their own waits), and in this order: they
+        // return in order, so a wait on one waits for all before it, and the
+        // values of A, whose use is two iterations away, come last.
+        const double* at[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) at[q] = r_at[q] + r_rel[q];
+        load_rel(M, ch + 4);
+        load_map(M, ch + 5);
+        __builtin_amdgcn_sched_barrier(0);
+        load_b(M, ch + 2);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v_a[buf ^ 1][q] = *at[q];  // chunk ch + 3
+        __builtin_amdgcn_sched_barrier(0);
+        products();
+        frags(f1);
+        products();
         __syncthreads();
+    };
+    using Any = std::integral_constant<int, -1>;
+    using Below = std::integral_constant<int, kBelow>;
+    using Above = std::integral_constant<int, kAbove>;
+    using X0 = std::integral_constant<int, 0>;
+    using X1 = std::integral_constant<int, 1>;
+    {
+        // chunk 0 in LDS, A of chunks 1 and 2 and B of chunk 1, rel entries of
+        // chunk 3, pairs of chunk 4.  The first chunks' chains of loads run
+        // side by side, and the loads that stay in flight are issued in the
+        // loop's order (its waits count the loads behind the one they need).
+        i64x2 c[4][4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            load_map(Any{}, n);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[n][q] = m_cr[q];
+        }
+        const double* at3[3][4];
+        uint32_t re[3][4];
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) m_cr[q] = c[n][q];
+            load_rel(Any{}, n);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) at3[n][q] = r_at[q], re[n][q] = r_rel[q];
+        }
+        double a0[4];
+        d2u b0[NP];
+        load_b(Any{}, 0);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) b0[q] = v_b[q];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a0[q] = at3[0][q][re[0][q]];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v_a[1][q] = at3[1][q][re[1][q]];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m_cr[q] = c[3][q];
+        load_rel(Any{}, 3);
+        load_map(Any{}, 4);
+        __builtin_amdgcn_sched_barrier(0);
+        load_b(Any{}, 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v_a[0][q] = at3[2][q][re[2][q]];
+        __builtin_amdgcn_sched_barrier(0);
+        d2u b1[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) b1[q] = v_b[q], v_b[q] = b0[q];
+        store(Any{}, a0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < NP; ++q) v_b[q] = b1[q];
     }
+    __syncthreads();
+    // Iteration ch handles chunks ch + 1 (store) to ch + 5 (map): the mode is
+    // known where all of them lie on one side of the band and the last chunk,
+    // which is read again past the end, is whole.
+    const bool whole = ((Ke - Kb) & (TBK - 1)) == 0;
+    const int nb0 = max(0, min(r0 - Kb, Ke - Kb) / TBK);  // whole chunks below the band
+    const int belowEnd = kTri == 2 ? 0 : (whole && nb0 == nch ? nch : max(0, nb0 - 5));
+    const bool above = kTri != 1 && Kb + (nch - 1) * TBK >= r0 + TBM;  // the last chunk is
+    const int aboveBegin = above ? max(0, (r0 + TBM - Kb + TBK - 1) / TBK - 1) : nch;
+    const int aboveEnd = whole ? nch : max(0, (Ke - Kb) / TBK - 5);
+    int ch = 0;
+    auto run = [&](auto M, int end) {
+        if ((ch & 1) && ch < end) body(M, X1{}, ch++);
+        for (; ch + 1 < end; ch += 2) {
+            body(M, X0{}, ch);
+            body(M, X1{}, ch + 1);
+        }
+        if (ch < end) body(M, X0{}, ch++);
+    };
+    run(Below{}, belowEnd);
+    run(Any{}, aboveBegin);
+    run(Above{}, aboveEnd);
+    run(Any{}, nch);
     mfma_drain();
 }
 
-template <int BN, bool kPair = false>
-__device__ __forceinline__ void gemm_task(GemmLds& L, const Task t, const BlockDesc d, double* __restrict__ Ap,
+template <int BN, class LDS>
+__device__ __forceinline__ void gemm_task(LDS& L, const Task t, const BlockDesc d, double* __restrict__ Ap,
                           const double* __restrict__ Hp, const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
     const int r0 = t.i0, n0 = t.j0;
     d4 acc[2][4] = {};
-    gather_mma<BN, kPair, 0>(L, d, r0, n0, t.kb, t.ke, Ap, Hp + d.hoff, c, cr2, rel, acc);
+    gather_mma<BN, 0>(L, d, r0, n0, t.kb, t.ke, Ap, Hp + d.hoff, c, cr2, rel, acc);
     // transposed accumulation: stores and atomics run down the columns of X
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
@@ -752,18 +860,15 @@ __device__ __forceinline__ void gemm_task(GemmLds& L, const Task t, const BlockD
     });
 }
 
-__global__ __launch_bounds__(kThreads) void k_gemm(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
+__global__ __launch_bounds__(kThreads, 2) void k_gemm(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                    double* __restrict__ Ap, const double* __restrict__ Hp,
                                                    const int64_t* __restrict__ cr2,
                                                    const int32_t* __restrict__ rel)
 {
-    __shared__ GemmLds L;
+    __shared__ GatherLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
-    // even |C|: L_hat read two rows per load
-#define SELINV_CALL(BN)                                                \
-    if (BN >= 32 && (d.c & 1) == 0) gemm_task<BN, BN >= 32>(L, t, d, Ap, Hp, cr2, rel); \
-    else gemm_task<BN, false>(L, t, d, Ap, Hp, cr2, rel)
+#define SELINV_CALL(BN) gemm_task<BN>(L, t, d, Ap, Hp, cr2, rel)
     SELINV_BN_DISPATCH(t.bn, SELINV_CALL)
 #undef SELINV_CALL
 }
@@ -2174,6 +2279,7 @@ template <int NB>  // the widest diagonal block (16 NB; inversion kernels: none,
 union PersistLds {
     TileLds tile;
     GemmLds gemm;
+    GatherLds gather;
     SdiagLds sd;
     DiagLds<NB> diag;
     SbLds sb[kThreads / 64];
@@ -2276,7 +2382,7 @@ __device__ __forceinline__ void panel_bounded(GemmLds& L, const Task& t, const B
 
 // gather-GEMM tile; the host keeps t.bn <= BNMAX in this variant's levels
 template <int BNMAX>
-__device__ __forceinline__ void gemm_bounded(GemmLds& L, const Task& t, const BlockDesc& d, double* Ap,
+__device__ __forceinline__ void gemm_bounded(GatherLds& L, const Task& t, const BlockDesc& d, double* Ap,
                                              const double* Hp, const int64_t* cr2,
                                              const int32_t* rel)
 {
@@ -2411,7 +2517,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_persist_invert(const QueueArgs 
                     zero_task(d, Ap, Tp);
                     break;
                 case qGemm:
-                    gemm_bounded<BNMAX>(sm.gemm, u, d, Ap, Hp, cr2, rel);
+                    gemm_bounded<BNMAX>(sm.gather, u, d, Ap, Hp, cr2, rel);
                     break;
                 default:
                     sdiag_task(sm.sd, u, d, Ap, Hp, Tp);
@@ -2530,8 +2636,14 @@ __global__ __launch_bounds__(kThreads) void k_rs1(const Task* __restrict__ tasks
 #undef SELINV_CALL
 }
 
-template <int BN, bool kPair>
-__device__ void rs2_task(GemmLds& L, const Task t, const BlockDesc d, const double* __restrict__ Ap,
+// the gathered product, then a plain one
+union ReverseLds {
+    GatherLds g;
+    TileLds t;
+};
+
+template <int BN>
+__device__ void rs2_task(ReverseLds& L, const Task t, const BlockDesc d, const double* __restrict__ Ap,
                          const double* __restrict__ Zb, double* __restrict__ Hb, const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
     const int s = d.s, c = d.c;
@@ -2540,7 +2652,7 @@ __device__ void rs2_task(GemmLds& L, const Task t, const BlockDesc d, const doub
     const double* Zd = Zb + d.poff;
     d4 acc[2][4] = {};
     // G Xbar: G gathered from the inverse panels, Xbar = Zbar(C,B)
-    gather_mma<BN, kPair, 0>(L, d, r0, n0, t.kb, t.ke, Ap, Zb + d.poff + s, ld, cr2, rel, acc);
+    gather_mma<BN, 0>(L.g, d, r0, n0, t.kb, t.ke, Ap, Zb + d.poff + s, ld, cr2, rel, acc);
     if (t.kb == 0) {  // -X Ybar, once per tile
         auto loadX = [&](int k0, int kk, int ii) -> double {
             const int i = r0 + ii, k = k0 + kk;
@@ -2550,7 +2662,7 @@ __device__ void rs2_task(GemmLds& L, const Task t, const BlockDesc d, const doub
             const int k = k0 + kk, jj = n0 + j;
             return (k < s && jj < s) ? ybar_at(Zd, ld, k, jj) : 0.0;
         };
-        tile_mma<BN>(reinterpret_cast<TileLds&>(L), 0, s, acc, loadX, loadY, [](int) { return false; });
+        tile_mma<BN>(L.t, 0, s, acc, loadX, loadY, [](int) { return false; });
     }
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
@@ -2561,16 +2673,14 @@ __device__ void rs2_task(GemmLds& L, const Task t, const BlockDesc d, const doub
     });
 }
 
-__global__ __launch_bounds__(kThreads) void k_rs2(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
+__global__ __launch_bounds__(kThreads, 2) void k_rs2(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                   const double* __restrict__ Ap, const double* __restrict__ Zb,
                                                   double* __restrict__ Hb, const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
-    __shared__ GemmLds L;
+    __shared__ ReverseLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
-#define SELINV_CALL(BN)                                                                        \
-    if (BN >= 32 && (d.c & 1) == 0) rs2_task<BN, BN >= 32>(L, t, d, Ap, Zb, Hb, cr2, rel); \
-    else rs2_task<BN, false>(L, t, d, Ap, Zb, Hb, cr2, rel)
+#define SELINV_CALL(BN) rs2_task<BN>(L, t, d, Ap, Zb, Hb, cr2, rel)
     SELINV_BN_DISPATCH(t.bn, SELINV_CALL)
 #undef SELINV_CALL
 }
@@ -2625,8 +2735,8 @@ __global__ void k_tbar_init(const Task* __restrict__ tasks, const BlockDesc* __r
 }
 
 // Lhat_bar += Ubar F(C,B), Ubar(i,k) = -Fbar(C[i],C[k]) for i >= k
-template <int BN, bool kPair>
-__device__ void rf1a_task(GemmLds& L, const Task t, const BlockDesc d, const double* __restrict__ Zb,
+template <int BN>
+__device__ void rf1a_task(ReverseLds& L, const Task t, const BlockDesc d, const double* __restrict__ Zb,
                           const double* __restrict__ Lp, double* __restrict__ Hb, const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
     const int s = d.s, c = d.c;
@@ -2634,7 +2744,7 @@ __device__ void rf1a_task(GemmLds& L, const Task t, const BlockDesc d, const dou
     const int r0 = t.i0, n0 = t.j0;
     d4 acc[2][4] = {};
     // Ubar(i,k) = -Fbar(C[i],C[k]) for k <= i, gathered from the adjoint panels; B = F(C,B)
-    gather_mma<BN, kPair, 1>(L, d, r0, n0, t.kb, t.ke, Zb, Lp + d.poff + s, ld, cr2, rel, acc);
+    gather_mma<BN, 1>(L.g, d, r0, n0, t.kb, t.ke, Zb, Lp + d.poff + s, ld, cr2, rel, acc);
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
         if (ii < c && jj < s) {
@@ -2644,24 +2754,22 @@ __device__ void rf1a_task(GemmLds& L, const Task t, const BlockDesc d, const dou
     });
 }
 
-__global__ __launch_bounds__(kThreads) void k_rf1a(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
+__global__ __launch_bounds__(kThreads, 2) void k_rf1a(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                    const double* __restrict__ Zb, const double* __restrict__ Lp,
                                                    double* __restrict__ Hb, const int64_t* __restrict__ cr2,
                                                    const int32_t* __restrict__ rel)
 {
-    __shared__ GemmLds L;
+    __shared__ ReverseLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
-#define SELINV_CALL(BN)                                                                         \
-    if (BN >= 32 && (d.c & 1) == 0) rf1a_task<BN, BN >= 32>(L, t, d, Zb, Lp, Hb, cr2, rel); \
-    else rf1a_task<BN, false>(L, t, d, Zb, Lp, Hb, cr2, rel)
+#define SELINV_CALL(BN) rf1a_task<BN>(L, t, d, Zb, Lp, Hb, cr2, rel)
     SELINV_BN_DISPATCH(t.bn, SELINV_CALL)
 #undef SELINV_CALL
 }
 
 // Fbar(C,B) = Ubar^T L_hat (+ Lhat_bar T on piece 0), Ubar^T(i,k) = -Fbar(C[k],C[i]) for k >= i
-template <int BN, bool kPair>
-__device__ void rf1b_task(GemmLds& L, const Task t, const BlockDesc d, double* __restrict__ Zb,
+template <int BN>
+__device__ void rf1b_task(ReverseLds& L, const Task t, const BlockDesc d, double* __restrict__ Zb,
                           const double* __restrict__ Hp, const double* __restrict__ Hb, const double* __restrict__ Tp,
                           const int64_t* __restrict__ cr2,
                           const int32_t* __restrict__ rel)
@@ -2671,7 +2779,7 @@ __device__ void rf1b_task(GemmLds& L, const Task t, const BlockDesc d, double* _
     const int r0 = t.i0, n0 = t.j0;
     d4 acc[2][4] = {};
     // -Ubar^T L_hat: Fbar(C[k],C[i]) for k >= i, gathered from the adjoint panels
-    gather_mma<BN, kPair, 2>(L, d, r0, n0, t.kb, t.ke, Zb, Hp + d.hoff, c, cr2, rel, acc);
+    gather_mma<BN, 2>(L.g, d, r0, n0, t.kb, t.ke, Zb, Hp + d.hoff, c, cr2, rel, acc);
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
@@ -2685,7 +2793,7 @@ __device__ void rf1b_task(GemmLds& L, const Task t, const BlockDesc d, double* _
             const int k = k0 + kk, jj = n0 + j;
             return (k < s && jj < s) ? Tp[d.woff + k + (int64_t)jj * s] : 0.0;
         };
-        tile_mma<BN>(reinterpret_cast<TileLds&>(L), 0, s, acc, loadA2, loadB2, [](int) { return false; });
+        tile_mma<BN>(L.t, 0, s, acc, loadA2, loadB2, [](int) { return false; });
     }
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
@@ -2696,18 +2804,16 @@ __device__ void rf1b_task(GemmLds& L, const Task t, const BlockDesc d, double* _
     });
 }
 
-__global__ __launch_bounds__(kThreads) void k_rf1b(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
+__global__ __launch_bounds__(kThreads, 2) void k_rf1b(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                    double* __restrict__ Zb, const double* __restrict__ Hp,
                                                    const double* __restrict__ Hb, const double* __restrict__ Tp,
                                                    const int64_t* __restrict__ cr2,
                                                    const int32_t* __restrict__ rel)
 {
-    __shared__ GemmLds L;
+    __shared__ ReverseLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
-#define SELINV_CALL(BN)                                                                             \
-    if (BN >= 32 && (d.c & 1) == 0) rf1b_task<BN, BN >= 32>(L, t, d, Zb, Hp, Hb, Tp, cr2, rel); \
-    else rf1b_task<BN, false>(L, t, d, Zb, Hp, Hb, Tp, cr2, rel)
+#define SELINV_CALL(BN) rf1b_task<BN>(L, t, d, Zb, Hp, Hb, Tp, cr2, rel)
     SELINV_BN_DISPATCH(t.bn, SELINV_CALL)
 #undef SELINV_CALL
 }

@@ -33,7 +33,7 @@ def _plan(m, **kw):
 
 @pytest.mark.parametrize("det", [False, True])
 @pytest.mark.parametrize("n,cap", [(1, 128), (15, 128), (16, 128), (17, 128), (33, 128), (65, 128), (127, 128),
-                                   (128, 128), (129, 128), (200, 37), (330, 100), (600, 128)])
+                                   (128, 128), (129, 128), (200, 37), (330, 100), (600, 128), (777, 100)])
 def test_dense_gradient(n, cap, det):
     import torch
     a, m = _dense(n, n)
@@ -59,7 +59,7 @@ def test_dense_gradient(n, cap, det):
 @pytest.mark.parametrize("run", ["levels", "persistent"])
 @pytest.mark.parametrize("n,cap", [(1, 128), (2, 128), (15, 128), (16, 128), (17, 128), (31, 128), (32, 128),
                                    (33, 128), (48, 128), (63, 128), (64, 128), (65, 128), (112, 128), (113, 128),
-                                   (127, 128), (128, 128), (129, 128), (90, 17), (135, 64), (250, 49), (385, 128)])
+                                   (127, 128), (128, 128), (129, 128), (90, 17), (135, 64), (250, 49), (385, 128), (777, 128), (1153, 96)])
 def test_dense_forward(n, cap, run):
     """Selected inverse and factor of chains of blocks of `cap` columns."""
     import torch
