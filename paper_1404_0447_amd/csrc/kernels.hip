@@ -874,11 +874,221 @@ __global__ __launch_bounds__(kThreads, 2) void k_gemm(const Task* __restrict__ t
 }
 
 // ---------------------------------------------------------------------------
+// The dense counterpart of the gather loop: acc += A B over the contraction
+// [Kb, Ke) for a 64 x BN tile, the same LDS rows and fragments, with operands
+// that lie in column-major arrays and are read through buffer descriptors, so
+// that a chunk's position is a scalar offset and no vector instruction forms
+// an address.  An operand row r (of A, or a column of B) holds its
+// contraction entry k at p[r + k ld] (kAlongK false: lanes run along the
+// rows) or at p[k + r ld] (kAlongK true: lanes take pairs along k).
+//  * Rows past the operand's end read what follows in the array; their
+//    products are never stored.
+//  * Contraction entries past Ke: operands along the rows must end there (the
+//    descriptor then returns 0); with operands along k a ragged last chunk
+//    reads the last entry again and A is masked.
+// Loads are issued two chunks ahead.  kT: accumulate transposed.
+// ---------------------------------------------------------------------------
+struct Operand {
+    __amdgpu_buffer_rsrc_t rsrc;
+    const double* p;
+    uint32_t ld8;  // bytes between columns
+};
+
+// p[0 .. count), columns ld apart
+__device__ __forceinline__ Operand operand(const double* p, int64_t count, int64_t ld)
+{
+    return {__builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)(uint32_t)(max(count, (int64_t)0) * 8), 0x00020000), p,
+            (uint32_t)(ld * 8)};
+}
+
+__device__ __forceinline__ double buffer_f64(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
+{
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
+}
+
+// One operand of NR rows: what a thread loads of a chunk, and where it goes
+template <int NR, bool kAlongK>
+struct DenseLoader {
+    static constexpr int NQ = kAlongK ? (NR >= 32 ? NR / 32 : 1) : NR / 16;  // loads per thread
+    static constexpr int KS = kAlongK ? 0 : 16 / NQ;                         // k step between them
+    static constexpr int NV = kAlongK ? 2 * NQ : NQ;                         // values
+    Operand o;
+    uint32_t voff;
+    int wpart, kp, wr[kAlongK ? 1 : NQ];
+    bool on;
+
+    __device__ __forceinline__ DenseLoader(const Operand& op, int wave) : o(op)
+    {
+        const int tid = threadIdx.x, lane = tid & 63;
+        auto at = [](int row, int k) {
+            return row * kGatherRow + (((k >> 1) ^ ((row >> 1) & 7)) << 4) + (k & 1) * 8;
+        };
+        if constexpr (kAlongK) {
+            kp = tid & 7;
+            const int row = tid >> 3;
+            voff = (uint32_t)row * o.ld8 + (uint32_t)kp * 16u;
+            wr[0] = at(row, 2 * kp);
+            on = NR >= 32 || wave < 2;
+            wpart = 0;
+        } else {
+            constexpr int RW = NR < 64 ? NR : 64;  // rows a wave covers
+            const int row = NR == 128 ? (wave & 1) * 64 + lane : lane % RW;
+            const int kl = lane / RW;  // k within the wave
+            wpart = NR == 128 ? wave >> 1 : wave * (64 / RW);
+            voff = (uint32_t)row * 8u + (uint32_t)kl * o.ld8;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) wr[q] = at(row, q * KS + wpart + kl);
+            kp = 0;
+            on = true;
+        }
+    }
+    // the chunk at k0; ragged: it passes Ke (along k only)
+    __device__ __forceinline__ void load(double (&v)[NV], int k0, bool ragged, int Ke) const
+    {
+        if constexpr (kAlongK) {
+            if (!ragged) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    const d2u x = __builtin_bit_cast(
+                        d2u, __builtin_amdgcn_raw_buffer_load_b128(o.rsrc, (int)(voff + q * 32 * o.ld8), k0 * 8, 0));
+                    v[2 * q] = x.x;
+                    v[2 * q + 1] = x.y;
+                }
+            } else {
+                const int e = Ke - 1 - k0, x0 = (min(2 * kp, e) - 2 * kp) * 8, x1 = (min(2 * kp + 1, e) - 2 * kp) * 8;
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    v[2 * q] = buffer_f64(o.rsrc, voff + q * 32 * o.ld8 + k0 * 8 + x0, 0);
+                    v[2 * q + 1] = buffer_f64(o.rsrc, voff + q * 32 * o.ld8 + k0 * 8 + x1, 0);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) v[q] = buffer_f64(o.rsrc, voff, (uint32_t)(k0 + q * KS + wpart) * o.ld8);
+        }
+    }
+    // mask: zero the entries past Ke (A of a ragged chunk along k)
+    __device__ __forceinline__ void store(char* lds, const double (&v)[NV], int k0, bool mask, int Ke) const
+    {
+        if constexpr (kAlongK) {
+            if (on) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    d2 x = {v[2 * q], v[2 * q + 1]};
+                    if (mask) {
+                        x.x = k0 + 2 * kp < Ke ? x.x : 0.0;
+                        x.y = k0 + 2 * kp + 1 < Ke ? x.y : 0.0;
+                    }
+                    *reinterpret_cast<d2*>(lds + wr[0] + q * 32 * kGatherRow) = x;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) *reinterpret_cast<double*>(lds + wr[q]) = v[q];
+        }
+    }
+};
+
+template <int BN, bool kAk, bool kBk, bool kT, class LDS, class FH>
+__device__ __forceinline__ void dense_mma(LDS& L, const Operand& opA, const Operand& opB, int Kb, int Ke,
+                                          d4 (&acc)[2][4], FH afterPrologue)
+{
+    using SH = TileShape<BN>;
+    static_assert(sizeof(L.B[0]) >= BN * kGatherRow, "the LDS tile holds BN columns");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int wm0 = (wave % SH::WM) * (TBM / SH::WM), wn0 = (wave / SH::WM) * (BN / SH::WN);
+    const int nch = Ke > Kb ? (Ke - Kb + TBK - 1) / TBK : 0;
+    const DenseLoader<TBM, kAk> la(opA, wave);
+    const DenseLoader<BN, kBk> lb(opB, wave);
+    using LA = DenseLoader<TBM, kAk>;
+    using LB = DenseLoader<BN, kBk>;
+    double va[2][LA::NV], vb[2][LB::NV];  // by the chunk's parity
+    auto k_of = [&](int ch) { return Kb + min(ch, nch - 1) * TBK; };
+    auto load = [&](double (&a)[LA::NV], double (&b)[LB::NV], int ch) {
+        const int k0 = k_of(ch);
+        const bool ragged = (kAk || kBk) && k0 + TBK > Ke;
+        la.load(a, k0, ragged, Ke);
+        lb.load(b, k0, ragged, Ke);
+    };
+    auto store = [&](const double (&a)[LA::NV], const double (&b)[LB::NV], int ch, int buf) {
+        const int k0 = k_of(ch);
+        la.store(L.A[buf], a, k0, kAk && k0 + TBK > Ke, Ke);
+        lb.store(L.B[buf], b, k0, false, Ke);
+    };
+    const int fr = lane & 15, fg = lane >> 4, key = (fr >> 1) & 7;
+    const int f0 = fr * kGatherRow + ((fg ^ key) << 4), f1 = fr * kGatherRow + (((4 + fg) ^ key) << 4);
+    if (nch > 0) {
+        double a0[LA::NV], b0[LB::NV];
+        load(a0, b0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load(va[1], vb[1], 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load(va[0], vb[0], 2);
+        __builtin_amdgcn_sched_barrier(0);
+        store(a0, b0, 0, 0);
+    }
+    afterPrologue();  // loads of the caller's own that may run under the main loop
+    __syncthreads();
+    auto body = [&](auto X, int ch) {  // X: the parity of ch
+        constexpr int buf = decltype(X)::value;
+        const char *A = L.A[buf] + wm0 * kGatherRow, *B = L.B[buf] + wn0 * kGatherRow;
+        d2 a[SH::MT], b[SH::NT];
+        auto frags = [&](int f) {
+#pragma unroll
+            for (int mt = 0; mt < SH::MT; ++mt) a[mt] = *reinterpret_cast<const d2*>(A + f + mt * 16 * kGatherRow);
+#pragma unroll
+            for (int nt = 0; nt < SH::NT; ++nt) b[nt] = *reinterpret_cast<const d2*>(B + f + nt * 16 * kGatherRow);
+        };
+        auto products = [&]() {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int mt = 0; mt < SH::MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < SH::NT; ++nt)
+                        acc[mt][nt] = kT ? mfma(b[nt][h], a[mt][h], acc[mt][nt]) : mfma(a[mt][h], b[nt][h], acc[mt][nt]);
+        };
+        frags(f0);
+        store(va[buf ^ 1], vb[buf ^ 1], ch + 1, buf ^ 1);
+        load(va[buf ^ 1], vb[buf ^ 1], ch + 3);
+        __builtin_amdgcn_sched_barrier(0);
+        products();
+        frags(f1);
+        products();
+        __syncthreads();
+    };
+    int ch = 0;
+    for (; ch + 1 < nch; ch += 2) {
+        body(std::integral_constant<int, 0>{}, ch);
+        body(std::integral_constant<int, 1>{}, ch + 1);
+    }
+    if (ch < nch) body(std::integral_constant<int, 0>{}, ch);
+    mfma_drain();
+}
+
+// ---------------------------------------------------------------------------
 // Factor panel (Algorithm 1 step 2, fused into the factorization):
 // L_hat(C,B) = F(C,B) T for rows [i0, i0+64), columns [j0, j0+BN).
 // ---------------------------------------------------------------------------
-template <int BN, bool kDeep = false>
-__device__ __forceinline__ void panel_task(GemmLds& L, const Task t, const BlockDesc d, const double* __restrict__ Lp,
+union DeepLds {
+    GemmLds g;
+    GatherLds d;
+};
+
+// L_hat(i, j) = sum over k of F(i, k) T(j, k): T is symmetric, so both
+// operands lie along their rows
+template <int BN, class LDS>
+__device__ __forceinline__ void panel_product(LDS& L, const Task& t, const BlockDesc& d, const double* F,
+                                              const double* T, d4 (&acc)[2][4])
+{
+    const int s = d.s, c = d.c;
+    const int64_t ld = (int64_t)s + c;
+    dense_mma<BN, false, false, true>(L, operand(F + t.i0, (int64_t)(s - 1) * ld + c - t.i0, ld),
+                                      operand(T + t.j0, (int64_t)s * s - t.j0, s), 0, s, acc, [] {});
+}
+
+template <int BN, bool kDeep = false, class LDS>
+__device__ __forceinline__ void panel_task(LDS& L, const Task t, const BlockDesc d, const double* __restrict__ Lp,
                            double* __restrict__ Hp, const double* __restrict__ Tp)
 {
     const int s = d.s, c = d.c;
@@ -887,25 +1097,25 @@ __device__ __forceinline__ void panel_task(GemmLds& L, const Task t, const Block
     d4 acc[2][4] = {};
     const double* F = Lp + d.poff + s;
     const double* T = Tp + d.woff;
-    auto addrA = [&](int k0, int kk, int ii, bool& ok) -> const double* {
-        const int i = r0 + ii, k = k0 + kk;
-        ok = i < c && k < s;
-        return ok ? F + i + (int64_t)k * ld : F;
-    };
-    auto addrB = [&](int k0, int kk, int j, bool& ok) -> const double* {
-        const int k = k0 + kk, jj = n0 + j;
-        ok = k < s && jj < s;
-        return ok ? T + k + (int64_t)jj * s : T;
-    };
     if constexpr (kDeep) {
+        auto addrA = [&](int k0, int kk, int ii, bool& ok) -> const double* {
+            const int i = r0 + ii, k = k0 + kk;
+            ok = i < c && k < s;
+            return ok ? F + i + (int64_t)k * ld : F;
+        };
+        auto addrB = [&](int k0, int kk, int j, bool& ok) -> const double* {
+            const int k = k0 + kk, jj = n0 + j;
+            ok = k < s && jj < s;
+            return ok ? T + k + (int64_t)jj * s : T;
+        };
         // chunks of 16 the contraction s needs: 1, 2, 4 or 8 (s <= 128)
-        if (s <= 16) tile_mma_deep<BN, 1, false, true>(L, 0, s, acc, addrA, addrB, [] {});
-        else if (s <= 32) tile_mma_deep<BN, 2, false, true>(L, 0, s, acc, addrA, addrB, [] {});
-        else if (s <= 64) tile_mma_deep<BN, 4, false, true>(L, 0, s, acc, addrA, addrB, [] {});
-        else if (s <= kDeepK) tile_mma_deep<BN, 8, false, true>(L, 0, s, acc, addrA, addrB, [] {});
-        else tile_mma2<BN, false, true>(L, 0, s, acc, addrA, addrB, [](int) { return false; }, [] {});
+        if (s <= 16) tile_mma_deep<BN, 1, false, true>(L.g, 0, s, acc, addrA, addrB, [] {});
+        else if (s <= 32) tile_mma_deep<BN, 2, false, true>(L.g, 0, s, acc, addrA, addrB, [] {});
+        else if (s <= 64) tile_mma_deep<BN, 4, false, true>(L.g, 0, s, acc, addrA, addrB, [] {});
+        else if (s <= kDeepK) tile_mma_deep<BN, 8, false, true>(L.g, 0, s, acc, addrA, addrB, [] {});
+        else panel_product<BN>(L.d, t, d, F, T, acc);
     } else {
-        tile_mma2<BN, false, true>(L, 0, s, acc, addrA, addrB, [](int) { return false; }, [] {});
+        panel_product<BN>(L, t, d, F, T, acc);
     }
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
@@ -917,7 +1127,7 @@ __global__ __launch_bounds__(kThreads) void k_panel(const Task* __restrict__ tas
                                                     const BlockDesc* __restrict__ blk, const double* __restrict__ Lp,
                                                     double* __restrict__ Hp, const double* __restrict__ Tp)
 {
-    __shared__ GemmLds L;
+    __shared__ GatherLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
 #define SELINV_CALL(BN) panel_task<BN>(L, t, d, Lp, Hp, Tp)
@@ -932,7 +1142,7 @@ __global__ __launch_bounds__(kThreads) void k_panel_deep(const Task* __restrict_
                                                          const double* __restrict__ Lp, double* __restrict__ Hp,
                                                          const double* __restrict__ Tp)
 {
-    __shared__ GemmLds L;
+    __shared__ DeepLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
     switch (t.bn) {
@@ -956,11 +1166,18 @@ __global__ __launch_bounds__(kThreads) void k_panel_deep(const Task* __restrict_
 // sixteen columns.  The scatter targets do not depend on the product: their
 // (cbase, rbase) pairs are loaded before the main loop and the rel entries
 // right after its prologue, so the epilogue issues only the updates.
+//
+// Bounds at 64^3: the products (padding included) 5.7 ms of MFMA, the
+// read-modify-write of the targets 27 GB, 6 ms at the copy rate; without the
+// update of the targets the kernel takes 8.6 ms.  With about ten vector
+// instructions per MFMA (addresses and masks, which share the SIMD with FP64
+// MFMAs) it took 16.0 ms; the loop of dense_mma has none: 15.5, and 14.5
+// with three work-groups on a CU (four spill: 18.8).
 // ---------------------------------------------------------------------------
-template <bool kDeep = false>
-__device__ __forceinline__ void schur_task(GemmLds& L, const Task t, const BlockDesc d, double* __restrict__ Lp,
-                           const double* __restrict__ Hp, const int64_t* __restrict__ cbase,
-                           const int64_t* __restrict__ rbase, const int32_t* __restrict__ rel)
+template <bool kDeep = false, class LDS>
+__device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc d, double* __restrict__ Lp,
+                                           const double* __restrict__ Hp, const int64_t* __restrict__ cr2,
+                                           const int32_t* __restrict__ rel)
 {
     using SH = TileShape<64>;
     const int s = d.s, c = d.c;
@@ -971,71 +1188,94 @@ __device__ __forceinline__ void schur_task(GemmLds& L, const Task t, const Block
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm0 = (wave % SH::WM) * (TBM / SH::WM), wn0 = (wave / SH::WM) * (64 / SH::WN);
     // this thread's outputs (mt, nt, v): target column kk = k0 + wm0 + 16 mt +
-    // lane / 16 + 4 v, row ii = i0 + wn0 + 16 nt + lane % 16
+    // lane / 16 + 4 v, row ii = i0 + wn0 + 16 nt + lane % 16; past C's end and
+    // above the diagonal (never stored) the map is read at a valid place
     auto col_of = [&](int mt, int v) { return k0c + wm0 + mt * 16 + (lane >> 4) + 4 * v; };
     auto row_of = [&](int nt) { return i0 + wn0 + nt * 16 + (lane & 15); };
-    int64_t cb[SH::MT][4], rb[SH::MT][4];
+    // a tile strictly below the diagonal and inside C has every entry live
+    const bool full = i0 > k0c && i0 + TBM <= c;
+    i64x2 cr[SH::MT][4];  // (cbase, rbase) of the column
 #pragma unroll
     for (int mt = 0; mt < SH::MT; ++mt)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int kk = col_of(mt, v);
-            const int64_t pk = d.coff + (kk < c ? kk : 0);
-            cb[mt][v] = cbase[pk];
-            rb[mt][v] = rbase[pk];
-        }
-    int32_t ro[SH::MT][SH::NT][4];
-    auto live = [&](int mt, int nt, int v) {
-        const int ii = row_of(nt), kk = col_of(mt, v);
-        return ii < c && kk < c && ii >= kk;
-    };
+        for (int v = 0; v < 4; ++v)
+            cr[mt][v] = *reinterpret_cast<const i64x2*>(cr2 + 2 * (d.coff + min(col_of(mt, v), c - 1)));
+    uint32_t ro[SH::MT][SH::NT][4];
     auto prefetch = [&]() {
-#pragma unroll
-        for (int mt = 0; mt < SH::MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < SH::NT; ++nt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) ro[mt][nt][v] = rel[rb[mt][v] + (live(mt, nt, v) ? row_of(nt) : 0)];
-    };
-    d4 acc[2][4] = {};
-    // A(kk, t) = F(k0 + kk, t): contiguous along the tile rows
-    auto addrA = [&](int t0, int tt, int kk, bool& ok) -> const double* {
-        const int k = k0c + kk, col = t0 + tt;
-        ok = k < c && col < s;
-        return ok ? F + k + (int64_t)col * ld : F;
-    };
-    // B(t, ii) = L_hat(i0 + ii, t): contiguous in ii
-    auto addrB = [&](int t0, int tt, int ii, bool& ok) -> const double* {
-        const int i = i0 + ii, k = t0 + tt;
-        ok = i < c && k < s;
-        return ok ? H + i + (int64_t)k * c : H;
-    };
-    if constexpr (kDeep) {
-        if (s <= 16) tile_mma_deep<64, 1, true, false>(L, 0, s, acc, addrA, addrB, prefetch);
-        else if (s <= 32) tile_mma_deep<64, 2, true, false>(L, 0, s, acc, addrA, addrB, prefetch);
-        else if (s <= 64) tile_mma_deep<64, 4, true, false>(L, 0, s, acc, addrA, addrB, prefetch);
-        else if (s <= kDeepK) tile_mma_deep<64, 8, true, false>(L, 0, s, acc, addrA, addrB, prefetch);
-        else tile_mma2<64, true, false>(L, 0, s, acc, addrA, addrB, [](int) { return false; }, prefetch);
-    } else {
-        tile_mma2<64, true, false>(L, 0, s, acc, addrA, addrB, [](int) { return false; }, prefetch);
-    }
-    auto target = [&](int mt, int nt, int v) { return Lp + cb[mt][v] + ro[mt][nt][v]; };
-    // a tile strictly below the diagonal and inside C has every entry live:
-    // its updates are issued without per-entry branches, which would put a
-    // wait on all outstanding memory operations in front of every store
-    const bool full = i0 > k0c && i0 + TBM <= c;
-    if (t.flags & 4) {
-        // no other block of the level updates these entries: plain
-        // read-modify-write, all reads issued before the first write (the
-        // targets of one thread are distinct entries)
-        double old[SH::MT][SH::NT][4];
         if (full) {
+#pragma unroll
+            for (int nt = 0; nt < SH::NT; ++nt) {
+                const int32_t* rq = rel + row_of(nt);
+#pragma unroll
+                for (int mt = 0; mt < SH::MT; ++mt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) ro[mt][nt][v] = (uint32_t)rq[cr[mt][v].y];
+            }
+        } else {
 #pragma unroll
             for (int mt = 0; mt < SH::MT; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < SH::NT; ++nt)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) old[mt][nt][v] = *target(mt, nt, v);
+                    for (int v = 0; v < 4; ++v) {
+                        const int ii = min(max(row_of(nt), col_of(mt, v)), c - 1);
+                        ro[mt][nt][v] = (uint32_t)rel[cr[mt][v].y + ii];
+                    }
+        }
+    };
+    d4 acc[2][4] = {};
+    if constexpr (kDeep) {
+        // A(kk, t) = F(k0 + kk, t): contiguous along the tile rows
+        auto addrA = [&](int t0, int tt, int kk, bool& ok) -> const double* {
+            const int k = k0c + kk, col = t0 + tt;
+            ok = k < c && col < s;
+            return ok ? F + k + (int64_t)col * ld : F;
+        };
+        // B(t, ii) = L_hat(i0 + ii, t): contiguous in ii
+        auto addrB = [&](int t0, int tt, int ii, bool& ok) -> const double* {
+            const int i = i0 + ii, k = t0 + tt;
+            ok = i < c && k < s;
+            return ok ? H + i + (int64_t)k * c : H;
+        };
+        if (s <= 16) tile_mma_deep<64, 1, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
+        else if (s <= 32) tile_mma_deep<64, 2, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
+        else if (s <= 64) tile_mma_deep<64, 4, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
+        else if (s <= kDeepK) tile_mma_deep<64, 8, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
+    }
+    auto dense = [&](auto& W) {
+        dense_mma<64, false, false, false>(W, operand(F + k0c, (int64_t)(s - 1) * ld + c - k0c, ld),
+                                           operand(H + i0, (int64_t)s * c - i0, c), 0, s, acc, prefetch);
+    };
+    if constexpr (kDeep) {
+        if (s > kDeepK) dense(L.d);
+    } else {
+        dense(L);
+    }
+    double* base[SH::MT][4];
+#pragma unroll
+    for (int mt = 0; mt < SH::MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) base[mt][v] = Lp + cr[mt][v].x;
+    auto target = [&](int mt, int nt, int v) { return base[mt][v] + ro[mt][nt][v]; };
+    auto live = [&](int mt, int nt, int v) {
+        const int ii = row_of(nt), kk = col_of(mt, v);
+        return ii < c && ii >= kk;  // and so kk < c
+    };
+    // full tiles: no per-entry branches, which would put a wait on all
+    // outstanding memory operations in front of every store
+    if (t.flags & 4) {
+        // no other block of the level updates these entries: plain
+        // read-modify-write, all reads issued before the first write (the
+        // targets of one thread are distinct entries; those of entries not
+        // live are read, not written)
+        double old[SH::MT][SH::NT][4];
+#pragma unroll
+        for (int mt = 0; mt < SH::MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < SH::NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) old[mt][nt][v] = *target(mt, nt, v);
+        if (full) {
 #pragma unroll
             for (int mt = 0; mt < SH::MT; ++mt)
 #pragma unroll
@@ -1043,12 +1283,6 @@ __device__ __forceinline__ void schur_task(GemmLds& L, const Task t, const Block
 #pragma unroll
                     for (int v = 0; v < 4; ++v) *target(mt, nt, v) = old[mt][nt][v] - acc[mt][nt][v];
         } else {
-#pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < SH::NT; ++nt)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) old[mt][nt][v] = live(mt, nt, v) ? *target(mt, nt, v) : 0.0;
 #pragma unroll
             for (int mt = 0; mt < SH::MT; ++mt)
 #pragma unroll
@@ -1075,29 +1309,27 @@ __device__ __forceinline__ void schur_task(GemmLds& L, const Task t, const Block
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_schur(const Task* __restrict__ tasks,
+__global__ __launch_bounds__(kThreads, 3) void k_schur(const Task* __restrict__ tasks,
                                                     const BlockDesc* __restrict__ blk, double* __restrict__ Lp,
                                                     const double* __restrict__ Hp,
-                                                    const int64_t* __restrict__ cbase,
-                                                    const int64_t* __restrict__ rbase,
+                                                    const int64_t* __restrict__ cr2,
                                                     const int32_t* __restrict__ rel)
 {
-    __shared__ GemmLds L;
+    __shared__ GatherLdsN<64> L;
     const Task t = tasks[blockIdx.x];
-    schur_task(L, t, blk[t.b], Lp, Hp, cbase, rbase, rel);
+    schur_task(L, t, blk[t.b], Lp, Hp, cr2, rel);
 }
 
 // colour groups with few tiles: the contraction (s <= 128) loaded up front
 __global__ __launch_bounds__(kThreads) void k_schur_deep(const Task* __restrict__ tasks,
                                                          const BlockDesc* __restrict__ blk, double* __restrict__ Lp,
                                                          const double* __restrict__ Hp,
-                                                         const int64_t* __restrict__ cbase,
-                                                         const int64_t* __restrict__ rbase,
+                                                         const int64_t* __restrict__ cr2,
                                                          const int32_t* __restrict__ rel)
 {
-    __shared__ GemmLds L;
+    __shared__ DeepLds L;
     const Task t = tasks[blockIdx.x];
-    schur_task<true>(L, t, blk[t.b], Lp, Hp, cbase, rbase, rel);
+    schur_task<true>(L, t, blk[t.b], Lp, Hp, cr2, rel);
 }
 
 // ---------------------------------------------------------------------------
@@ -2367,7 +2599,7 @@ __device__ __forceinline__ void diag_block(const BlockDesc& d, double* Lp, doubl
 
 // L_hat tile; tiles are at most as wide as the level's widest block
 template <int NB>
-__device__ __forceinline__ void panel_bounded(GemmLds& L, const Task& t, const BlockDesc& d, const double* Lp,
+__device__ __forceinline__ void panel_bounded(GatherLds& L, const Task& t, const BlockDesc& d, const double* Lp,
                                               double* Hp, const double* Tp)
 {
     if (t.bn <= 16) {
@@ -2404,7 +2636,8 @@ __global__ __launch_bounds__(kThreads, NB < 8 ? 2 : 1) void k_persist_factor(con
                                                              double* __restrict__ Hp, double* __restrict__ Tp,
                                                              const int64_t* __restrict__ cbase,
                                                              const int64_t* __restrict__ rbase,
-                                                             const int32_t* __restrict__ rel)
+                                                             const int32_t* __restrict__ rel,
+                                                             const int64_t* __restrict__ cr2)
 {
     __shared__ PersistLds<NB> sm;
     __shared__ int s_idx;
@@ -2452,10 +2685,10 @@ __global__ __launch_bounds__(kThreads, NB < 8 ? 2 : 1) void k_persist_factor(con
                     diag_block<NB>(d, Lp, Wp, Tp, a.status, a.require_spd, sm.diag);
                     break;
                 case qPanel:
-                    panel_bounded<NB>(sm.gemm, u, d, Lp, Hp, Tp);
+                    panel_bounded<NB>(sm.gather, u, d, Lp, Hp, Tp);
                     break;
                 default:
-                    schur_task(sm.gemm, u, d, Lp, Hp, cbase, rbase, rel);
+                    schur_task(sm.gather, u, d, Lp, Hp, cr2, rel);
                     break;
             }
             if (whole) __syncthreads();
@@ -3138,7 +3371,7 @@ hipError_t launch_schur_groups(Prof* P, const DevPtrs& D, const int64_t* cuts, i
         const int64_t n = cuts[g + 1] - cuts[g];
         if (n > 0)
             launch(P, kSchur, (panel_deep & 2) && n <= kDeepMaxTiles ? k_schur_deep : k_schur, dim3((unsigned)n), 0, s,
-                   D.t_schur + cuts[g], D.blocks, D.Lp, (const double*)D.Hp, D.cbase, D.rbase, D.rel);
+                   D.t_schur + cuts[g], D.blocks, D.Lp, (const double*)D.Hp, D.cr2, D.rel);
     }
     return hipGetLastError();
 }
@@ -3186,7 +3419,7 @@ hipError_t launch_persist_factor(Prof* P, const DevPtrs& D, const Task* q, int64
     if (ntasks <= 0) return hipSuccess;
     const QueueArgs a{q, ntasks, head, done, D.status, require_spd, spin_limit};
     const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(grid, ntasks));
-#define SELINV_PF(K) launch(P, kQFactor, K, dim3(g), 0, s, a, D.blocks, D.Lp, D.Wp, D.Hp, D.Tp, D.cbase, D.rbase, D.rel)
+#define SELINV_PF(K) launch(P, kQFactor, K, dim3(g), 0, s, a, D.blocks, D.Lp, D.Wp, D.Hp, D.Tp, D.cbase, D.rbase, D.rel, D.cr2)
     switch (variant) {
         case kLightFactor:
             launch(P, kQFactor, k_light_factor, dim3(g), 0, s, a, D.blocks, D.Lp, D.Hp, D.Tp, D.cbase, D.rbase, D.rel);
