@@ -654,11 +654,12 @@ selinv_status selinv_backward(selinv_plan P, const double* d_gsel, double* d_gA,
         const auto& a = P->t_rs1.off;
         const auto& b = P->t_rs2.off;
         const auto& cut = P->rs3_cuts[l];
+        const auto& d = P->t_diag.off;
         e = launch_revsel_level(&P->prof, D, a[l], a[l + 1] - a[l], b[l], b[l + 1] - b[l], cut.data(), (int)cut.size(),
-                                s);
+                                d[l], d[l + 1] - d[l], P->diag_smax[l], s);
         if (e) return hip_fail(e, "reverse inversion launch");
     }
-    e = launch_revfac_init(&P->prof, D, (int64_t)P->t_diag.tasks.size(), P->arena, s);
+    e = launch_revfac_init(&P->prof, D, P->arena, s);
     if (e) return hip_fail(e, "reverse factor setup");
     // reverse factorization: root first
     for (int l = 0; l < depth; l++) {

@@ -164,20 +164,10 @@ __global__ void k_export_L(const BlockDesc* __restrict__ blk, const int32_t* __r
 }
 
 // ---------------------------------------------------------------------------
-// Generic 64 x BN MFMA tile: acc += A(64 x K) B(K x BN), K streamed in
-// chunks of 16 through LDS, accumulated transposed (read it with
-// tile_epilogue_t).  loadA(k0, kk, i) -> A(i, k0+kk) and
-// loadB(k0, kk, j) -> B(k0+kk, j).  The A loads run with consecutive threads
-// along i, or along kk for chunks where chunkAlongK(k0) holds (contiguous
-// in k).  Four waves: BN >= 64 -> 2 x 2 waves of 32 x BN/2, else 4 x 1 waves
-// of 16 x BN.
+// 64 x BN MFMA tiles, four waves: BN >= 64 -> 2 x 2 waves of 32 x BN/2, else
+// 4 x 1 waves of 16 x BN; contractions in chunks of 16.
 // ---------------------------------------------------------------------------
 constexpr int TBM = 64, TBK = 16, TPAD = 4;
-
-struct TileLds {
-    double A[TBK][TBM + TPAD];
-    double B[TBK][128 + TPAD];
-};
 
 template <int BN>
 struct TileShape {
@@ -186,79 +176,6 @@ struct TileShape {
     static constexpr int MT = TBM / WM / 16;
     static constexpr int NT = BN / WN / 16;
 };
-
-template <int BN, class FA, class FB, class FAK>
-__device__ __forceinline__ void tile_mma(TileLds& L, int Kb, int Ke, d4 (&acc)[2][4], FA loadA, FB loadB,
-                                         FAK chunkAlongK)
-{
-    using SH = TileShape<BN>;
-    constexpr int NB = BN / 16;  // B elements per thread per chunk
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm0 = (wave % SH::WM) * (TBM / SH::WM), wn0 = (wave / SH::WM) * (BN / SH::WN);
-    // the next chunk is fetched into registers while the current one feeds
-    // the MFMAs, so gather latency overlaps the products
-    double ra[4], rb[NB];
-    bool along = false;
-    auto fetch = [&](int k0) {
-        along = chunkAlongK(k0);
-        if (along) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int e = threadIdx.x + q * kThreads;
-                ra[q] = loadA(k0, e & 15, e >> 4);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int e = threadIdx.x + q * kThreads;
-                ra[q] = loadA(k0, e >> 6, e & 63);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int e = threadIdx.x + q * kThreads;
-            rb[q] = loadB(k0, e & 15, e >> 4);
-        }
-    };
-    if (Kb < Ke) fetch(Kb);
-    for (int k0 = Kb; k0 < Ke; k0 += TBK) {
-        if (along) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int e = threadIdx.x + q * kThreads;
-                L.A[e & 15][e >> 4] = ra[q];
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int e = threadIdx.x + q * kThreads;
-                L.A[e >> 6][e & 63] = ra[q];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int e = threadIdx.x + q * kThreads;
-            L.B[e & 15][e >> 4] = rb[q];
-        }
-        __syncthreads();
-        if (k0 + TBK < Ke) fetch(k0 + TBK);
-#pragma unroll
-        for (int ks = 0; ks < TBK / 4; ++ks) {
-            const int kr = ks * 4 + (lane >> 4);
-            double a[SH::MT], b[SH::NT];
-#pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt) a[mt] = L.A[kr][wm0 + mt * 16 + (lane & 15)];
-#pragma unroll
-            for (int nt = 0; nt < SH::NT; ++nt) b[nt] = L.B[kr][wn0 + nt * 16 + (lane & 15)];
-#pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < SH::NT; ++nt) acc[mt][nt] = mfma(b[nt], a[mt], acc[mt][nt]);
-        }
-        __syncthreads();
-    }
-    mfma_drain();
-}
 
 // Visit every element f(i, j, value) (tile-local i, j) of a tile whose
 // MFMAs ran with their operands swapped: mfma(b, a) forms the transposed
@@ -281,173 +198,23 @@ __device__ __forceinline__ void tile_epilogue_t(const d4 (&acc)[2][4], F f)
                 f(wm0 + mt * 16 + (lane & 15), wn0 + nt * 16 + (lane >> 4) + 4 * v, acc[mt][nt][v]);
 }
 
-// ---------------------------------------------------------------------------
-// Pipelined 64 x BN MFMA tile: acc += A(64 x K) B(K x BN) over 16-deep
-// chunks, LDS double-buffered with one barrier per chunk.  While the MFMAs
-// consume chunk n, chunk n+1's values (loaded an iteration earlier) go to
-// the other buffer, chunk n+2's values are loaded from the addresses found
-// an iteration earlier, and chunk n+3's addresses are formed.  Loads are
-// unconditional: addrA(k0, kk, ii, ok) / addrB(k0, kk, j, ok) return an
-// in-bounds stand-in when !ok, and the mask is applied at the LDS store.
-// A chunk is read along k (contiguous in k) where alongA(k0) holds, else
-// along i; B along j (kBJ: B(k, j) contiguous in j) or along k.
-// ---------------------------------------------------------------------------
 struct GemmLds {
     double A[2][TBK][TBM + TPAD];
     double B[2][TBK][128 + TPAD];
 };
 
-template <int BN, bool kBJ, bool kT, bool kPairK = false, class FA, class FB, class FAK, class FH>
-__device__ __forceinline__ void tile_mma2(GemmLds& L, int Kb, int Ke, d4 (&acc)[2][4], FA addrA, FB addrB,
-                                          FAK alongA, FH afterPrologue)
-{
-    using SH = TileShape<BN>;
-    constexpr int NB = BN / 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave % SH::WM) * (TBM / SH::WM), wn0 = (wave / SH::WM) * (BN / SH::WN);
-    const int nch = Ke > Kb ? (Ke - Kb + TBK - 1) / TBK : 0;
-    const double *pa[4], *pb[NB];  // stage ADDR
-    bool oka[4], okb[NB], ala = false;
-    double va[4], vb[NB];          // stage VAL
-    bool vka[4], vkb[NB], vla = false;
-    // kPairK (both operands read along k, kBJ false, every chunk along k):
-    // rows k, k+1 of one column per load, the caller guaranteeing that a
-    // pair never straddles the end of the contraction
-    auto stage_addr = [&](int ch) {
-        const int k0 = Kb + ch * TBK;
-        const bool past = ch >= nch;
-        ala = alongA(k0);
-        if constexpr (kPairK) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int e = tid + q * kThreads;
-                pa[q] = addrA(k0, 2 * (e & 7), e >> 3, oka[q]);
-                oka[q] = oka[q] && !past;
-            }
-#pragma unroll
-            for (int q = 0; q < NB / 2; ++q) {
-                const int e = tid + q * kThreads;
-                pb[q] = addrB(k0, 2 * (e & 7), e >> 3, okb[q]);
-                okb[q] = okb[q] && !past;
-            }
-            return;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + q * kThreads;
-            const int kk = ala ? (e & 15) : (e >> 6), ii = ala ? (e >> 4) : (e & 63);
-            pa[q] = addrA(k0, kk, ii, oka[q]);
-            oka[q] = oka[q] && !past;
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int e = tid + q * kThreads;
-            const int kk = kBJ ? e / BN : (e & 15), j = kBJ ? e % BN : (e >> 4);
-            pb[q] = addrB(k0, kk, j, okb[q]);
-            okb[q] = okb[q] && !past;
-        }
-    };
-    auto stage_val = [&]() {
-        vla = ala;
-        if constexpr (kPairK) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const d2u x = *reinterpret_cast<const d2u*>(pa[q]);
-                va[2 * q] = x.x;
-                va[2 * q + 1] = x.y;
-                vka[q] = oka[q];
-            }
-#pragma unroll
-            for (int q = 0; q < NB / 2; ++q) {
-                const d2u x = *reinterpret_cast<const d2u*>(pb[q]);
-                vb[2 * q] = x.x;
-                vb[2 * q + 1] = x.y;
-                vkb[q] = okb[q];
-            }
-            return;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            va[q] = *pa[q];
-            vka[q] = oka[q];
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            vb[q] = *pb[q];
-            vkb[q] = okb[q];
-        }
-    };
-    auto stage_store = [&](int buf) {
-        if constexpr (kPairK) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int e = tid + q * kThreads;
-                L.A[buf][2 * (e & 7)][e >> 3] = vka[q] ? va[2 * q] : 0.0;
-                L.A[buf][2 * (e & 7) + 1][e >> 3] = vka[q] ? va[2 * q + 1] : 0.0;
-            }
-#pragma unroll
-            for (int q = 0; q < NB / 2; ++q) {
-                const int e = tid + q * kThreads;
-                L.B[buf][2 * (e & 7)][e >> 3] = vkb[q] ? vb[2 * q] : 0.0;
-                L.B[buf][2 * (e & 7) + 1][e >> 3] = vkb[q] ? vb[2 * q + 1] : 0.0;
-            }
-            return;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + q * kThreads;
-            const int kk = vla ? (e & 15) : (e >> 6), ii = vla ? (e >> 4) : (e & 63);
-            L.A[buf][kk][ii] = vka[q] ? va[q] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int e = tid + q * kThreads;
-            const int kk = kBJ ? e / BN : (e & 15), j = kBJ ? e % BN : (e >> 4);
-            L.B[buf][kk][j] = vkb[q] ? vb[q] : 0.0;
-        }
-    };
-    stage_addr(0);
-    stage_val();
-    stage_store(0);
-    stage_addr(1);
-    stage_val();
-    stage_addr(2);
-    afterPrologue();  // loads of the caller's own that may run under the main loop
-    __syncthreads();
-    for (int ch = 0; ch < nch; ++ch) {
-        const int buf = ch & 1;
-#pragma unroll
-        for (int ks = 0; ks < TBK / 4; ++ks) {
-            const int kr = ks * 4 + (lane >> 4);
-            double a[SH::MT], b[SH::NT];
-#pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt) a[mt] = L.A[buf][kr][wm0 + mt * 16 + (lane & 15)];
-#pragma unroll
-            for (int nt = 0; nt < SH::NT; ++nt) b[nt] = L.B[buf][kr][wn0 + nt * 16 + (lane & 15)];
-#pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < SH::NT; ++nt)
-                    acc[mt][nt] = kT ? mfma(b[nt], a[mt], acc[mt][nt]) : mfma(a[mt], b[nt], acc[mt][nt]);
-        }
-        stage_store(buf ^ 1);
-        stage_val();
-        stage_addr(ch + 3);
-        __syncthreads();
-    }
-    mfma_drain();
-}
-
 // ---------------------------------------------------------------------------
-// The same 64 x BN product for a contraction of at most NCH chunks of 16
+// acc += A(64 x K) B(K x BN) for a contraction of at most NCH chunks of 16
 // (NCH <= 8: at most 128), for levels with few tiles, where a tile's time is
 // its latency: every chunk's loads are issued before the first product, so
 // the global-memory latency is paid once instead of once per chunk.  The
 // loads of all NCH chunks are unconditional (past the contraction the
-// address callbacks return an in-bounds stand-in and a false mask), which
+// address callbacks addrA(k0, kk, ii, ok) / addrB(k0, kk, j, ok) return an
+// in-bounds stand-in and a false mask), which
 // keeps them in one straight run: with a branch per chunk the wait before
 // the first product would have to cover every path, i.e. all loads.  A read
-// along i, B as in tile_mma2 (kBJ), operands swapped when kT; masks kept as
+// along i, B along j (kBJ: B(k, j) contiguous in j) or along k, operands
+// swapped when kT; masks kept as
 // bits.  BN <= 64 (at most 8 values per thread a chunk).
 // ---------------------------------------------------------------------------
 template <int BN, int NCH, bool kBJ, bool kT, class FA, class FB, class FH>
@@ -552,10 +319,10 @@ __device__ __forceinline__ void tile_mma_deep(GemmLds& L, int Kb, int Ke, d4 (&a
 //  * Rows past c read row c - 1 (their products are never stored), columns
 //    past s read column s - 1, and chunks past the end read the last chunk
 //    again, so no load needs a mask.
-//  * Both operands lie in LDS as rows of 16 contraction entries (128 bytes),
-//    their 16-byte slots exclusive-or'ed with row / 2 mod 8, which makes the
-//    16-byte reads of an MFMA pair conflict-free without padding; a pair of
-//    reads feeds two MFMAs (contraction entries 8 t + 2 g and + 1).
+//  * Both operands lie in LDS as rows of 16 contraction entries (128 bytes):
+//    a 16-byte slot holds entries k and k + 4, what a lane needs for two
+//    consecutive MFMAs, and slots are exclusive-or'ed with row / 2 mod 8,
+//    which makes these reads conflict-free without padding.
 // Vector instructions per 32 MFMAs: 154 -> 21.  Gather-GEMM of the 64^3
 // matrix: 22.0 -> 18.4 ms (11.2 ms of it MFMA at the rate above, padding
 // included; without the loads of A it takes 15.3).
@@ -568,6 +335,13 @@ __device__ __forceinline__ void tile_mma_deep(GemmLds& L, int Kb, int Ke, d4 (&a
 // Byte offsets inside a block's panel and C's maps are 32-bit: a |C| that
 // exceeds them (4 million) would need a 16 TB inverse.
 constexpr int kGatherRow = 16 * (int)sizeof(double);  // bytes of one LDS row
+// byte offset of contraction entry k of a row: entries 8 t + g and 8 t + 4 + g
+// (g < 4) share slot 4 t + g
+__device__ __forceinline__ int lds_at(int row, int k)
+{
+    const int slot = ((k >> 3) << 2) | (k & 3);
+    return row * kGatherRow + ((slot ^ ((row >> 1) & 7)) << 4) + ((k >> 2) & 1) * 8;
+}
 template <int BNMAX>
 struct alignas(16) GatherLdsN {
     char A[2][TBM * kGatherRow];
@@ -685,12 +459,10 @@ __device__ __forceinline__ void gather_mma(LDS& L, const BlockDesc d, const int 
             }
         }
     };
-    // LDS byte offsets: row * 128 + ((k / 2) ^ (row / 2 mod 8)) * 16 + (k mod 2) * 8
-    auto at = [](int row, int k) { return row * kGatherRow + (((k >> 1) ^ ((row >> 1) & 7)) << 4) + (k & 1) * 8; };
-    const int wAbove = at(ai, ak), wB = at(bj, 2 * bk);
+    const int wAbove = lds_at(ai, ak), wB = lds_at(bj, 2 * bk), wB1 = lds_at(bj, 2 * bk + 1);
     int wBelow[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) wBelow[q] = at(lane, 4 * q + wave);
+    for (int q = 0; q < 4; ++q) wBelow[q] = lds_at(lane, 4 * q + wave);
     auto store = [&](auto M, const double (&va)[4], int ch, int buf) {
         constexpr int kM = decltype(M)::value;
         const int k0 = k_of(ch), md = kM >= 0 ? kM : mode_of(k0);
@@ -713,13 +485,16 @@ __device__ __forceinline__ void gather_mma(LDS& L, const BlockDesc d, const int 
         char* B = L.B[buf];
         if (BN >= 32 || wave < 2) {
 #pragma unroll
-            for (int q = 0; q < NP; ++q) *reinterpret_cast<d2*>(B + wB + q * 32 * kGatherRow) = d2{v_b[q].x, v_b[q].y};
+            for (int q = 0; q < NP; ++q) {
+                *reinterpret_cast<double*>(B + wB + q * 32 * kGatherRow) = v_b[q].x;
+                *reinterpret_cast<double*>(B + wB1 + q * 32 * kGatherRow) = v_b[q].y;
+            }
         }
     };
     // fragment rows: wm0, wn0 and 16 mt are multiples of 16, so one slot per
     // lane and half chunk serves every fragment
     const int fr = lane & 15, fg = lane >> 4;
-    const int f0 = at(fr, 2 * fg), f1 = at(fr, 8 + 2 * fg);
+    const int f0 = lds_at(fr, fg), f1 = lds_at(fr, 8 + fg);
     auto body = [&](auto M, auto X, int ch) {  // X: the parity of ch
         constexpr int buf = decltype(X)::value;
         const char *A = L.A[buf] + wm0 * kGatherRow, *B = L.B[buf] + wn0 * kGatherRow;
@@ -914,20 +689,18 @@ struct DenseLoader {
     static constexpr int NV = kAlongK ? 2 * NQ : NQ;                         // values
     Operand o;
     uint32_t voff;
-    int wpart, kp, wr[kAlongK ? 1 : NQ];
+    int wpart, kp, wr[kAlongK ? 2 : NQ];
     bool on;
 
     __device__ __forceinline__ DenseLoader(const Operand& op, int wave) : o(op)
     {
         const int tid = threadIdx.x, lane = tid & 63;
-        auto at = [](int row, int k) {
-            return row * kGatherRow + (((k >> 1) ^ ((row >> 1) & 7)) << 4) + (k & 1) * 8;
-        };
         if constexpr (kAlongK) {
             kp = tid & 7;
             const int row = tid >> 3;
             voff = (uint32_t)row * o.ld8 + (uint32_t)kp * 16u;
-            wr[0] = at(row, 2 * kp);
+            wr[0] = lds_at(row, 2 * kp);
+            wr[1] = lds_at(row, 2 * kp + 1);
             on = NR >= 32 || wave < 2;
             wpart = 0;
         } else {
@@ -937,7 +710,7 @@ struct DenseLoader {
             wpart = NR == 128 ? wave >> 1 : wave * (64 / RW);
             voff = (uint32_t)row * 8u + (uint32_t)kl * o.ld8;
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) wr[q] = at(row, q * KS + wpart + kl);
+            for (int q = 0; q < NQ; ++q) wr[q] = lds_at(row, q * KS + wpart + kl);
             kp = 0;
             on = true;
         }
@@ -979,7 +752,8 @@ struct DenseLoader {
                         x.x = k0 + 2 * kp < Ke ? x.x : 0.0;
                         x.y = k0 + 2 * kp + 1 < Ke ? x.y : 0.0;
                     }
-                    *reinterpret_cast<d2*>(lds + wr[0] + q * 32 * kGatherRow) = x;
+                    *reinterpret_cast<double*>(lds + wr[0] + q * 32 * kGatherRow) = x.x;
+                    *reinterpret_cast<double*>(lds + wr[1] + q * 32 * kGatherRow) = x.y;
                 }
             }
         } else {
@@ -1015,8 +789,7 @@ __device__ __forceinline__ void dense_mma(LDS& L, const Operand& opA, const Oper
         la.store(L.A[buf], a, k0, kAk && k0 + TBK > Ke, Ke);
         lb.store(L.B[buf], b, k0, false, Ke);
     };
-    const int fr = lane & 15, fg = lane >> 4, key = (fr >> 1) & 7;
-    const int f0 = fr * kGatherRow + ((fg ^ key) << 4), f1 = fr * kGatherRow + (((4 + fg) ^ key) << 4);
+    const int f0 = lds_at(lane & 15, lane >> 4), f1 = lds_at(lane & 15, 8 + (lane >> 4));
     if (nch > 0) {
         double a0[LA::NV], b0[LB::NV];
         load(a0, b0, 0);
@@ -1174,17 +947,17 @@ __global__ __launch_bounds__(kThreads) void k_panel_deep(const Task* __restrict_
 // MFMAs) it took 16.0 ms; the loop of dense_mma has none: 15.5, and 14.5
 // with three work-groups on a CU (four spill: 18.8).
 // ---------------------------------------------------------------------------
-template <bool kDeep = false, class LDS>
-__device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc d, double* __restrict__ Lp,
-                                           const double* __restrict__ Hp, const int64_t* __restrict__ cr2,
-                                           const int32_t* __restrict__ rel)
+// The scatter of a 64 x 64 tile of updates: product(acc, prefetch) forms the
+// tile (target columns k0.. along its rows, rows i0.. along its columns) and
+// calls prefetch once its own first loads are issued; value(ii, kk, x) is
+// what entry (ii, kk) of C x C adds to its place in the arena Z.
+template <class FP, class FV>
+__device__ __forceinline__ void scatter_update(const Task& t, const BlockDesc& d, double* __restrict__ Z,
+                                               const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel,
+                                               FP product, FV value)
 {
     using SH = TileShape<64>;
-    const int s = d.s, c = d.c;
-    const int64_t ld = (int64_t)s + c;
-    const int i0 = t.i0, k0c = t.j0;
-    const double* H = Hp + d.hoff;
-    const double* F = Lp + d.poff + s;
+    const int c = d.c, i0 = t.i0, k0c = t.j0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm0 = (wave % SH::WM) * (TBM / SH::WM), wn0 = (wave / SH::WM) * (64 / SH::WN);
     // this thread's outputs (mt, nt, v): target column kk = k0 + wm0 + 16 mt +
@@ -1224,38 +997,12 @@ __device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc
         }
     };
     d4 acc[2][4] = {};
-    if constexpr (kDeep) {
-        // A(kk, t) = F(k0 + kk, t): contiguous along the tile rows
-        auto addrA = [&](int t0, int tt, int kk, bool& ok) -> const double* {
-            const int k = k0c + kk, col = t0 + tt;
-            ok = k < c && col < s;
-            return ok ? F + k + (int64_t)col * ld : F;
-        };
-        // B(t, ii) = L_hat(i0 + ii, t): contiguous in ii
-        auto addrB = [&](int t0, int tt, int ii, bool& ok) -> const double* {
-            const int i = i0 + ii, k = t0 + tt;
-            ok = i < c && k < s;
-            return ok ? H + i + (int64_t)k * c : H;
-        };
-        if (s <= 16) tile_mma_deep<64, 1, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
-        else if (s <= 32) tile_mma_deep<64, 2, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
-        else if (s <= 64) tile_mma_deep<64, 4, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
-        else if (s <= kDeepK) tile_mma_deep<64, 8, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
-    }
-    auto dense = [&](auto& W) {
-        dense_mma<64, false, false, false>(W, operand(F + k0c, (int64_t)(s - 1) * ld + c - k0c, ld),
-                                           operand(H + i0, (int64_t)s * c - i0, c), 0, s, acc, prefetch);
-    };
-    if constexpr (kDeep) {
-        if (s > kDeepK) dense(L.d);
-    } else {
-        dense(L);
-    }
+    product(acc, prefetch);
     double* base[SH::MT][4];
 #pragma unroll
     for (int mt = 0; mt < SH::MT; ++mt)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) base[mt][v] = Lp + cr[mt][v].x;
+        for (int v = 0; v < 4; ++v) base[mt][v] = Z + cr[mt][v].x;
     auto target = [&](int mt, int nt, int v) { return base[mt][v] + ro[mt][nt][v]; };
     auto live = [&](int mt, int nt, int v) {
         const int ii = row_of(nt), kk = col_of(mt, v);
@@ -1281,7 +1028,7 @@ __device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc
 #pragma unroll
                 for (int nt = 0; nt < SH::NT; ++nt)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) *target(mt, nt, v) = old[mt][nt][v] - acc[mt][nt][v];
+                    for (int v = 0; v < 4; ++v) *target(mt, nt, v) = old[mt][nt][v] + value(row_of(nt), col_of(mt, v), acc[mt][nt][v]);
         } else {
 #pragma unroll
             for (int mt = 0; mt < SH::MT; ++mt)
@@ -1289,7 +1036,7 @@ __device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc
                 for (int nt = 0; nt < SH::NT; ++nt)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        if (live(mt, nt, v)) *target(mt, nt, v) = old[mt][nt][v] - acc[mt][nt][v];
+                        if (live(mt, nt, v)) *target(mt, nt, v) = old[mt][nt][v] + value(row_of(nt), col_of(mt, v), acc[mt][nt][v]);
         }
     } else if (full) {
 #pragma unroll
@@ -1297,7 +1044,7 @@ __device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc
 #pragma unroll
             for (int nt = 0; nt < SH::NT; ++nt)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) unsafeAtomicAdd(target(mt, nt, v), -acc[mt][nt][v]);
+                for (int v = 0; v < 4; ++v) unsafeAtomicAdd(target(mt, nt, v), value(row_of(nt), col_of(mt, v), acc[mt][nt][v]));
     } else {
 #pragma unroll
         for (int mt = 0; mt < SH::MT; ++mt)
@@ -1305,8 +1052,50 @@ __device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc
             for (int nt = 0; nt < SH::NT; ++nt)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
-                    if (live(mt, nt, v)) unsafeAtomicAdd(target(mt, nt, v), -acc[mt][nt][v]);
+                    if (live(mt, nt, v)) unsafeAtomicAdd(target(mt, nt, v), value(row_of(nt), col_of(mt, v), acc[mt][nt][v]));
     }
+}
+
+template <bool kDeep = false, class LDS>
+__device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc d, double* __restrict__ Lp,
+                                           const double* __restrict__ Hp, const int64_t* __restrict__ cr2,
+                                           const int32_t* __restrict__ rel)
+{
+    const int s = d.s, c = d.c;
+    const int64_t ld = (int64_t)s + c;
+    const int i0 = t.i0, k0c = t.j0;
+    const double* H = Hp + d.hoff;
+    const double* F = Lp + d.poff + s;
+    auto product = [&](d4(&acc)[2][4], auto prefetch) {
+        if constexpr (kDeep) {
+            // A(kk, t) = F(k0 + kk, t): contiguous along the tile rows
+            auto addrA = [&](int t0, int tt, int kk, bool& ok) -> const double* {
+                const int k = k0c + kk, col = t0 + tt;
+                ok = k < c && col < s;
+                return ok ? F + k + (int64_t)col * ld : F;
+            };
+            // B(t, ii) = L_hat(i0 + ii, t): contiguous in ii
+            auto addrB = [&](int t0, int tt, int ii, bool& ok) -> const double* {
+                const int i = i0 + ii, k = t0 + tt;
+                ok = i < c && k < s;
+                return ok ? H + i + (int64_t)k * c : H;
+            };
+            if (s <= 16) tile_mma_deep<64, 1, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
+            else if (s <= 32) tile_mma_deep<64, 2, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
+            else if (s <= 64) tile_mma_deep<64, 4, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
+            else if (s <= kDeepK) tile_mma_deep<64, 8, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
+        }
+        auto dense = [&](auto& W) {
+            dense_mma<64, false, false, false>(W, operand(F + k0c, (int64_t)(s - 1) * ld + c - k0c, ld),
+                                               operand(H + i0, (int64_t)s * c - i0, c), 0, s, acc, prefetch);
+        };
+        if constexpr (kDeep) {
+            if (s > kDeepK) dense(L.d);
+        } else {
+            dense(L);
+        }
+    };
+    scatter_update(t, d, Lp, cr2, rel, product, [](int, int, double x) { return -x; });
 }
 
 __global__ __launch_bounds__(kThreads, 3) void k_schur(const Task* __restrict__ tasks,
@@ -1437,7 +1226,13 @@ __device__ __forceinline__ void sdiag_task(SdiagLds& S, const Task t, const Bloc
 // Products accumulate transposed (lane l holds tile row l % 16), so stores
 // and atomics run down the columns of the panel.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void sdiag64_task(GemmLds& L, const Task t, const BlockDesc d, double* __restrict__ Ap,
+// the tile's operands, then the exchange of a diagonal tile's transpose
+union SdiagLds64 {
+    GatherLdsN<64> d;
+    double S[TBM][TBM + 1];
+};
+
+__device__ __forceinline__ void sdiag64_task(SdiagLds64& L, const Task t, const BlockDesc d, double* __restrict__ Ap,
                                              const double* __restrict__ Hp, const double* __restrict__ Tp)
 {
     using SH = TileShape<64>;
@@ -1453,21 +1248,9 @@ __device__ __forceinline__ void sdiag64_task(GemmLds& L, const Task t, const Blo
     const double* V = second ? H : X;
     const int64_t ldu = second ? ld : c, ldv = second ? c : ld;
     d4 acc[2][4] = {};
-    auto addrA = [&](int k0, int kk, int ii, bool& ok) -> const double* {
-        const int r = k0 + kk, col = I0 + ii;
-        ok = r < ke && col < s;
-        return ok ? U + r + (int64_t)col * ldu : U;
-    };
-    auto addrB = [&](int k0, int kk, int j, bool& ok) -> const double* {
-        const int r = k0 + kk, col = J0 + j;
-        ok = r < ke && col < s;
-        return ok ? V + r + (int64_t)col * ldv : V;
-    };
-    // pairs of rows never straddle the end of the contraction when c and kb are even
-    if ((c & 1) == 0 && (kb & 1) == 0)
-        tile_mma2<64, false, true, true>(L, kb, ke, acc, addrA, addrB, [](int) { return true; }, [] {});
-    else
-        tile_mma2<64, false, true>(L, kb, ke, acc, addrA, addrB, [](int) { return true; }, [] {});
+    dense_mma<64, true, true, true>(L.d, operand(U + (int64_t)I0 * ldu, (int64_t)(s - 1 - I0) * ldu + c, ldu),
+                                    operand(V + (int64_t)J0 * ldv, (int64_t)(s - 1 - J0) * ldv + c, ldv), kb, ke, acc,
+                                    [] {});
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm0 = (wave % SH::WM) * (TBM / SH::WM), wn0 = (wave / SH::WM) * (64 / SH::WN);
     const double* T = Tp + d.woff;
@@ -1489,9 +1272,7 @@ __device__ __forceinline__ void sdiag64_task(GemmLds& L, const Task t, const Blo
         return;
     }
     // diagonal tile: the loop ended on a barrier, the LDS tile is free
-    double(*S)[TBM + 1] = reinterpret_cast<double(*)[TBM + 1]>(&L);
-    static_assert(sizeof(double) * TBM * (TBM + 1) <= sizeof(GemmLds), "exchange tile fits the LDS tile");
-    static_assert(sizeof(TileLds) <= sizeof(GemmLds), "the one-stage tile fits the LDS tile");
+    double(*S)[TBM + 1] = L.S;
 #pragma unroll
     for (int mt = 0; mt < SH::MT; ++mt)
 #pragma unroll
@@ -1523,7 +1304,7 @@ __global__ __launch_bounds__(kThreads) void k_sdiag64(const Task* __restrict__ t
                                                       const BlockDesc* __restrict__ blk, double* __restrict__ Ap,
                                                       const double* __restrict__ Hp, const double* __restrict__ Tp)
 {
-    __shared__ GemmLds L;
+    __shared__ SdiagLds64 L;
     const Task t = tasks[blockIdx.x];
     sdiag64_task(L, t, blk[t.b], Ap, Hp, Tp);
 }
@@ -2509,8 +2290,6 @@ __global__ __launch_bounds__(kThreads) void k_sb_invert(const Task* __restrict__
 // ===========================================================================
 template <int NB>  // the widest diagonal block (16 NB; inversion kernels: none, NB = 1)
 union PersistLds {
-    TileLds tile;
-    GemmLds gemm;
     GatherLds gather;
     SdiagLds sd;
     DiagLds<NB> diag;
@@ -2834,24 +2613,27 @@ __device__ __forceinline__ double ybar_at(const double* __restrict__ Zd, int64_t
     return 0.5 * Zd[a + (int64_t)b * ld];
 }
 
+// Tb(B) := Ybar of the level's blocks: the adjoint of T, and the symmetric
+// operand of the two products below
+__global__ void k_tbar_init(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
+                            const double* __restrict__ Zb, double* __restrict__ Tb)
+{
+    const BlockDesc d = blk[tasks[blockIdx.x].b];
+    const int64_t ld = (int64_t)d.s + d.c;
+    for (int e = threadIdx.x + blockIdx.y * blockDim.x; e < d.s * d.s; e += blockDim.x * gridDim.y)
+        Tb[d.woff + e] = ybar_at(Zb + d.poff, ld, e % d.s, e / d.s);
+}
+
 template <int BN>
-__device__ void rs1_task(TileLds& L, const Task t, const BlockDesc d, double* __restrict__ Zb,
-                         const double* __restrict__ Hp)
+__device__ __forceinline__ void rs1_task(GatherLds& L, const Task t, const BlockDesc d, double* __restrict__ Zb,
+                                         const double* __restrict__ Hp, const double* __restrict__ Tb)
 {
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
     const int r0 = t.i0, n0 = t.j0;
-    const double* Zd = Zb + d.poff;
     d4 acc[2][4] = {};
-    auto loadA = [&](int k0, int kk, int ii) -> double {
-        const int i = r0 + ii, k = k0 + kk;
-        return (i < c && k < s) ? Hp[d.hoff + i + (int64_t)k * c] : 0.0;
-    };
-    auto loadB = [&](int k0, int kk, int j) -> double {
-        const int k = k0 + kk, jj = n0 + j;
-        return (k < s && jj < s) ? ybar_at(Zd, ld, k, jj) : 0.0;
-    };
-    tile_mma<BN>(L, 0, s, acc, loadA, loadB, [](int) { return false; });
+    dense_mma<BN, false, false, true>(L, operand(Hp + d.hoff + r0, (int64_t)s * c - r0, c),
+                                      operand(Tb + d.woff + n0, (int64_t)s * s - n0, s), 0, s, acc, [] {});
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
         if (ii < c && jj < s) Zb[d.poff + s + ii + (int64_t)jj * ld] -= v;
@@ -2859,44 +2641,30 @@ __device__ void rs1_task(TileLds& L, const Task t, const BlockDesc d, double* __
 }
 
 __global__ __launch_bounds__(kThreads) void k_rs1(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
-                                                  double* __restrict__ Zb, const double* __restrict__ Hp)
+                                                  double* __restrict__ Zb, const double* __restrict__ Hp,
+                                                  const double* __restrict__ Tb)
 {
-    __shared__ TileLds L;
+    __shared__ GatherLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
-#define SELINV_CALL(BN) rs1_task<BN>(L, t, d, Zb, Hp)
+#define SELINV_CALL(BN) rs1_task<BN>(L, t, d, Zb, Hp, Tb)
     SELINV_BN_DISPATCH(t.bn, SELINV_CALL)
 #undef SELINV_CALL
 }
 
-// the gathered product, then a plain one
-union ReverseLds {
-    GatherLds g;
-    TileLds t;
-};
-
 template <int BN>
-__device__ void rs2_task(ReverseLds& L, const Task t, const BlockDesc d, const double* __restrict__ Ap,
-                         const double* __restrict__ Zb, double* __restrict__ Hb, const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
+__device__ __forceinline__ void rs2_task(GatherLds& L, const Task t, const BlockDesc d, const double* __restrict__ Ap,
+                         const double* __restrict__ Zb, const double* __restrict__ Tb, double* __restrict__ Hb, const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
     const int r0 = t.i0, n0 = t.j0;
-    const double* Zd = Zb + d.poff;
     d4 acc[2][4] = {};
     // G Xbar: G gathered from the inverse panels, Xbar = Zbar(C,B)
-    gather_mma<BN, 0>(L.g, d, r0, n0, t.kb, t.ke, Ap, Zb + d.poff + s, ld, cr2, rel, acc);
-    if (t.kb == 0) {  // -X Ybar, once per tile
-        auto loadX = [&](int k0, int kk, int ii) -> double {
-            const int i = r0 + ii, k = k0 + kk;
-            return (i < c && k < s) ? Ap[d.poff + s + i + (int64_t)k * ld] : 0.0;
-        };
-        auto loadY = [&](int k0, int kk, int j) -> double {
-            const int k = k0 + kk, jj = n0 + j;
-            return (k < s && jj < s) ? ybar_at(Zd, ld, k, jj) : 0.0;
-        };
-        tile_mma<BN>(L.t, 0, s, acc, loadX, loadY, [](int) { return false; });
-    }
+    gather_mma<BN, 0>(L, d, r0, n0, t.kb, t.ke, Ap, Zb + d.poff + s, ld, cr2, rel, acc);
+    if (t.kb == 0)  // -X Ybar, once per tile
+        dense_mma<BN, false, false, true>(L, operand(Ap + d.poff + s + r0, (int64_t)(s - 1) * ld + c - r0, ld),
+                                          operand(Tb + d.woff + n0, (int64_t)s * s - n0, s), 0, s, acc, [] {});
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
         if (ii < c && jj < s) {
@@ -2908,68 +2676,40 @@ __device__ void rs2_task(ReverseLds& L, const Task t, const BlockDesc d, const d
 
 __global__ __launch_bounds__(kThreads, 2) void k_rs2(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                   const double* __restrict__ Ap, const double* __restrict__ Zb,
+                                                  const double* __restrict__ Tb,
                                                   double* __restrict__ Hb, const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
-    __shared__ ReverseLds L;
+    __shared__ GatherLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
-#define SELINV_CALL(BN) rs2_task<BN>(L, t, d, Ap, Zb, Hb, cr2, rel)
+#define SELINV_CALL(BN) rs2_task<BN>(L, t, d, Ap, Zb, Tb, Hb, cr2, rel)
     SELINV_BN_DISPATCH(t.bn, SELINV_CALL)
 #undef SELINV_CALL
 }
 
 // ancestors' Zbar += -(Xbar L_hat^T + L_hat Xbar^T): lower tile rows
-// [i0, i0+64) x columns [k0, k0+64), contraction over [Xbar | L_hat]
-__global__ __launch_bounds__(kThreads) void k_rs3(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
-                                                  double* __restrict__ Zb, const double* __restrict__ Hp,
-                                                  const int64_t* __restrict__ cbase,
-                                                  const int64_t* __restrict__ rbase, const int32_t* __restrict__ rel)
+// [i0, i0+64) x columns [k0, k0+64); a diagonal entry of C x C counts half
+__global__ __launch_bounds__(kThreads, 3) void k_rs3(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
+                                                     double* __restrict__ Zb, const double* __restrict__ Hp,
+                                                     const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
-    __shared__ TileLds L;
+    __shared__ GatherLdsN<64> L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
-    const int i0 = t.i0, k0c = t.j0;
-    const double* Xb = Zb + d.poff + s;
-    const double* H = Hp + d.hoff;
-    d4 acc[2][4] = {};
-    auto loadA = [&](int q0, int qq, int ii) -> double {
-        const int i = i0 + ii, q = q0 + qq;
-        if (i >= c || q >= 2 * s) return 0.0;
-        return q < s ? Xb[i + (int64_t)q * ld] : H[i + (int64_t)(q - s) * c];
+    auto xbar = [&](int r) { return operand(Zb + d.poff + s + r, (int64_t)(s - 1) * ld + c - r, ld); };
+    auto lhat = [&](int r) { return operand(Hp + d.hoff + r, (int64_t)s * c - r, c); };
+    auto product = [&](d4(&acc)[2][4], auto prefetch) {
+        dense_mma<64, false, false, false>(L, xbar(t.j0), lhat(t.i0), 0, s, acc, prefetch);
+        dense_mma<64, false, false, false>(L, lhat(t.j0), xbar(t.i0), 0, s, acc, [] {});
     };
-    auto loadB = [&](int q0, int qq, int j) -> double {
-        const int k = k0c + j, q = q0 + qq;
-        if (k >= c || q >= 2 * s) return 0.0;
-        return q < s ? H[k + (int64_t)q * c] : Xb[k + (int64_t)(q - s) * ld];
-    };
-    tile_mma<64>(L, 0, 2 * s, acc, loadA, loadB, [](int) { return false; });
-    tile_epilogue_t<64>(acc, [&](int i, int j, double v) {
-        const int ii = i0 + i, kk = k0c + j;
-        if (ii < c && kk < c && ii >= kk) {
-            const int64_t pk = d.coff + kk;
-            double* z = Zb + cbase[pk] + rel[rbase[pk] + ii];
-            const double u = ii == kk ? -0.5 * v : -v;
-            if (t.flags & 4) *z += u;  // colour group: no other writer in this launch
-            else unsafeAtomicAdd(z, u);
-        }
-    });
-}
-
-// Tbar := Ybar for every block, once the reverse selected inversion is done
-__global__ void k_tbar_init(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
-                            const double* __restrict__ Zb, double* __restrict__ Tb)
-{
-    const BlockDesc d = blk[tasks[blockIdx.x].b];
-    const int64_t ld = (int64_t)d.s + d.c;
-    for (int e = threadIdx.x; e < d.s * d.s; e += blockDim.x)
-        Tb[d.woff + e] = ybar_at(Zb + d.poff, ld, e % d.s, e / d.s);
+    scatter_update(t, d, Zb, cr2, rel, product, [](int ii, int kk, double x) { return ii == kk ? -0.5 * x : -x; });
 }
 
 // Lhat_bar += Ubar F(C,B), Ubar(i,k) = -Fbar(C[i],C[k]) for i >= k
 template <int BN>
-__device__ void rf1a_task(ReverseLds& L, const Task t, const BlockDesc d, const double* __restrict__ Zb,
+__device__ __forceinline__ void rf1a_task(GatherLds& L, const Task t, const BlockDesc d, const double* __restrict__ Zb,
                           const double* __restrict__ Lp, double* __restrict__ Hb, const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
     const int s = d.s, c = d.c;
@@ -2977,7 +2717,7 @@ __device__ void rf1a_task(ReverseLds& L, const Task t, const BlockDesc d, const 
     const int r0 = t.i0, n0 = t.j0;
     d4 acc[2][4] = {};
     // Ubar(i,k) = -Fbar(C[i],C[k]) for k <= i, gathered from the adjoint panels; B = F(C,B)
-    gather_mma<BN, 1>(L.g, d, r0, n0, t.kb, t.ke, Zb, Lp + d.poff + s, ld, cr2, rel, acc);
+    gather_mma<BN, 1>(L, d, r0, n0, t.kb, t.ke, Zb, Lp + d.poff + s, ld, cr2, rel, acc);
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
         if (ii < c && jj < s) {
@@ -2992,7 +2732,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rf1a(const Task* __restrict__ t
                                                    double* __restrict__ Hb, const int64_t* __restrict__ cr2,
                                                    const int32_t* __restrict__ rel)
 {
-    __shared__ ReverseLds L;
+    __shared__ GatherLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
 #define SELINV_CALL(BN) rf1a_task<BN>(L, t, d, Zb, Lp, Hb, cr2, rel)
@@ -3002,7 +2742,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rf1a(const Task* __restrict__ t
 
 // Fbar(C,B) = Ubar^T L_hat (+ Lhat_bar T on piece 0), Ubar^T(i,k) = -Fbar(C[k],C[i]) for k >= i
 template <int BN>
-__device__ void rf1b_task(ReverseLds& L, const Task t, const BlockDesc d, double* __restrict__ Zb,
+__device__ __forceinline__ void rf1b_task(GatherLds& L, const Task t, const BlockDesc d, double* __restrict__ Zb,
                           const double* __restrict__ Hp, const double* __restrict__ Hb, const double* __restrict__ Tp,
                           const int64_t* __restrict__ cr2,
                           const int32_t* __restrict__ rel)
@@ -3012,22 +2752,14 @@ __device__ void rf1b_task(ReverseLds& L, const Task t, const BlockDesc d, double
     const int r0 = t.i0, n0 = t.j0;
     d4 acc[2][4] = {};
     // -Ubar^T L_hat: Fbar(C[k],C[i]) for k >= i, gathered from the adjoint panels
-    gather_mma<BN, 2>(L.g, d, r0, n0, t.kb, t.ke, Zb, Hp + d.hoff, c, cr2, rel, acc);
+    gather_mma<BN, 2>(L, d, r0, n0, t.kb, t.ke, Zb, Hp + d.hoff, c, cr2, rel, acc);
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = -acc[mt][nt];
-    if (t.flags & 2) {
-        auto loadA2 = [&](int k0, int kk, int ii) -> double {
-            const int i = r0 + ii, k = k0 + kk;
-            return (i < c && k < s) ? Hb[d.hoff + i + (int64_t)k * c] : 0.0;
-        };
-        auto loadB2 = [&](int k0, int kk, int j) -> double {
-            const int k = k0 + kk, jj = n0 + j;
-            return (k < s && jj < s) ? Tp[d.woff + k + (int64_t)jj * s] : 0.0;
-        };
-        tile_mma<BN>(L.t, 0, s, acc, loadA2, loadB2, [](int) { return false; });
-    }
+    if (t.flags & 2)  // T is symmetric
+        dense_mma<BN, false, false, true>(L, operand(Hb + d.hoff + r0, (int64_t)s * c - r0, c),
+                                          operand(Tp + d.woff + n0, (int64_t)s * s - n0, s), 0, s, acc, [] {});
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
         if (ii < c && jj < s) {
@@ -3043,7 +2775,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rf1b(const Task* __restrict__ t
                                                    const int64_t* __restrict__ cr2,
                                                    const int32_t* __restrict__ rel)
 {
-    __shared__ ReverseLds L;
+    __shared__ GatherLds L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
 #define SELINV_CALL(BN) rf1b_task<BN>(L, t, d, Zb, Hp, Hb, Tp, cr2, rel)
@@ -3051,53 +2783,28 @@ __global__ __launch_bounds__(kThreads, 2) void k_rf1b(const Task* __restrict__ t
 #undef SELINV_CALL
 }
 
-// Tbar(I,J) += F(C,B)^T Lhat_bar over rows [kb, ke) of C, one 32 x 32 tile
+// Tbar(I,J) += F(C,B)^T Lhat_bar over rows [kb, ke) of C, one 64 x 64 tile
 __global__ __launch_bounds__(kThreads) void k_rf2(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                   const double* __restrict__ Lp, const double* __restrict__ Hb,
                                                   double* __restrict__ Tb)
 {
-    __shared__ double FI[16][SDT + 1], HJ[16][SDT + 1];
+    __shared__ GatherLdsN<64> L;
     const Task t = tasks[blockIdx.x];
     const BlockDesc d = blk[t.b];
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
     const int I0 = t.i0, J0 = t.j0;
-    const double* F = Lp + d.poff + s;
-    const double* H = Hb + d.hoff;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int fm = (wave & 1) * 16, fn = (wave >> 1) * 16;
-    d4 acc = {0, 0, 0, 0};
-    const int rend = min(c, t.ke);
-    for (int r0 = t.kb; r0 < rend; r0 += 16) {
-#pragma unroll
-        for (int q = 0; q < (16 * SDT) / kThreads; ++q) {
-            const int e = threadIdx.x + q * kThreads;
-            const int kk = e & 15, col = e >> 4;
-            const int r = r0 + kk;
-            const bool okr = r < rend;
-            const int ci = I0 + col, cj = J0 + col;
-            const double f = (okr && ci < s) ? F[r + (int64_t)ci * ld] : 0.0;
-            const double h = (okr && cj < s) ? H[r + (int64_t)cj * c] : 0.0;
-            FI[kk][col] = f;
-            HJ[kk][col] = h;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int kr = ks * 4 + (lane >> 4);
-            acc = mfma(FI[kr][fm + (lane & 15)], HJ[kr][fn + (lane & 15)], acc);
-        }
-        __syncthreads();
-    }
-    mfma_drain();
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        const int gi = I0 + fm + (lane >> 4) + 4 * v, gj = J0 + fn + (lane & 15);
+    d4 acc[2][4] = {};
+    dense_mma<64, true, true, true>(L, operand(Lp + d.poff + s + I0 * ld, (int64_t)(s - 1 - I0) * ld + c, ld),
+                                    operand(Hb + d.hoff + (int64_t)J0 * c, (int64_t)(s - 1 - J0) * c + c, c), t.kb,
+                                    min(t.ke, c), acc, [] {});
+    tile_epilogue_t<64>(acc, [&](int i, int j, double v) {
+        const int gi = I0 + i, gj = J0 + j;
         if (gi < s && gj < s) {
             double* p = Tb + d.woff + gi + (int64_t)gj * s;
-            if (t.flags & 1) unsafeAtomicAdd(p, acc[v]); else *p += acc[v];
+            if (t.flags & 1) unsafeAtomicAdd(p, v); else *p += v;
         }
-    }
+    });
 }
 
 // Fbar(B,B) stored lower = -T (Tbar + Tbar^T) T with the diagonal halved
@@ -3215,25 +2922,28 @@ hipError_t launch_backward_init(Prof* P, const DevPtrs& D, int64_t arena, int64_
 }
 
 hipError_t launch_revsel_level(Prof* P, const DevPtrs& D, int64_t a0, int64_t na, int64_t b0, int64_t nb,
-                               const int64_t* rs3_cuts, int ncuts, hipStream_t s)
+                               const int64_t* rs3_cuts, int ncuts, int64_t d0, int64_t nd, int smax, hipStream_t s)
 {
-    if (na > 0) launch(P, kRevSel, k_rs1, dim3((unsigned)na), 0, s, D.t_rs1 + a0, D.blocks, D.Zb, (const double*)D.Hp);
+    if (nd > 0)  // a work-group per 4096 entries of the widest block
+        launch(P, kRevSel, k_tbar_init, dim3((unsigned)nd, (unsigned)((smax * smax + 4095) / 4096)), 0, s,
+               D.t_diag + d0, D.blocks, (const double*)D.Zb, D.Tb);
+    if (na > 0)
+        launch(P, kRevSel, k_rs1, dim3((unsigned)na), 0, s, D.t_rs1 + a0, D.blocks, D.Zb, (const double*)D.Hp,
+               (const double*)D.Tb);
     if (nb > 0)
         launch(P, kRevSel, k_rs2, dim3((unsigned)nb), 0, s, D.t_rs2 + b0, D.blocks, (const double*)D.Ap,
-               (const double*)D.Zb, D.Hb, D.cr2, D.rel);
+               (const double*)D.Zb, (const double*)D.Tb, D.Hb, D.cr2, D.rel);
     for (int g = 0; g + 1 < ncuts; g++) {
         const int64_t n = rs3_cuts[g + 1] - rs3_cuts[g];
         if (n > 0)
             launch(P, kRevSel, k_rs3, dim3((unsigned)n), 0, s, D.t_rs3 + rs3_cuts[g], D.blocks, D.Zb,
-                   (const double*)D.Hp, D.cbase, D.rbase, D.rel);
+                   (const double*)D.Hp, D.cr2, D.rel);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_revfac_init(Prof* P, const DevPtrs& D, int64_t nblocks, int64_t arena, hipStream_t s)
+hipError_t launch_revfac_init(Prof* P, const DevPtrs& D, int64_t arena, hipStream_t s)
 {
-    if (nblocks > 0)
-        launch(P, kRevFac, k_tbar_init, dim3((unsigned)nblocks), 0, s, D.t_diag, D.blocks, (const double*)D.Zb, D.Tb);
     return launch_fill(P, kRevFac, D.Zb, arena, 0.0, s);
 }
 

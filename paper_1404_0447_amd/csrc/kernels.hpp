@@ -33,10 +33,11 @@ struct DevPtrs {
 hipError_t launch_backward_init(Prof* P, const DevPtrs& D, int64_t arena, int64_t harena, const double* gsel,
                                 int64_t nnzL, hipStream_t s);
 // rs3_cuts[0..ncuts): the level's t_rs3 tasks in groups launched one after
-// the other (colour groups of disjoint scatters in the deterministic mode)
+// the other (colour groups of disjoint scatters in the deterministic mode);
+// smax: the widest of the level's blocks t_diag[d0 .. d0+nd)
 hipError_t launch_revsel_level(Prof* P, const DevPtrs& D, int64_t a0, int64_t na, int64_t b0, int64_t nb,
-                               const int64_t* rs3_cuts, int ncuts, hipStream_t s);
-hipError_t launch_revfac_init(Prof* P, const DevPtrs& D, int64_t nblocks, int64_t arena, hipStream_t s);
+                               const int64_t* rs3_cuts, int ncuts, int64_t d0, int64_t nd, int smax, hipStream_t s);
+hipError_t launch_revfac_init(Prof* P, const DevPtrs& D, int64_t arena, hipStream_t s);
 // smax: the widest of the level's blocks t_diag[d0 .. d0+nd)
 hipError_t launch_revfac_level(Prof* P, const DevPtrs& D, int64_t a0, int64_t na, int64_t b0, int64_t nb, int64_t c0,
                                int64_t nc, int64_t d0, int64_t nd, int smax, hipStream_t s);

@@ -316,22 +316,20 @@ void build_schedule(selinv_plan_s* P)
     std::vector<char> excl(P->blocks.size(), 0);
     for (int l = 0; l < D; l++) {
         exclusive_blocks(P, lv[l], touch, excl);
-        // tiles this level has without splitting contractions over C: of the
-        // tiled forward path, and of the reverse sweep (every block)
-        int64_t base = 0, dbase = 0, rbase_ = 0, rdbase = 0;
+        // tiles the reverse sweep (every block) has in this level without
+        // splitting contractions over C
+        int64_t rbase_ = 0, rdbase = 0;
         std::vector<int> small;
         for (int B : lv[l]) {
             const BlockDesc& d = P->blocks[B];
             const int64_t tiles = (int64_t)((d.c + kTileM - 1) / kTileM) * ((d.s + tile_bn(d.s) - 1) / tile_bn(d.s));
-            const int nd = (d.s + kDiagTile - 1) / kDiagTile;
+            const int nd = (d.s + kDiagTile64 - 1) / kDiagTile64;
             rbase_ += tiles;
-            rdbase += nd * (nd + 1) / 2;
+            rdbase += (int64_t)nd * nd;
             if (small_block(d.s, d.c)) {
                 small.push_back(B);
                 continue;
             }
-            base += tiles;
-            dbase += nd * (nd + 1) / 2;
         }
         push_sb_groups(small, qSbFactor, P->t_sb.tasks);
         auto fill_for = [](int64_t tiles) { return tiles > 0 && tiles < kFillTiles ? (kFillTiles + tiles - 1) / tiles : 1; };
@@ -351,8 +349,6 @@ void build_schedule(selinv_plan_s* P)
         // may be cut finer to fill the device
         const int64_t dwant = det ? 1 : best_split(dg, kGemmSlots, kSdiagTaskOvh, 64, kMinSplitKDiag);
         const int64_t rwant = det ? 1 : fill_for(rbase_), rdwant = det ? 1 : fill_for(rdbase);
-        (void)base;
-        (void)dbase;
         // few panel tiles: at most 64 wide each, for the whole-contraction kernel
         int64_t npanel64 = 0;
         int smax = 0;
@@ -376,12 +372,12 @@ void build_schedule(selinv_plan_s* P)
             P->t_diag.tasks.push_back({B, 0, 0, 0, 0, 0, 0, 0});
             P->diag_smax[l] = std::max(P->diag_smax[l], d.s);
             // reverse sweep: every block, tiled
-            const int nd = (s + kDiagTile - 1) / kDiagTile;
+            const int nd = (s + kDiagTile64 - 1) / kDiagTile64;
             const int rsplit = split_for(rdwant, c);
             for (int I = 0; I < nd; I++)
                 for (int J = 0; J < nd; J++)
                     pieces(0, c, rsplit, [&](int kb, int ke, int) {
-                        P->t_rf2.tasks.push_back({B, I * kDiagTile, J * kDiagTile, 0, kb, ke, rsplit > 1, 0});
+                        P->t_rf2.tasks.push_back({B, I * kDiagTile64, J * kDiagTile64, 0, kb, ke, rsplit > 1, 0});
                     });
             for (int j = 0; j < s; j += bn)
                 for (int r = 0; r < c; r += kTileM) {
