@@ -7,7 +7,7 @@
 // cut into pieces, summed afterwards in a fixed order), so no kernel here
 // needs atomics.  Products run on FP64 MFMA: a 64 x 64 complex output
 // tile per work-group, real and imaginary parts as separate accumulators,
-// operands staged through LDS in 16-deep chunks.
+// operands staged through LDS in 8-deep chunks.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -24,16 +24,23 @@ typedef double z2 __attribute__((ext_vector_type(2)));  // (re, im)
 __device__ __forceinline__ z2 zmul(z2 a, z2 b) { return z2{a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 
 constexpr int kZT = 64;  // output tile edge
-constexpr int kZK = 16;  // contraction chunk
+constexpr int kZK = 8;   // contraction chunk
 
 // ---------------------------------------------------------------------------
-// A 64 x 64 complex product tile on FP64 MFMA: real and imaginary parts in
-// separate LDS planes, four waves of 32 x 32 (2 x 2 MFMA tiles each), and
-// per 4-deep step four real products per output tile:
+// A 64 x 64 complex product tile on FP64 MFMA: four waves of 32 x 32 (2 x 2
+// MFMA tiles each), and per 4-deep step four real products per output tile:
 //   C_re += A_re B_re - A_im B_im,  C_im += A_re B_im + A_im B_re.
 // v_mfma_f64_16x16x4f64: lane l holds A[l%16][l/16], B[l/16][l%16]; result
-// element (l/16 + 4 v, l%16) in register v.  Operands of the next chunk are
-// loaded into registers while the current one's products run.
+// element (l/16 + 4 v, l%16) in register v.
+//
+// What bounds it: FP64 MFMAs and vector instructions share the SIMD's FP64
+// hardware, so the loops issue few of the latter.  Operands go through LDS as
+// rows of kZK complex contraction entries (128 bytes), their 16-byte slots
+// exclusive-or'ed with row / 2 mod 8 (conflict-free 16-byte reads, no
+// padding): one read gives an MFMA step its real and its imaginary operand.
+// Two buffers, one barrier per chunk; global operands are read through buffer
+// descriptors, a chunk's position being a scalar offset.
+// 32 poles of n = 8,000 (factor + inversion): 34.9 -> 31.2 ms.
 // ---------------------------------------------------------------------------
 typedef double zd4 __attribute__((ext_vector_type(4)));
 
@@ -42,10 +49,10 @@ __device__ __forceinline__ zd4 zmfma(double a, double b, zd4 c)
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-constexpr int kZP = kZT + 4;  // padded LDS row
+constexpr int kZRow = kZK * (int)sizeof(z2);
 
-struct ZLdsM {
-    double ar[kZK][kZP], ai[kZK][kZP], br[kZK][kZP], bi[kZK][kZP];
+struct alignas(16) ZLds {
+    char A[2][kZT * kZRow], B[2][kZT * kZRow];
 };
 
 struct ZAcc {
@@ -56,65 +63,164 @@ struct ZNoHook {
     __device__ void operator()() const {}
 };
 
-// after_first: loads of the caller's own, issued once the first chunk's
-// operand loads are in flight (they may then wait under the products)
-template <class LA, class LB, class AF = ZNoHook>
-__device__ __forceinline__ void ztile_mfma(ZLdsM& L, int K, ZAcc& acc, LA loadA, LB loadB, AF after_first = AF())
+// LDS byte offset of entry (row, k)
+__device__ __forceinline__ int zat(int row, int k) { return row * kZRow + ((k ^ ((row >> 1) & 7)) << 4); }
+
+// The products of one chunk in LDS, `between` run between its two steps'
+// fragment reads.  kT: accumulated transposed (lane l % 16 is a row of the
+// tile, so that stores run down the columns of a panel).
+template <bool kT, class FB>
+__device__ __forceinline__ void zproducts(const char* A, const char* B, ZAcc& acc, FB between)
 {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm0 = (wave & 1) * 32, wn0 = (wave >> 1) * 32;
-    constexpr int NQ = (kZK * kZT) / kThreads;
-    z2 ra[NQ], rb[NQ];
-    auto fetch = [&](int k0) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const char *Aw = A + (wave & 1) * 32 * kZRow, *Bw = B + (wave >> 1) * 32 * kZRow;
+    const int f[2] = {zat(lane & 15, lane >> 4), zat(lane & 15, 4 + (lane >> 4))};
+    z2 x[2], y[2];
+    auto frags = [&](int t) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int e = t + q * kThreads, kk = e / kZT, i = e % kZT;
-            ra[q] = loadA(k0 + kk, i);
-            rb[q] = loadB(k0 + kk, i);
+        for (int m = 0; m < 2; ++m) {
+            x[m] = *reinterpret_cast<const z2*>(Aw + f[t] + m * 16 * kZRow);
+            y[m] = *reinterpret_cast<const z2*>(Bw + f[t] + m * 16 * kZRow);
         }
     };
-    if (K > 0) fetch(0);
-    after_first();
-    for (int k0 = 0; k0 < K; k0 += kZK) {
+    auto mma = [&]() {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int e = t + q * kThreads, kk = e / kZT, i = e % kZT;
-            L.ar[kk][i] = ra[q].x;
-            L.ai[kk][i] = ra[q].y;
-            L.br[kk][i] = rb[q].x;
-            L.bi[kk][i] = rb[q].y;
-        }
-        __syncthreads();
-        if (k0 + kZK < K) fetch(k0 + kZK);
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
-        for (int ks = 0; ks < kZK / 4; ++ks) {
-            const int kr = 4 * ks + (lane >> 4);
-            double xr[2], xi[2], yr[2], yi[2];
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                xr[m] = L.ar[kr][wm0 + 16 * m + (lane & 15)];
-                xi[m] = L.ai[kr][wm0 + 16 * m + (lane & 15)];
-                yr[m] = L.br[kr][wn0 + 16 * m + (lane & 15)];
-                yi[m] = L.bi[kr][wn0 + 16 * m + (lane & 15)];
+            for (int n = 0; n < 2; ++n) {
+                const z2 a = kT ? y[n] : x[m], b = kT ? x[m] : y[n];
+                acc.re[m][n] = zmfma(a.x, b.x, acc.re[m][n]);
+                acc.im[m][n] = zmfma(a.x, b.y, acc.im[m][n]);
+                acc.re[m][n] = zmfma(-a.y, b.y, acc.re[m][n]);
+                acc.im[m][n] = zmfma(a.y, b.x, acc.im[m][n]);
             }
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int n = 0; n < 2; ++n) {
-                    acc.re[m][n] = zmfma(xr[m], yr[n], acc.re[m][n]);
-                    acc.re[m][n] = zmfma(-xi[m], yi[n], acc.re[m][n]);
-                    acc.im[m][n] = zmfma(xr[m], yi[n], acc.im[m][n]);
-                    acc.im[m][n] = zmfma(xi[m], yr[n], acc.im[m][n]);
-                }
-        }
-        __syncthreads();
-    }
+    };
+    frags(0);
+    between();
+    mma();
+    frags(1);
+    mma();
+}
+
+__device__ __forceinline__ void zdrain()
+{
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// f(i, j, value) for every element of the tile (tile-local i, j)
+// A column-major complex array p[0 .. count), columns ld apart
+struct ZOperand {
+    __amdgpu_buffer_rsrc_t rsrc;
+    uint32_t ld16;  // bytes between columns
+};
+__device__ __forceinline__ ZOperand zoperand(const double* p, int64_t off, int64_t count, int64_t ld)
+{
+    return {__builtin_amdgcn_make_buffer_rsrc((void*)(p + 2 * off), 0,
+                                              (int)(uint32_t)((count > 0 ? count : 0) * (int64_t)sizeof(z2)), 0x00020000),
+            (uint32_t)(ld * (int64_t)sizeof(z2))};
+}
+__device__ __forceinline__ z2 zbuffer(const ZOperand& o, uint32_t voff, uint32_t soff)
+{
+    return __builtin_bit_cast(z2, __builtin_amdgcn_raw_buffer_load_b128(o.rsrc, (int)voff, (int)soff, 0));
+}
+
+// One operand of 64 rows; row r holds its contraction entry k at p[r + k ld]
+// (lanes along the rows; entries past the contraction are past the array and
+// read 0) or, kAlongK, at p[k + r ld] (lanes along k; entries past Ke read
+// the last one and are masked where `mask`).
+template <bool kAlongK>
+struct ZLoader {
+    ZOperand o;
+    uint32_t voff;
+    int kk, wr[2];
+    __device__ __forceinline__ ZLoader(const ZOperand& op, int wave) : o(op)
+    {
+        const int t = threadIdx.x, lane = t & 63;
+        if constexpr (kAlongK) {
+            kk = t & 7;
+            voff = (uint32_t)(t >> 3) * o.ld16 + (uint32_t)kk * 16u;
+            wr[0] = zat(t >> 3, kk);
+            wr[1] = wr[0] + 32 * kZRow;
+        } else {
+            kk = wave;
+            voff = (uint32_t)lane * 16u;
+            wr[0] = zat(lane, wave);
+            wr[1] = zat(lane, 4 + wave);
+        }
+    }
+    __device__ __forceinline__ void load(z2 (&v)[2], int k0, int Ke) const
+    {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if constexpr (kAlongK) {
+                const uint32_t back = k0 + kZK > Ke ? (uint32_t)(kk - min(kk, Ke - 1 - k0)) * 16u : 0u;
+                v[q] = zbuffer(o, voff + (uint32_t)q * 32u * o.ld16 - back, (uint32_t)k0 * 16u);
+            } else {
+                v[q] = zbuffer(o, voff, (uint32_t)(k0 + 4 * q + kk) * o.ld16);
+            }
+        }
+    }
+    __device__ __forceinline__ void store(char* lds, const z2 (&v)[2], int k0, bool mask, int Ke) const
+    {
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            *reinterpret_cast<z2*>(lds + wr[q]) = kAlongK && mask && k0 + kk >= Ke ? z2{0.0, 0.0} : v[q];
+    }
+};
+
+// acc += A B over [Kb, Ke); after_first: loads of the caller's own, issued
+// once the first chunks' operand loads are in flight (they may then wait
+// under the products).  Loads are issued two chunks ahead.
+template <bool kAk, bool kBk, bool kT, class AF = ZNoHook>
+__device__ __forceinline__ void zdense(ZLds& L, const ZOperand& oa, const ZOperand& ob, int Kb, int Ke, ZAcc& acc,
+                                       AF after_first = AF())
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nch = Ke > Kb ? (Ke - Kb + kZK - 1) / kZK : 0;
+    const ZLoader<kAk> la(oa, wave);
+    const ZLoader<kBk> lb(ob, wave);
+    z2 va[2][2], vb[2][2];  // by the chunk's parity
+    auto k_of = [&](int ch) { return Kb + min(ch, nch - 1) * kZK; };
+    auto load = [&](z2 (&a)[2], z2 (&b)[2], int ch) {
+        la.load(a, k_of(ch), Ke);
+        lb.load(b, k_of(ch), Ke);
+    };
+    auto store = [&](const z2 (&a)[2], const z2 (&b)[2], int ch, int buf) {
+        la.store(L.A[buf], a, k_of(ch), true, Ke);
+        lb.store(L.B[buf], b, k_of(ch), false, Ke);
+    };
+    if (nch > 0) {
+        z2 a0[2], b0[2];
+        load(a0, b0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load(va[1], vb[1], 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load(va[0], vb[0], 2);
+        __builtin_amdgcn_sched_barrier(0);
+        store(a0, b0, 0, 0);
+    }
+    after_first();
+    __syncthreads();
+    auto body = [&](auto X, int ch) {  // X: the parity of ch
+        constexpr int buf = decltype(X)::value;
+        zproducts<kT>(L.A[buf], L.B[buf], acc, [&] {
+            store(va[buf ^ 1], vb[buf ^ 1], ch + 1, buf ^ 1);
+            load(va[buf ^ 1], vb[buf ^ 1], ch + 3);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        __syncthreads();
+    };
+    int ch = 0;
+    for (; ch + 1 < nch; ch += 2) {
+        body(std::integral_constant<int, 0>{}, ch);
+        body(std::integral_constant<int, 1>{}, ch + 1);
+    }
+    if (ch < nch) body(std::integral_constant<int, 0>{}, ch);
+    zdrain();
+}
+
+// f(i, j, value) for every element of a tile accumulated transposed
 template <class F>
 __device__ __forceinline__ void zvisit(const ZAcc& acc, F f)
 {
@@ -126,7 +232,7 @@ __device__ __forceinline__ void zvisit(const ZAcc& acc, F f)
         for (int n = 0; n < 2; ++n)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                f(wm0 + 16 * m + (lane >> 4) + 4 * v, wn0 + 16 * n + (lane & 15), z2{acc.re[m][n][v], acc.im[m][n][v]});
+                f(wm0 + 16 * m + (lane & 15), wn0 + 16 * n + (lane >> 4) + 4 * v, z2{acc.re[m][n][v], acc.im[m][n][v]});
 }
 
 __device__ __forceinline__ z2 zload(const double* p, int64_t e) { return *reinterpret_cast<const z2*>(p + 2 * e); }
@@ -304,27 +410,32 @@ __global__ __launch_bounds__(kThreads) void k_zpanel(const Task* __restrict__ ta
     const BlockDesc d = blk[tk.b];
     const int s = d.s, c = d.c, r0 = tk.i0;
     const int64_t ld = (int64_t)s + c;
-    auto la = [&](int k, int i) { return (k < s && r0 + i < c) ? zload(Lp, d.poff + s + r0 + i + (int64_t)k * ld) : z2{0, 0}; };
-    auto lb = [&](int k, int j) { return (k < s && j < s) ? zload(Tp, d.woff + k + (int64_t)j * s) : z2{0, 0}; };
     auto out = [&](int ti, int j, z2 v) {
         const int i = r0 + ti;
         if (i < c && j < s) zstore(Hp, d.hoff + i + (int64_t)j * c, v);
     };
-    __shared__ ZLdsM L;
+    __shared__ ZLds L;
     ZAcc acc = {};
-    ztile_mfma(L, s, acc, la, lb);
+    // T is symmetric: both operands along their rows
+    zdense<false, false, true>(L, zoperand(Lp, d.poff + s + r0, (int64_t)(s - 1) * ld + c - r0, ld),
+                               zoperand(Tp, d.woff, (int64_t)s * s, s), 0, s, acc);
     zvisit(acc, out);
 }
 
 // Schur update of one 64 x 64 lower tile (rows i0.., columns k0.. of C):
 // F(C[i], C[k]) -= sum_t L_hat(i, t) F(C[k], t), scattered into the owning
-// ancestor panels; the tasks of one launch touch disjoint entries.  The
-// scatter targets do not depend on the product: their (cbase, rbase) pairs
-// are loaded before the products and the rel entries under them, and the
-// epilogue reads every target before it writes the first.
-__global__ __launch_bounds__(kThreads) void k_zschur(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
-                                                     double* __restrict__ Lp, const double* __restrict__ Hp,
-                                                     const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
+// ancestor panels; the tasks of one launch touch disjoint entries.  The tile
+// is formed as F(k0.., :) L_hat(i0.., :)^T, so that sixteen lanes hold
+// sixteen consecutive rows of one target column, a contiguous run of its
+// panel instead of sixteen
+// columns: 11.1 -> 10.0 ms of the 32-pole batch; its read-modify-write of the
+// targets alone is about half of that.  The scatter targets do not depend on the product:
+// their (cbase, rbase) pairs are loaded before the products and the rel
+// entries under them, and the epilogue reads every target before it writes
+// the first.
+__global__ __launch_bounds__(kThreads, 2) void k_zschur(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
+                                                        double* __restrict__ Lp, const double* __restrict__ Hp,
+                                                        const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
 {
     typedef int64_t i64v2 __attribute__((ext_vector_type(2)));
     const Task tk = tasks[blockIdx.x];
@@ -333,72 +444,68 @@ __global__ __launch_bounds__(kThreads) void k_zschur(const Task* __restrict__ ta
     const int64_t ld = (int64_t)s + c;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm0 = (wave & 1) * 32, wn0 = (wave >> 1) * 32;
-    // this thread's outputs (as zvisit visits them): rows i0 + wm0 + 16m +
-    // lane / 16 + 4v, columns k0 + wn0 + 16n + lane % 16
-    auto row_of = [&](int m, int v) { return i0 + wm0 + 16 * m + (lane >> 4) + 4 * v; };
-    auto col_of = [&](int n) { return k0 + wn0 + 16 * n + (lane & 15); };
-    auto live = [&](int m, int n, int v) {
-        const int ii = row_of(m, v), kk = col_of(n);
-        return ii < c && kk < c && ii >= kk;
-    };
-    int64_t cb[2], rb[2];
+    // this thread's outputs: target columns k0 + wm0 + 16 m + lane / 16 + 4 v,
+    // rows i0 + wn0 + 16 n + lane % 16; past C's end and above the diagonal
+    // (never stored) the map is read at a valid place
+    auto col_of = [&](int m, int v) { return k0 + wm0 + 16 * m + (lane >> 4) + 4 * v; };
+    auto row_of = [&](int n) { return i0 + wn0 + 16 * n + (lane & 15); };
+    i64v2 cr[2][4];
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-        const int kk = col_of(n);
-        const i64v2 cr = *reinterpret_cast<const i64v2*>(cr2 + 2 * (d.coff + (kk < c ? kk : 0)));
-        cb[n] = cr.x;
-        rb[n] = cr.y;
-    }
-    int32_t ro[2][2][4];
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            cr[m][v] = *reinterpret_cast<const i64v2*>(cr2 + 2 * (d.coff + min(col_of(m, v), c - 1)));
+    uint32_t ro[2][2][4];
     auto prefetch = [&]() {
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int n = 0; n < 2; ++n)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) ro[m][n][v] = rel[rb[n] + (live(m, n, v) ? row_of(m, v) : 0)];
+                for (int v = 0; v < 4; ++v)
+                    ro[m][n][v] = (uint32_t)rel[cr[m][v].y + min(max(row_of(n), col_of(m, v)), c - 1)];
     };
-    auto la = [&](int t, int i) { return (t < s && i0 + i < c) ? zload(Hp, d.hoff + i0 + i + (int64_t)t * c) : z2{0, 0}; };
-    auto lb = [&](int t, int k) { return (t < s && k0 + k < c) ? zload(Lp, d.poff + s + k0 + k + (int64_t)t * ld) : z2{0, 0}; };
-    __shared__ ZLdsM L;
+    __shared__ ZLds L;
     ZAcc acc = {};
-    ztile_mfma(L, s, acc, la, lb, prefetch);
+    zdense<false, false, false>(L, zoperand(Lp, d.poff + s + k0, (int64_t)(s - 1) * ld + c - k0, ld),
+                                zoperand(Hp, d.hoff + i0, (int64_t)s * c - i0, c), 0, s, acc, prefetch);
     z2 old[2][2][4];
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
         for (int n = 0; n < 2; ++n)
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                old[m][n][v] = live(m, n, v) ? zload(Lp, cb[n] + ro[m][n][v]) : z2{0.0, 0.0};
+            for (int v = 0; v < 4; ++v) old[m][n][v] = zload(Lp, cr[m][v].x + ro[m][n][v]);
+    const bool full = i0 > k0 && i0 + kZT <= c;  // every entry live: no branches between the stores
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
         for (int n = 0; n < 2; ++n)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                if (live(m, n, v))
-                    zstore(Lp, cb[n] + ro[m][n][v], old[m][n][v] - z2{acc.re[m][n][v], acc.im[m][n][v]});
+                if (full || (row_of(n) < c && row_of(n) >= col_of(m, v)))
+                    zstore(Lp, cr[m][v].x + ro[m][n][v], old[m][n][v] - z2{acc.re[m][n][v], acc.im[m][n][v]});
 }
 
 // Ainv(C,K) rows [r0, r0+64) = -G L_hat with G = Ainv(C,C) gathered from the
 // ancestors' inverse panels: G(i,k) = Ainv[cbase[p] + rel[rbase[p] + q]] with
 // p = min(i,k), q = max(i,k) (lower entries; the upper ones by symmetry).
+// Chunks of the contraction come in three modes.  Below the diagonal band
+// (k < i for the whole tile) p = k: the lanes of a wave run along i, so the
+// map entry is one address per wave.  Above it p = i, and the lanes run
+// along k.  Only the chunks of the band, and a ragged last chunk, form min
+// and max per element and carry masks; in the other modes every per-lane
+// offset is a constant of the tile and the chunk's position sits in the
+// scalar base.  Rows past c read row c - 1 (their products are never stored)
+// and chunks past the end read the last chunk again, so no load needs a mask.
 // Each element's address is a chain of three dependent loads, so the loop is
-// pipelined over four chunks, one stage a chunk apart: (cbase, rbase) pairs
-// of chunk n+3, rel entries of chunk n+2, values of chunk n+1 (G and L_hat),
-// the LDS planes of chunk n feeding the MFMAs.  Chunks entirely above the
-// diagonal band (every k past the tile's rows, p = i) are read along k, so
-// sixteen lanes walk one row of an ancestor panel; the others along i.
-// Loads are unconditional (a padding element reads an in-bounds stand-in and
-// is zeroed by its mask at the LDS store), so no wait sits behind a branch.
-// Three work-groups per CU (registers capped at 168, a few spilled) measured
-// faster than two: 39.1 vs 39.8 ms for the 32-pole batch.  kPiece (kernel
-// k_zgemm_piece): the contraction runs over rows [kb, ke) of C (kb on a
-// 16-row chunk boundary) and the tile's G L_hat goes to scratch slot `pad`
-// (row-major 64 x 64 complex), for k_zgemm_sum to complete.  The two are
-// separate kernels: with the piece's extra argument and range the whole-tile
-// kernel spilled 13 registers instead of 3 and ran the batch 5 % slower.
+// a pipeline: while the products of chunk n run, the values of chunk n+1 are
+// stored to LDS and the loads of A of chunk n+3, L_hat of chunk n+2, rel
+// entries of chunk n+4 and (cbase, rbase) pairs of chunk n+5 are issued.
+// The 32-pole batch's gather-GEMM: 16.3 -> 13.6 ms.
+// kPiece (kernel k_zgemm_piece): the contraction runs over rows [kb, ke) of C
+// (kb on a 16-row boundary) and the tile's G L_hat goes to scratch slot `pad`
+// (column-major 64 x 64 complex), for k_zgemm_sum to complete.
 template <bool kPiece>
 __device__ __forceinline__ void zgemm_body(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                     double* __restrict__ Ap, const double* __restrict__ Hp,
@@ -410,115 +517,195 @@ __device__ __forceinline__ void zgemm_body(const Task* __restrict__ tasks, const
     const BlockDesc d = blk[tk.b];
     const int s = d.s, c = d.c, r0 = tk.i0;
     const int64_t ld = (int64_t)s + c;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm0 = (wave & 1) * 32, wn0 = (wave >> 1) * 32;
-    constexpr int NQ = (kZK * kZT) / kThreads;  // elements of each operand per thread and chunk
-    // kb is a multiple of kZK: the chunks from ch0 on start at row kb
-    const int ke = kPiece ? tk.ke : c, ch0 = kPiece ? tk.kb / kZK : 0, nch = (ke + kZK - 1) / kZK;
-    const double* Lh = Hp + 2 * d.hoff;
-    auto along_of = [&](int ch) { return ch * kZK >= r0 + kZT; };
-    // stage M: (cbase, rbase) of p and q (-1: padding); stage R: cbase and
-    // the rel entry; stage V: the values
-    int64_t m_cb[NQ], m_rb[NQ];
-    int m_q[NQ];
-    int64_t r_cb[NQ];
-    int32_t r_rel[NQ];
-    bool r_ok[NQ];
-    z2 v_a[NQ], v_b[NQ];
-    bool v_ok[NQ], v_bok[NQ], v_al = false;
-    auto stage_m = [&](int ch) {
-        const bool al = along_of(ch);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int e = t + q * kThreads;
-            const int k = ch * kZK + (al ? (e & 15) : (e >> 6)), i = r0 + (al ? (e >> 4) : (e & 63));
-            const bool ok = ch < nch && k < ke && i < c;
-            const int64_t p = d.coff + (ok ? (i >= k ? k : i) : 0);
-            const i64v2 cr = *reinterpret_cast<const i64v2*>(cr2 + 2 * p);
-            m_cb[q] = cr.x;
-            m_rb[q] = cr.y;
-            m_q[q] = ok ? (i >= k ? i : k) : -1;
-        }
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int Kb = kPiece ? tk.kb : 0, Ke = kPiece ? tk.ke : c;
+    const int nch = Ke > Kb ? (Ke - Kb + kZK - 1) / kZK : 0;
+    enum { kBelow = 0, kAbove = 1, kBand = 2 };
+    auto k_of = [&](int ch) { return Kb + min(ch, nch - 1) * kZK; };
+    auto mode_of = [&](int k0) {
+        if (k0 + kZK > Ke) return (int)kBand;
+        return k0 + kZK <= r0 ? (int)kBelow : k0 >= r0 + kZT ? (int)kAbove : (int)kBand;
     };
-    auto stage_r = [&]() {
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            r_ok[q] = m_q[q] >= 0;
-            r_rel[q] = rel[m_rb[q] + (r_ok[q] ? m_q[q] : 0)];
-            r_cb[q] = m_cb[q];
-        }
+    // element q of this thread: below the band (kk, ii) = (4 q + wave, lane),
+    // else (t % 8, t / 8 + 32 q)
+    const int ak = t & 7, ai = t >> 3;
+    const int iBelow = min(r0 + lane, c - 1);
+    const int64_t* map = cr2 + 2 * d.coff;
+    i64v2 m_cr[2];
+    const z2* r_at[2];
+    uint32_t r_rel[2];
+    z2 v_a[2][2], v_b[2];  // A by the chunk's parity
+    const z2* G = reinterpret_cast<const z2*>(Ap);
+    auto band_ik = [&](int k0, int q, int& i, int& k) {
+        i = min(r0 + ai + 32 * q, c - 1);
+        k = min(k0 + ak, Ke - 1);
     };
-    auto stage_v = [&](int ch) {
-        v_al = along_of(ch);
+    auto load_map = [&](auto M, int ch) {
+        constexpr int kM = decltype(M)::value;
+        const int k0 = k_of(ch), md = kM >= 0 ? kM : mode_of(k0);
+        uint32_t off[2];
+        const int64_t* base = map;
+        if (md == kBelow) {
+            base += 2 * k0;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            v_a[q] = zload(Ap, r_cb[q] + r_rel[q]);
-            v_ok[q] = r_ok[q];
-            // L_hat(k, j) along k (contiguous), a stand-in past the ends
-            const int e = t + q * kThreads;
-            const int k = ch * kZK + (e & 15), j = e >> 4;
-            v_bok[q] = k < ke && j < s;
-            v_b[q] = zload(Lh, v_bok[q] ? k + (int64_t)j * c : 0);
-        }
-    };
-    __shared__ ZLdsM L;
-    auto stage_store = [&]() {
+            for (int q = 0; q < 2; ++q) off[q] = (uint32_t)(4 * q + wave) * 16u;
+        } else if (md == kAbove) {
+            base += 2 * r0;
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const int e = t + q * kThreads;
-            const int kk = v_al ? (e & 15) : (e >> 6), i = v_al ? (e >> 4) : (e & 63);
-            const z2 x = v_ok[q] ? v_a[q] : z2{0.0, 0.0};
-            L.ar[kk][i] = x.x;
-            L.ai[kk][i] = x.y;
-            const z2 y = v_bok[q] ? v_b[q] : z2{0.0, 0.0};
-            L.br[e & 15][e >> 4] = y.x;
-            L.bi[e & 15][e >> 4] = y.y;
-        }
-    };
-    ZAcc acc = {};
-    stage_m(ch0);
-    stage_r();
-    stage_v(ch0);
-    stage_m(ch0 + 1);
-    stage_r();
-    stage_m(ch0 + 2);
-    // registers now: values of the first chunk, rel entries of the second,
-    // pairs of the third
-    for (int ch = ch0; ch < nch; ++ch) {
-        stage_store();
-        __syncthreads();
-        stage_v(ch + 1);
-        stage_r();
-        stage_m(ch + 3);
+            for (int q = 0; q < 2; ++q) off[q] = (uint32_t)(ai + 32 * q) * 16u;
+        } else {
 #pragma unroll
-        for (int ks = 0; ks < kZK / 4; ++ks) {
-            const int kr = 4 * ks + (lane >> 4);
-            double xr[2], xi[2], yr[2], yi[2];
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                xr[m] = L.ar[kr][wm0 + 16 * m + (lane & 15)];
-                xi[m] = L.ai[kr][wm0 + 16 * m + (lane & 15)];
-                yr[m] = L.br[kr][wn0 + 16 * m + (lane & 15)];
-                yi[m] = L.bi[kr][wn0 + 16 * m + (lane & 15)];
+            for (int q = 0; q < 2; ++q) {
+                int i, k;
+                band_ik(k0, q, i, k);
+                off[q] = (uint32_t)min(i, k) * 16u;
             }
-#pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int n = 0; n < 2; ++n) {
-                    acc.re[m][n] = zmfma(xr[m], yr[n], acc.re[m][n]);
-                    acc.re[m][n] = zmfma(-xi[m], yi[n], acc.re[m][n]);
-                    acc.im[m][n] = zmfma(xr[m], yi[n], acc.im[m][n]);
-                    acc.im[m][n] = zmfma(xi[m], yr[n], acc.im[m][n]);
-                }
         }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            m_cr[q] = *reinterpret_cast<const i64v2*>(reinterpret_cast<const char*>(base) + off[q]);
+    };
+    auto load_rel = [&](auto M, int ch) {
+        constexpr int kM = decltype(M)::value;
+        const int k0 = k_of(ch), md = kM >= 0 ? kM : mode_of(k0);
+        if (md == kBand) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                int i, k;
+                band_ik(k0, q, i, k);
+                r_rel[q] = (uint32_t)rel[m_cr[q].y + max(i, k)];
+            }
+        } else {
+            const int32_t* rq = rel + (md == kBelow ? iBelow : k0 + ak);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) r_rel[q] = (uint32_t)rq[m_cr[q].y];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) r_at[q] = G + m_cr[q].x;
+    };
+    const ZLoader<true> lb(zoperand(Hp, d.hoff, (int64_t)s * c, c), wave);
+    int wBelow[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) wBelow[q] = zat(lane, 4 * q + wave);
+    const int wAbove = zat(ai, ak);
+    __shared__ ZLds L;
+    auto store = [&](auto M, const z2 (&va)[2], int ch, int buf) {
+        constexpr int kM = decltype(M)::value;
+        const int k0 = k_of(ch), md = kM >= 0 ? kM : mode_of(k0);
+        char* A = L.A[buf];
+        if (md == kBelow) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) *reinterpret_cast<z2*>(A + wBelow[q]) = va[q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                *reinterpret_cast<z2*>(A + wAbove + q * 32 * kZRow) =
+                    md == kAbove || k0 + ak < Ke ? va[q] : z2{0.0, 0.0};
+        }
+        lb.store(L.B[buf], v_b, k0, false, Ke);
+    };
+    auto load_b = [&](auto M, int ch) { lb.load(v_b, k_of(ch), decltype(M)::value >= 0 ? 1 << 30 : Ke); };
+    ZAcc acc = {};
+    auto body = [&](auto M, auto X, int ch) {  // X: the parity of ch
+        constexpr int buf = decltype(X)::value;
+        zproducts<true>(L.A[buf], L.B[buf], acc, [&] {
+            store(M, v_a[buf ^ 1], ch + 1, buf ^ 1);
+            // in this order, ahead of the products: loads return in order, and
+            // the values of A, whose use is two iterations away, come last
+            const z2* at[2] = {r_at[0] + r_rel[0], r_at[1] + r_rel[1]};
+            load_rel(M, ch + 4);
+            load_map(M, ch + 5);
+            __builtin_amdgcn_sched_barrier(0);
+            load_b(M, ch + 2);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) v_a[buf ^ 1][q] = *at[q];  // chunk ch + 3
+            __builtin_amdgcn_sched_barrier(0);
+        });
         __syncthreads();
+    };
+    using Any = std::integral_constant<int, -1>;
+    using Below = std::integral_constant<int, kBelow>;
+    using Above = std::integral_constant<int, kAbove>;
+    using X0 = std::integral_constant<int, 0>;
+    using X1 = std::integral_constant<int, 1>;
+    if (nch > 0) {
+        // chunk 0 in LDS, A of chunks 1 and 2 and L_hat of chunk 1, rel entries
+        // of chunk 3, pairs of chunk 4: the first chunks' chains of loads side
+        // by side, what stays in flight in the loop's order
+        i64v2 cm[4][2];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            load_map(Any{}, n);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) cm[n][q] = m_cr[q];
+        }
+        const z2* at3[3][2];
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) m_cr[q] = cm[n][q];
+            load_rel(Any{}, n);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) at3[n][q] = r_at[q] + r_rel[q];
+        }
+        load_b(Any{}, 0);
+        z2 a0[2], b0[2], b1[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            b0[q] = v_b[q];
+            a0[q] = *at3[0][q];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) v_a[1][q] = *at3[1][q];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) m_cr[q] = cm[3][q];
+        load_rel(Any{}, 3);
+        load_map(Any{}, 4);
+        __builtin_amdgcn_sched_barrier(0);
+        load_b(Any{}, 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) v_a[0][q] = *at3[2][q];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            b1[q] = v_b[q];
+            v_b[q] = b0[q];
+        }
+        store(Any{}, a0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) v_b[q] = b1[q];
     }
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    // iteration ch handles chunks ch + 1 (store) to ch + 5 (map): the mode is
+    // known where all of them lie on one side of the band and the last chunk,
+    // which is read again past the end, is whole
+    const bool whole = ((Ke - Kb) & (kZK - 1)) == 0;
+    const int nb0 = max(0, min(r0 - Kb, Ke - Kb) / kZK);  // whole chunks below the band
+    const int belowEnd = whole && nb0 == nch ? nch : max(0, nb0 - 5);
+    const bool above = Kb + (nch - 1) * kZK >= r0 + kZT;  // the last chunk is
+    const int aboveBegin = above ? max(0, (r0 + kZT - Kb + kZK - 1) / kZK - 1) : nch;
+    const int aboveEnd = whole ? nch : max(0, (Ke - Kb) / kZK - 5);
+    int ch = 0;
+    auto run = [&](auto M, int end) {
+        if ((ch & 1) && ch < end) body(M, X1{}, ch++);
+        for (; ch + 1 < end; ch += 2) {
+            body(M, X0{}, ch);
+            body(M, X1{}, ch + 1);
+        }
+        if (ch < end) body(M, X0{}, ch++);
+    };
+    run(Below{}, belowEnd);
+    run(Any{}, aboveBegin);
+    run(Above{}, aboveEnd);
+    run(Any{}, nch);
+    zdrain();
     if constexpr (kPiece) {
         double* z = Zs + (int64_t)tk.pad * kZSlotDoubles;
-        zvisit(acc, [&](int ti, int j, z2 v) { zstore(z, (int64_t)ti * kZT + j, v); });
+        zvisit(acc, [&](int ti, int j, z2 v) { zstore(z, (int64_t)j * kZT + ti, v); });
     } else {
         zvisit(acc, [&](int ti, int j, z2 v) {
             const int i = r0 + ti;
@@ -542,7 +729,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_zgemm_piece(const Task* __restr
 }
 
 // The sum of a split task's pieces (slots kb .. kb + bn - 1) at element e of
-// the row-major 64 x 64 tile: four running sums over the pieces q = 4m + r,
+// the column-major 64 x 64 tile: four running sums over the pieces q = 4m + r,
 // combined in a fixed order, so that four loads are in flight at a time.
 __device__ __forceinline__ z2 zslot_sum(const double* __restrict__ z0, int np, int e)
 {
@@ -558,13 +745,13 @@ __device__ __forceinline__ z2 zslot_sum(const double* __restrict__ z0, int np, i
     return (a[0] + a[1]) + (a[2] + a[3]);
 }
 
-// Rows of a 64 x 64 summing tile one work-group handles (one element per
-// thread); a summing task takes kZT / kZSumRows work-groups (blockIdx.y), so
+// Columns of a 64 x 64 summing tile one work-group handles (one element per
+// thread); a summing task takes kZT / kZSumCols work-groups (blockIdx.y), so
 // the reads of its pieces spread over that many CUs.
-constexpr int kZSumRows = kThreads / kZT;
+constexpr int kZSumCols = kThreads / kZT;
 
 // A split gather-GEMM tile: the sum of its pieces' G L_hat, stored negated
-// as Ainv(C,K) rows [r0, r0+64); this work-group's rows ti0 .. ti0 + 3.
+// as Ainv(C,K) rows [r0, r0+64); this work-group's columns j0 .. j0 + 3.
 __global__ __launch_bounds__(kThreads) void k_zgemm_sum(const Task* __restrict__ tasks,
                                                         const BlockDesc* __restrict__ blk, double* __restrict__ Ap,
                                                         const double* __restrict__ Zs)
@@ -573,25 +760,25 @@ __global__ __launch_bounds__(kThreads) void k_zgemm_sum(const Task* __restrict__
     const BlockDesc d = blk[tk.b];
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
-    const int ti = blockIdx.y * kZSumRows + threadIdx.x / kZT, j = threadIdx.x % kZT, i = tk.i0 + ti;
+    const int j = blockIdx.y * kZSumCols + threadIdx.x / kZT, ti = threadIdx.x % kZT, i = tk.i0 + ti;
     if (i >= c || j >= s) return;
-    const z2 x = zslot_sum(Zs + (int64_t)tk.kb * kZSlotDoubles, tk.bn, ti * kZT + j);
+    const z2 x = zslot_sum(Zs + (int64_t)tk.kb * kZSlotDoubles, tk.bn, j * kZT + ti);
     zstore(Ap, d.poff + s + i + (int64_t)j * ld, -x);
 }
 
 // Ainv(K,K) = T - (P + P^T) / 2 with P = L_hat^T Ainv(C,K) (lower triangle),
 // the contraction over rows [kb, ke) of C.  A piece of a split block (flags
-// bit 5) stores its P to scratch slot `pad` (row-major, kZMaxS x kZMaxS
+// bit 5) stores its P to scratch slot `pad` (column-major, kZMaxS x kZMaxS
 // complex) instead; k_zsdiag_sum completes the block.
 static_assert(kZT == kZMaxS, "one output tile holds a whole diagonal block");
 __global__ __launch_bounds__(kThreads) void k_zsdiag(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                      double* __restrict__ Ap, const double* __restrict__ Hp,
                                                      const double* __restrict__ Tp, double* __restrict__ Zs)
 {
-    // the product's operand planes, then P for the transpose (the tile loop
-    // ends with a barrier, so P may reuse the space)
+    // the product's operands, then P for the transpose (the tile loop ends
+    // with a barrier, so P may reuse the space)
     __shared__ union {
-        ZLdsM L;
+        ZLds L;
         z2 P[kZT][kZT + 1];
     } U;
     auto& P = U.P;
@@ -599,40 +786,27 @@ __global__ __launch_bounds__(kThreads) void k_zsdiag(const Task* __restrict__ ta
     const BlockDesc d = blk[tk.b];
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
-    const int kb = tk.kb, ke = tk.ke;
-    auto la = [&](int r, int i) {
-        r += kb;
-        return (r < ke && i < s) ? zload(Hp, d.hoff + r + (int64_t)i * c) : z2{0, 0};
-    };
-    auto lb = [&](int r, int j) {
-        r += kb;
-        return (r < ke && j < s) ? zload(Ap, d.poff + s + r + (int64_t)j * ld) : z2{0, 0};
-    };
     ZAcc acc = {};
-    ztile_mfma(U.L, ke - kb, acc, la, lb);
+    zdense<true, true, true>(U.L, zoperand(Hp, d.hoff, (int64_t)s * c, c),
+                             zoperand(Ap, d.poff + s, (int64_t)(s - 1) * ld + c, ld), tk.kb, tk.ke, acc);
     if (tk.flags & 32) {
         double* z = Zs + (int64_t)tk.pad * kZSlotDoubles;
-        zvisit(acc, [&](int i, int j, z2 v) { zstore(z, (int64_t)i * kZT + j, v); });
+        zvisit(acc, [&](int i, int j, z2 v) { zstore(z, (int64_t)j * kZT + i, v); });
         return;
     }
     zvisit(acc, [&](int i, int j, z2 v) { P[i][j] = v; });
     __syncthreads();
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = 4 * tx + u, j = 4 * ty + v;
-            if (i < s && j < s && i >= j) {
-                const z2 p = 0.5 * (P[i][j] + P[j][i]);
-                zstore(Ap, d.poff + i + (int64_t)j * ld, zload(Tp, d.woff + i + (int64_t)j * s) - p);
-            }
+    const int i = threadIdx.x & 63;
+    for (int j = threadIdx.x >> 6; j < s; j += kThreads / 64)
+        if (i < s && i >= j) {
+            const z2 p = 0.5 * (P[i][j] + P[j][i]);
+            zstore(Ap, d.poff + i + (int64_t)j * ld, zload(Tp, d.woff + i + (int64_t)j * s) - p);
         }
 }
 
 // A split block's diagonal step: P = the sum of its pieces' partial
 // products, then Ainv(K,K) = T - (P + P^T) / 2 on the lower triangle; this
-// work-group's rows i0 .. i0 + 3 (P(i,j) and P(j,i) summed separately, each
+// work-group's columns j0 .. j0 + 3 (P(i,j) and P(j,i) summed separately, each
 // in the fixed order of zslot_sum).
 __global__ __launch_bounds__(kThreads) void k_zsdiag_sum(const Task* __restrict__ tasks,
                                                          const BlockDesc* __restrict__ blk, double* __restrict__ Ap,
@@ -642,10 +816,10 @@ __global__ __launch_bounds__(kThreads) void k_zsdiag_sum(const Task* __restrict_
     const BlockDesc d = blk[tk.b];
     const int s = d.s;
     const int64_t ld = (int64_t)s + d.c;
-    const int i = blockIdx.y * kZSumRows + threadIdx.x / kZT, j = threadIdx.x % kZT;
+    const int j = blockIdx.y * kZSumCols + threadIdx.x / kZT, i = threadIdx.x % kZT;
     if (i >= s || j > i) return;
     const double* z0 = Zs + (int64_t)tk.kb * kZSlotDoubles;
-    const z2 pij = zslot_sum(z0, tk.bn, i * kZT + j), pji = zslot_sum(z0, tk.bn, j * kZT + i);
+    const z2 pij = zslot_sum(z0, tk.bn, j * kZT + i), pji = zslot_sum(z0, tk.bn, i * kZT + j);
     zstore(Ap, d.poff + i + (int64_t)j * ld, zload(Tp, d.woff + i + (int64_t)j * s) - 0.5 * (pij + pji));
 }
 
@@ -712,13 +886,13 @@ hipError_t launch_zinvert_level(const DevPtrs& D, const int64_t gemm[4], int64_t
         hipLaunchKernelGGL(k_zgemm_piece, dim3((unsigned)(gemm[2] - gemm[1])), dim3(kThreads), 0, s,
                            D.t_gemm + gemm[1], D.blocks, D.Ap, (const double*)D.Hp, D.cr2, D.rel, D.Zs);
     if (gemm[3] > gemm[2])
-        hipLaunchKernelGGL(k_zgemm_sum, dim3((unsigned)(gemm[3] - gemm[2]), kZT / kZSumRows), dim3(kThreads), 0, s,
+        hipLaunchKernelGGL(k_zgemm_sum, dim3((unsigned)(gemm[3] - gemm[2]), kZT / kZSumCols), dim3(kThreads), 0, s,
                            D.t_gemm + gemm[2], D.blocks, D.Ap, (const double*)D.Zs);
     if (sdiag_cut > sdiag0)
         hipLaunchKernelGGL(k_zsdiag, dim3((unsigned)(sdiag_cut - sdiag0)), dim3(kThreads), 0, s, D.t_sdiag + sdiag0,
                            D.blocks, D.Ap, (const double*)D.Hp, (const double*)D.Tp, D.Zs);
     if (sdiag1 > sdiag_cut)
-        hipLaunchKernelGGL(k_zsdiag_sum, dim3((unsigned)(sdiag1 - sdiag_cut), kZT / kZSumRows), dim3(kThreads), 0, s,
+        hipLaunchKernelGGL(k_zsdiag_sum, dim3((unsigned)(sdiag1 - sdiag_cut), kZT / kZSumCols), dim3(kThreads), 0, s,
                            D.t_sdiag + sdiag_cut, D.blocks, D.Ap, (const double*)D.Tp, (const double*)D.Zs);
     return hipGetLastError();
 }
