@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "lanes.hpp"
 #include "plan.hpp"
 #include "tiles.hpp"
 
@@ -1362,25 +1363,6 @@ __device__ void ldlt_global(const BlockDesc d, double* __restrict__ Lp, double* 
     }
 }
 
-// f(integral_constant<int, I>) for I = I0 .. N - 1, each call with its own
-// compile-time index (register arrays indexed by it stay in registers)
-template <int I0, int N>
-struct StaticFor {
-    template <class Fn>
-    __device__ __forceinline__ static void run(Fn&& f)
-    {
-        f(std::integral_constant<int, I0>{});
-        StaticFor<I0 + 1, N>::run(f);
-    }
-};
-template <int N>
-struct StaticFor<N, N> {
-    template <class Fn>
-    __device__ __forceinline__ static void run(Fn&&)
-    {
-    }
-};
-
 // 1 / d: hardware reciprocal and two Newton steps (each squares the relative
 // error; the first estimate is good to about 2^-26)
 __device__ __forceinline__ double recip(double d)
@@ -1424,29 +1406,6 @@ struct alignas(16) DiagLds {
     double Lb[2][16][kDiagPad];  // -L_pp
     double D[2][16];
 };
-
-// x of lane J of each row of 16 lanes, in every lane of the row
-template <int J>
-__device__ __forceinline__ double row_lane(double x)
-{
-    return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + J, 0xF, 0xF, true));
-}
-// row G (of the wave's four rows of 16 lanes) in every row: halves, then
-// neighbouring rows swapped between two copies
-template <int G>
-__device__ __forceinline__ unsigned row_copy32(unsigned x)
-{
-    const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    const unsigned y = (G & 2) ? a[1] : a[0];
-    const auto b = __builtin_amdgcn_permlane16_swap(y, y, false, false);
-    return (G & 1) ? b[1] : b[0];
-}
-template <int G>
-__device__ __forceinline__ double row_copy(double x)
-{
-    return __hiloint2double((int)row_copy32<G>((unsigned)__double2hiint(x)),
-                            (int)row_copy32<G>((unsigned)__double2loint(x)));
-}
 
 // Gauss-Jordan inversion of a symmetric 16 x 16 block, lane (m, g) holding
 // row m, columns g + 4 v.  Pivot j: l = column j / d_j; every row m != j

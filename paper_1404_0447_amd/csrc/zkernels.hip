@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "kernels.hpp"
+#include "lanes.hpp"
 #include "plan.hpp"
 #include "tiles.hpp"
 
@@ -251,154 +252,228 @@ __device__ __forceinline__ z2 zrecip(z2 b)
 }
 
 // ---------------------------------------------------------------------------
-// Diagonal block by the symmetric sweep (Gauss-Jordan) in registers: pivot p
-// in natural order (d = M(p,p), c = column p) sets M(i,j) -= c_i c_j / d,
-// M(i,p) = c_i / d, M(p,p) = -1/d, plain (not conjugate) products, so after
-// all s pivots M = -F_KK^{-1} = -T_K; only T leaves the kernel.  Thread
-// (tx, ty) holds the lower 16 x 16 sub-blocks' entries (tx + 16a, ty + 16b),
-// a >= b; a pivot's column goes through LDS (two alternating slots, one
-// barrier per pivot).  Row and column p are cleared by lane masks and the
-// pivot's own entries of the update vectors set to -1/d (rows) and -1
-// (columns), so one rank-1 pass also writes the new row and column p.  Per
-// pivot the slots holding the next pivot's column are updated first and the
-// column published; the rest follow the barrier, while that column's LDS
-// reads are in flight.  s <= 64, one work-group per block; a zero or
-// non-finite pivot latches its column.
+// Diagonal block, s <= 64: T_K = F_KK^{-1} by symmetric Gauss-Jordan sweeps
+// over pivot blocks of 16 columns, natural order, plain (not conjugate)
+// products.  Sweeping block p, with C(R) = M(R, p) and Q = M(p, p)^{-1}:
+//   M(I, J) -= (C(I) Q) C(J)^T  (I, J != p),  M(R, p) = C(R) Q,  M(p, p) = -Q;
+// after the last block M = -F_KK^{-1} = -T_K; only T leaves the kernel.
+//
+// What bounds it is the chain of s dependent pivots: wave 0 inverts the pivot
+// blocks in its own registers (zgj16: lane broadcasts, no LDS, no barrier)
+// while the other three waves update the tiles of M, which live in LDS, with
+// MFMA products.  A block of 64 columns: 24 us against 50 us when every
+// pivot's column went through LDS behind a barrier (one pole: 5.2 -> 4.3 ms).  Rows and columns past s
+// hold the identity.  A zero or non-finite pivot latches its column.
 // ---------------------------------------------------------------------------
-template <int N, class Fn>
-__device__ __forceinline__ void zfor(Fn&& f)
+// 16 complex entries a row and 16 bytes: conflict-free operand reads
+constexpr int kZDiagPad = 17;
+constexpr int kZNB = kZT / 16, kZNT = kZNB * (kZNB + 1) / 2;
+struct ZDiagLds {
+    z2 M[kZNT][16][kZDiagPad];  // tile (I, J), I >= J, at I (I + 1) / 2 + J
+    z2 C[kZT][kZDiagPad], N[kZT][kZDiagPad];
+};
+
+// Gauss-Jordan inversion of a symmetric 16 x 16 block, lane (m, g) holding
+// row m, columns g + 4 v.  Pivot j: l = column j / d_j; every row m != j
+// loses l_m times row j, and column j becomes -l (1 in row j).  Row j itself
+// is scaled by 1 / d_j once, at the end.  dm: d_m.
+__device__ __forceinline__ void zgj16(z2 (&P)[4], z2& dm, const int m, const int g)
 {
-    if constexpr (N > 0) {
-        zfor<N - 1>(f);
-        f(std::integral_constant<int, N - 1>{});
-    }
+    z2 im = {0.0, 0.0};  // 1 / d_m
+    StaticFor<0, 16>::run([&](auto jc) {
+        constexpr int j = decltype(jc)::value, gj = j & 3, vj = j >> 2;
+        const z2 c = {row_copy<gj>(P[vj].x), row_copy<gj>(P[vj].y)};  // column j
+        const z2 dj = {row_lane<j>(c.x), row_lane<j>(c.y)};
+        const z2 inv = zrecip(dj);
+        const z2 l = zmul(c, inv);
+        const z2 lz = m == j ? z2{0.0, 0.0} : l;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const z2 r = {row_lane<j>(P[v].x), row_lane<j>(P[v].y)};
+            P[v].x = fma(lz.y, r.y, fma(-lz.x, r.x, P[v].x));
+            P[v].y = fma(-lz.y, r.x, fma(-lz.x, r.y, P[v].y));
+        }
+        if (g == gj) P[vj] = m == j ? z2{1.0, 0.0} : -l;
+        if (m == j) {
+            im = inv;
+            dm = dj;
+        }
+    });
+#pragma unroll
+    for (int v = 0; v < 4; ++v) P[v] = zmul(P[v], im);
 }
 
-__device__ __forceinline__ z2 zuniform(z2 v)
+// (re, im) += a b, 16 x 16 blocks as lane (m, g) holds them: entry
+// (m, g + 4 v) of a, and of b transposed, in register v
+__device__ __forceinline__ void zblock_mma(const z2 (&a)[4], const z2 (&b)[4], zd4& re, zd4& im)
 {
-    const double x = v.x, y = v.y;
-    const int a = __builtin_amdgcn_readfirstlane(__double2loint(x)), b = __builtin_amdgcn_readfirstlane(__double2hiint(x));
-    const int c = __builtin_amdgcn_readfirstlane(__double2loint(y)), e = __builtin_amdgcn_readfirstlane(__double2hiint(y));
-    return z2{__hiloint2double(b, a), __hiloint2double(e, c)};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        re = zmfma(a[v].x, b[v].x, re);
+        im = zmfma(a[v].x, b[v].y, im);
+        re = zmfma(-a[v].y, b[v].y, re);
+        im = zmfma(a[v].y, b[v].x, im);
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void k_zdiag(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                     double* __restrict__ Lp, double* __restrict__ Tp,
                                                     unsigned long long* __restrict__ status)
 {
-    constexpr int NB = kZT / 16;
-    constexpr int NS = NB * (NB + 1) / 2;
-    __shared__ z2 cb[2][kZT];
+    __shared__ ZDiagLds S;
     const BlockDesc d = blk[tasks[blockIdx.x].b];
-    const int s = d.s, tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int s = d.s, nb = (s + 15) >> 4;
     const int64_t ld = (int64_t)d.s + d.c;
-    auto slot = [](int a, int b) { return a * (a + 1) / 2 + b; };
-    z2 M[NS];
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = 0; b <= a; ++b) {
-            const int i = tx + 16 * a, k = ty + 16 * b;
-            z2 v = {0.0, 0.0};
-            if (i < s && k < s) v = i >= k ? zload(Lp, d.poff + i + (int64_t)k * ld) : zload(Lp, d.poff + k + (int64_t)i * ld);
-            M[slot(a, b)] = v;
-        }
-    // column p into col: rows at and below p's sub-block row from the
-    // column's owners, the rows above from the owners of row p
-    auto publish = [&](int p, z2* col) {
-        const int pt = p & 15, pb = p >> 4;
-        zfor<NB>([&](auto c) {
-            constexpr int b0 = decltype(c)::value;
-            if (pb == b0) {
-                if (ty == pt) {
-#pragma unroll
-                    for (int a = b0; a < NB; ++a) col[tx + 16 * a] = M[slot(a, b0)];
-                }
-                if (tx == pt) {
-#pragma unroll
-                    for (int b = 0; b < b0; ++b) col[ty + 16 * b] = M[slot(b0, b)];
-                }
-            }
-        });
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const bool chain = wave == 0;
+    constexpr int NK = kThreads / 64 - 1;  // tile waves
+    const int wk = wave - 1;
+    auto tile = [](int I, int J) { return (int)((unsigned)(I * (I + 1)) >> 1) + J; };
+    auto tile_of = [&](int t, int& I, int& J) {  // row by row: rows 1 .. 3 start at tiles 1, 3, 6
+        I = __builtin_popcount((1u << 1 | 1u << 3 | 1u << 6) & ((2u << t) - 1));
+        J = t - tile(I, 0);
     };
-    if (s > 0) publish(0, cb[0]);
+    z2 Q[4];
+    // invert the pivot block P of step p and store -Q
+    auto pivots = [&](int p, const z2 (&P)[4]) {
+        z2 dm = {1.0, 0.0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) Q[v] = P[v];
+        zgj16(Q, dm, m, g);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) S.M[tile(p, p)][m][g + 4 * v] = -Q[v];
+        if (g == 0 && 16 * p + m < s && !((dm.x != 0.0 || dm.y != 0.0) && isfinite(dm.x) && isfinite(dm.y)))
+            atomicMin(status, (unsigned long long)(d.first + 16 * p + m));
+    };
+    // F(i, j) of tile (I, J), the identity past s
+    auto load_tile = [&](int I, int J, z2 (&x)[4]) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * I + m, j = 16 * J + g + 4 * v;
+            const int a = min(max(i, j), s - 1), b = min(min(i, j), s - 1);
+            const z2 f = zload(Lp, d.poff + a + (int64_t)b * ld);
+            x[v] = i < s && j < s ? f : z2{i == j ? 1.0 : 0.0, 0.0};
+        }
+    };
+    if (chain) {
+        z2 P[4];
+        load_tile(0, 0, P);
+        pivots(0, P);
+    } else {
+        constexpr int NL = (kZNT - 1 + NK - 1) / NK;
+        z2 x[NL][4];
+        const int nt = nb * (nb + 1) / 2;
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            int I, J;
+            tile_of(min(1 + u * NK + wk, nt - 1), I, J);
+            load_tile(I, J, x[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < NL; ++u) {
+            const int t = 1 + u * NK + wk;
+            if (t < nt) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) S.M[t][m][g + 4 * v] = x[u][v];
+            }
+        }
+    }
     __syncthreads();
-    // column p as read from LDS: rows tx + 16a, rows ty + 16b, the pivot
-    z2 ri[NB], rk[NB], dp;
-    auto read_col = [&](int p) {
-        const z2* col = cb[p & 1];
+    for (int p = 0; p < nb; ++p) {
+        const bool more = p + 1 < nb;
+        // C(R), N(R)^T = -Q C(R)^T and M(R, p) = -N(R), row R
+        auto row = [&](const z2 (&nQ)[4], int R, z2 (&c)[4], z2 (&n)[4]) {
+            z2* tp = &S.M[tile(max(R, p), min(R, p))][0][0];
+            if (R > p) {
 #pragma unroll
-        for (int a = 0; a < NB; ++a) ri[a] = col[tx + 16 * a];
+                for (int v = 0; v < 4; ++v) c[v] = tp[m * kZDiagPad + g + 4 * v];
+            } else {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) rk[b] = col[ty + 16 * b];
-        dp = zuniform(col[p]);
-    };
-    if (s > 0) read_col(0);
-    int bad = -1;
-    for (int p = 0; p < s; ++p) {
-        if (!((dp.x != 0.0 || dp.y != 0.0) && isfinite(dp.x) && isfinite(dp.y))) {
-            bad = p;
-            break;
-        }
-        const z2 inv = zrecip(dp);
-        bool rz[NB], cz[NB];
-        z2 si[NB], sk[NB];
+                for (int v = 0; v < 4; ++v) c[v] = tp[(g + 4 * v) * kZDiagPad + m];
+            }
+            zd4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+            zblock_mma(nQ, c, re, im);
 #pragma unroll
-        for (int a = 0; a < NB; ++a) {
-            rz[a] = tx + 16 * a == p;
-            si[a] = rz[a] ? -inv : zmul(ri[a], inv);
-        }
+            for (int v = 0; v < 4; ++v) S.C[16 * R + m][g + 4 * v] = c[v];
+            zdrain();
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            cz[b] = ty + 16 * b == p;
-            sk[b] = cz[b] ? z2{-1.0, 0.0} : rk[b];
-        }
-        auto upd = [&](int a, int b) {
-            const z2 m = (rz[a] || cz[b]) ? z2{0.0, 0.0} : M[slot(a, b)];
-            M[slot(a, b)] = m - zmul(si[a], sk[b]);
+            for (int v = 0; v < 4; ++v) {
+                n[v] = z2{re[v], im[v]};
+                S.N[16 * R + m][g + 4 * v] = n[v];
+            }
+            if (R > p) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) tp[m * kZDiagPad + g + 4 * v] = -n[v];
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) tp[(g + 4 * v) * kZDiagPad + m] = -n[v];
+            }
         };
-        // the slots of the next pivot's sub-block column and row first, so
-        // that its column is published (and read) while the rest update
-        const int q = p + 1, qb = q >> 4;
-        if (qb >= NB) {  // the last pivot of a full block
+        z2 nQ[4], c[4], n[4], P[4];
 #pragma unroll
-            for (int a = 0; a < NB; ++a)
+        for (int v = 0; v < 4; ++v) nQ[v] = chain ? -Q[v] : S.M[tile(p, p)][m][g + 4 * v];
+        if (chain) {
+            // row p + 1, and the next pivot block with it (the last step has
+            // no such row: then row 0)
+            if (more) {
 #pragma unroll
-                for (int b = 0; b <= a; ++b) upd(a, b);
-        }
-        zfor<NB>([&](auto cc) {
-            constexpr int b0 = decltype(cc)::value;
-            if (qb == b0) {
-#pragma unroll
-                for (int a = b0; a < NB; ++a) upd(a, b0);
-#pragma unroll
-                for (int b = 0; b < b0; ++b) upd(b0, b);
-                if (q < s) publish(q, cb[q & 1]);
-                __syncthreads();
-                if (q < s) read_col(q);
-#pragma unroll
-                for (int a = 0; a < NB; ++a)
-#pragma unroll
-                    for (int b = 0; b <= a; ++b)
-                        if (a != b0 && b != b0) upd(a, b);
+                for (int v = 0; v < 4; ++v) P[v] = S.M[tile(p + 1, p + 1)][m][g + 4 * v];
             }
-        });
-    }
-    if (bad >= 0) {  // every thread took the same branch
-        if (tid == 0) atomicMin(status, (unsigned long long)(d.first + bad));
-        return;
-    }
-    // T = -M from the lower triangle (exactly symmetric)
+            if (nb > 1) row(nQ, more ? p + 1 : 0, c, n);
+            if (more) {
+                zd4 re = {P[0].x, P[1].x, P[2].x, P[3].x}, im = {P[0].y, P[1].y, P[2].y, P[3].y};
+                zblock_mma(c, n, re, im);
+                zdrain();
 #pragma unroll
-    for (int a = 0; a < NB; ++a)
+                for (int v = 0; v < 4; ++v) P[v] = z2{re[v], im[v]};
+            }
+        } else {
+            // p + 2, p + 3, .. cyclically, without p
+            const int r = 1 + wk, R = p + 1 + r < nb ? p + 1 + r : p + 1 + r - nb;
+            if (r < nb - 1) row(nQ, R, c, n);
+        }
+        __syncthreads();
+        if (chain) {
+            if (more) pivots(p + 1, P);
+        } else {
+            // M(I, J) += N(I) C(J)^T over the tiles outside row and column p
+            // and the next pivot block
+            const int nt = nb * (nb - 1) / 2;
+            for (int t = wk; t < nt; t += NK) {
+                int I, J;
+                tile_of(t, I, J);
+                I += I >= p;
+                J += J >= p;
+                if (I == p + 1 && J == p + 1) continue;
+                z2(*tp)[kZDiagPad] = S.M[tile(I, J)];
+                z2 a[4], b[4], x[4];
 #pragma unroll
-        for (int b = 0; b <= a; ++b) {
-            const int i = tx + 16 * a, j = ty + 16 * b;
-            if (i < s && j < s && i >= j) {
-                zstore(Tp, d.woff + i + (int64_t)j * s, -M[slot(a, b)]);
-                zstore(Tp, d.woff + j + (int64_t)i * s, -M[slot(a, b)]);
+                for (int v = 0; v < 4; ++v) {
+                    x[v] = tp[m][g + 4 * v];
+                    a[v] = S.C[16 * J + m][g + 4 * v];
+                    b[v] = S.N[16 * I + m][g + 4 * v];
+                }
+                zd4 re = {x[0].x, x[1].x, x[2].x, x[3].x}, im = {x[0].y, x[1].y, x[2].y, x[3].y};
+                zblock_mma(a, b, re, im);
+                zdrain();
+#pragma unroll
+                for (int v = 0; v < 4; ++v) tp[m][g + 4 * v] = z2{re[v], im[v]};
             }
         }
+        __syncthreads();
+    }
+    // T = -M, made exactly symmetric from the lower triangle
+    for (int t = wave; t < nb * (nb + 1) / 2; t += kThreads / 64) {
+        int I, J;
+        tile_of(t, I, J);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int k = g + 4 * v, i = 16 * I + m, j = 16 * J + k, i2 = 16 * I + k, j2 = 16 * J + m;
+            if (i < s && j <= i) zstore(Tp, d.woff + i + (int64_t)j * s, -S.M[t][m][k]);
+            if (i2 < s && j2 < i2) zstore(Tp, d.woff + j2 + (int64_t)i2 * s, -S.M[t][k][m]);
+        }
+    }
 }
 
 // L_hat(C,K) rows [r0, r0+64) = F(C,K) T_K
