@@ -298,16 +298,25 @@ void level_variants(const selinv_plan_s* P, const std::vector<Task>& q, const st
     var.assign(off.empty() ? 0 : off.size() - 1, 0);
     for (size_t l = 0; l + 1 < off.size(); l++) {
         bool tiled = false;
-        int widest = 0;
+        int widest = 0, sb_s = 0, sb_c = 0;
         for (int64_t k = off[l]; k < off[l + 1]; k++) {
             const int op = q[k].flags >> 8;
-            if (op == sb_op) continue;
+            if (op == sb_op) {
+                for (int b : {q[k].b, q[k].i0, q[k].j0, q[k].bn}) {
+                    if (b < 0) continue;
+                    sb_s = std::max(sb_s, P->blocks[b].s);
+                    sb_c = std::max(sb_c, P->blocks[b].c);
+                }
+                continue;
+            }
             tiled = true;
             if (op == qLdlt || op == qMbFactor) widest = std::max(widest, P->blocks[q[k].b].s);
             if (op == qGemm || op == qMbInvert) widest = std::max(widest, q[k].bn);
         }
-        if (factor) var[l] = !tiled ? kLightFactor : widest <= 32 ? kFactor32 : widest <= 64 ? kFactor64 : kFactor128;
-        else var[l] = !tiled ? kLightInvert : widest <= 32 ? kInvert32 : widest <= 64 ? kInvert64 : kInvert128;
+        if (tiled && factor) var[l] = widest <= 32 ? kFactor32 : widest <= 64 ? kFactor64 : kFactor128;
+        else if (tiled) var[l] = widest <= 32 ? kInvert32 : widest <= 64 ? kInvert64 : kInvert128;
+        else if (factor) var[l] = sb_s <= 4 ? kLightFactor4 : sb_s <= 8 ? kLightFactor8 : kLightFactor16;
+        else var[l] = sb_c <= 8 ? kLightInvert8 : sb_c <= 16 ? kLightInvert16 : kLightInvert256;
     }
 }
 
@@ -945,7 +954,7 @@ selinv_status run_persistent(selinv_plan_s* P, const double* d_valsA, double* d_
         // light (wave-granular) levels fill the occupancy; tiled levels take
         // grid_mult work-groups per CU, capped by it
         const int occ = std::max(1, P->occ[variant]);
-        const bool light = variant == kLightFactor || variant == kLightInvert;
+        const bool light = is_light(variant);
         return P->n_cu * (light ? occ : std::min(P->sched.grid_mult, occ));
     };
     hipError_t e = launch_status_reset(D.status, s);

@@ -54,14 +54,6 @@ __device__ __forceinline__ void mfma_drain()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// LDS written by some lanes of a wave, then read by others
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 __global__ void k_fill(double* __restrict__ p, int64_t n, double v)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -1412,18 +1404,22 @@ struct alignas(16) DiagLds {
 // loses l_m times row j, and column j becomes -l (1 in row j).  Row j itself
 // is scaled by 1 / d_j once, at the end: until then the recurrence is linear
 // in it.  L: the multipliers l (rows below the diagonal: L_pp); dm: d_m.
-__device__ __forceinline__ void gj16(double (&P)[4], double (&L)[4], double& dm, const int m, const int g)
+// Rows from n on hold the identity and their pivots are skipped.
+template <int NV>
+__device__ __forceinline__ void gj16(double (&P)[NV], double (&L)[NV], double& dm, const int m, const int g,
+                                     const int n = 16)
 {
-    double im = 0.0;  // 1 / d_m
-    StaticFor<0, 16>::run([&](auto jc) {
+    double im = 1.0;  // 1 / d_m
+    StaticFor<0, 4 * NV>::run([&](auto jc) {
         constexpr int j = decltype(jc)::value, gj = j & 3, vj = j >> 2;
+        if (j >= n) return;  // uniform
         const double c = row_copy<gj>(P[vj]);  // column j
         const double dj = row_lane<j>(c);
         const double inv = recip(dj);
         const double l = c * inv;
         const double lz = m == j ? 0.0 : l;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) P[v] = fma(-lz, row_lane<j>(P[v]), P[v]);
+        for (int v = 0; v < NV; ++v) P[v] = fma(-lz, row_lane<j>(P[v]), P[v]);
         if (g == gj) {
             P[vj] = m == j ? 1.0 : -l;
             L[vj] = l;
@@ -1434,7 +1430,7 @@ __device__ __forceinline__ void gj16(double (&P)[4], double (&L)[4], double& dm,
         }
     });
 #pragma unroll
-    for (int v = 0; v < 4; ++v) P[v] *= im;
+    for (int v = 0; v < NV; ++v) P[v] *= im;
 }
 
 // NW waves work on the block.  Lane (m, g) = (l % 16, l / 16) holds entry (m, g + 4 v) of a 16 x 16 block in
@@ -2043,196 +2039,304 @@ __global__ __launch_bounds__(kThreads) void k_ldlt_bk(const Task* __restrict__ t
 
 // ===========================================================================
 // Small blocks (s <= 16, c <= 256): one wave runs a whole block, every phase
-// in turn, on 16 x 16 FP64 MFMA tiles (output rows in groups of 16, the
-// contraction in steps of 4), so a block needs no other wave and no
-// work-group barrier.  Per wave, LDS holds the s x s diagonal block during
-// its sweep (then T = -M) and one 16 x 16 tile for transposition.
-//   factor:  sweep F_BB -> L_BB, D, T;  per row group I of C: L_hat(I,:) =
-//            F(I,B) T, then for every row group K <= I the Schur tile
-//            -L_hat(I,:) F(K,:)^T added into the ancestors (lower part);
+// in turn, on 16 x 16 FP64 MFMA tiles.  Lane (m, g) = (l % 16, l / 16) holds
+// entry (m, g + 4 v) of a 16 x 16 block in register v, which is the form of
+// both MFMA operands and, with the product formed transposed, of its result:
+// every phase feeds the next from registers, with no LDS and no barrier.
+//   factor:  F_BB -> L_BB, D, T (gj16); per row group I of C: L_hat(I,:) =
+//            F(I,B) T, then for every group K <= I the Schur tile
+//            -F(K,:) L_hat(I,:)^T added into the ancestors (lower part);
 //   invert:  per row group I: X(I,:) = -G(I,:) L_hat, written to Ainv(C,B),
-//            and P += L_hat(I,:)^T X(I,:) straight from the accumulators;
-//            then Ainv(B,B) = ((T - P) + (T - P)^T) / 2 on the lower triangle.
+//            with P += L_hat(I,:)^T X(I,:) and its transpose;
+//            then Ainv(B,B) = T - (P + P^T) / 2 on the lower triangle.
+// What bounds them is latency (a block is a chain of dependent loads: map,
+// rel, value) and, in levels that fill the card, the atomics.  So the loads
+// of NG x NG groups of 16 positions of C are issued together, and sixteen
+// lanes add into one run of an ancestor column.  NG = 2 (200 registers)
+// where a level's launch has a wave to itself, NG = 1 (128 and fewer, for
+// residency) in the batched levels; NV and NC cut the registers and the MFMA
+// steps to the block's s and c.  Per pass, against a version that kept the
+// diagonal block in LDS and loaded each tile's values one at a time: the
+// 17 levels of one 32^2 grid 173 -> 80 us; the light levels of a batch
+// of 256 grids of 32^2 .. 96^2 (1.2 M unknowns, 49 M atomics) 1.85 -> 1.21 ms.
 // ===========================================================================
-struct SbLds {
-    double M[16][17];
-    double L[16][17];
-};
-
-__device__ void sb_factor(const BlockDesc d, double* __restrict__ Lp, double* __restrict__ Hp,
-                          double* __restrict__ Tp, const int64_t* __restrict__ cbase,
-                          const int64_t* __restrict__ rbase, const int32_t* __restrict__ rel,
-                          unsigned long long* __restrict__ status, int require_spd, SbLds& S)
+// s <= 4 NV
+template <int NG, int NV>
+__device__ __forceinline__ void sb_factor_n(const BlockDesc d, double* __restrict__ Lp, double* __restrict__ Hp,
+                                          double* __restrict__ Tp, const int64_t* __restrict__ cr2,
+                                          const int32_t* __restrict__ rel, unsigned long long* __restrict__ status,
+                                          int require_spd)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
     double* F = Lp + d.poff;
-    // diagonal block: symmetric Gauss-Jordan sweep (as in ldlt_sweep), lane
-    // holds entries (e & 15, e >> 4) for e = lane + 64 q
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = lane + 64 * q, i = e & 15, k = e >> 4;
-        S.M[i][k] = (i < s && k < s) ? (i >= k ? F[i + k * ld] : F[k + i * ld]) : 0.0;
-    }
-    wave_sync();
-    for (int j = 0; j < s; ++j) {
-        const double dj = S.M[j][j];
-        const double inv = 1.0 / dj;
-        double nv[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = lane + 64 * q, i = e & 15, k = e >> 4;
-            const double ci = S.M[i][j], ck = S.M[k][j], m = S.M[i][k];
-            nv[q] = (i == j && k == j) ? -inv : (i == j ? ck * inv : (k == j ? ci * inv : m - ci * ck * inv));
-        }
-        const double cl = S.M[lane & 15][j];  // Schur-complement column j
-        wave_sync();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = lane + 64 * q, i = e & 15, k = e >> 4;
-            if (i < s && k < s) S.M[i][k] = nv[q];
-        }
-        if (lane < s && lane > j) F[lane + j * ld] = cl * inv;  // L_BB(i, j)
-        if (lane == j) F[j + j * ld] = dj;                      // D_j
-        if (lane == 0 && !(isfinite(dj) && dj != 0.0 && (!require_spd || dj > 0.0)))
-            atomicMin(status, (unsigned long long)(d.first + j));
-        wave_sync();
-    }
-    // T = -M (the sweep keeps M exactly symmetric)
     double* T = Tp + d.woff;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = lane + 64 * q, i = e & 15, k = e >> 4;
-        if (i < s && k < s) T[i + (int64_t)k * s] = -S.M[i][k];
-    }
-    const double* FC = F + s;  // F(C,B)(i, k) = FC[i + k ld]
     double* H = Hp + d.hoff;
-    const int m16 = lane & 15, q4 = lane >> 4;
-    for (int r0 = 0; r0 < c; r0 += 16) {
-        // L_hat(I,:) = F(I,B) T
-        d4 acc = {0, 0, 0, 0};
-        for (int k0 = 0; k0 < s; k0 += 4) {
-            const int kk = k0 + q4;
-            const double a = (r0 + m16 < c && kk < s) ? FC[(r0 + m16) + (int64_t)kk * ld] : 0.0;
-            const double b = (kk < s && m16 < s) ? -S.M[kk][m16] : 0.0;
-            acc = mfma(a, b, acc);
-        }
-        mfma_drain();
+    const int ng = (c + 15) >> 4;  // groups of C
+    // F(C,B): row 16 I + m (past C: the last), columns g + 4 v (past s: 0)
+    int64_t fcol[NV];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = r0 + q4 + 4 * v;
-            if (row < c && m16 < s) H[row + (int64_t)m16 * c] = acc[v];
-            S.L[q4 + 4 * v][m16] = acc[v];
+    for (int v = 0; v < NV; ++v) fcol[v] = s + (int64_t)min(g + 4 * v, s - 1) * ld;
+    auto load_f = [&](int I, double (&f)[NV]) {
+        const int row = min(16 * I + m, c - 1);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) f[v] = F[fcol[v] + row];
+    };
+    auto mask_f = [&](double (&f)[NV]) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) f[v] = g + 4 * v < s ? f[v] : 0.0;
+    };
+    // the (cbase, rbase) pairs of columns 16 K + g + 4 v of C
+    auto load_map = [&](int K, i64x2 (&cr)[4]) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            cr[v] = *reinterpret_cast<const i64x2*>(cr2 + 2 * (d.coff + min(16 * K + g + 4 * v, c - 1)));
+    };
+    double P[NV], L[NV] = {}, dm = 1.0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int k = g + 4 * v, a = min(max(m, k), s - 1), b = min(min(m, k), s - 1);
+        const double f = F[a + (int64_t)b * ld];
+        P[v] = m < s && k < s ? f : (m == k ? 1.0 : 0.0);
+    }
+    double f[NG][NV];
+    i64x2 cr[NG][4];
+    if (c > 0) {
+#pragma unroll
+        for (int e = 0; e < NG; ++e) {
+            load_f(min(e, ng - 1), f[e]);
+            load_map(min(e, ng - 1), cr[e]);
         }
-        wave_sync();
-        // Schur tiles (I, K), K <= I: F(C,C) -= L_hat(I,:) F(K,:)^T, lower part
-        for (int k0c = 0; k0c <= r0; k0c += 16) {
-            d4 u = {0, 0, 0, 0};
-            for (int t0 = 0; t0 < s; t0 += 4) {
-                const int kk = t0 + q4;
-                const double a = kk < s ? S.L[m16][kk] : 0.0;
-                const double b = (k0c + m16 < c && kk < s) ? FC[(k0c + m16) + (int64_t)kk * ld] : 0.0;
-                u = mfma(a, b, u);
+    }
+    gj16(P, L, dm, m, g, s);
+    if (g == 0 && m < s && !(isfinite(dm) && dm != 0.0 && (!require_spd || dm > 0.0)))
+        atomicMin(status, (unsigned long long)(d.first + m));
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int k = g + 4 * v;
+        if (m < s && k <= m) {  // L_BB, D; T made exactly symmetric from the lower triangle
+            F[m + (int64_t)k * ld] = m == k ? dm : L[v];
+            T[m + (int64_t)k * s] = P[v];
+            T[k + (int64_t)m * s] = P[v];
+        }
+    }
+    for (int K0 = 0; K0 < ng; K0 += NG) {
+        if (K0 > 0) {
+#pragma unroll
+            for (int e = 0; e < NG; ++e) {
+                load_f(min(K0 + e, ng - 1), f[e]);
+                load_map(min(K0 + e, ng - 1), cr[e]);
             }
-            mfma_drain();
+        }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int ii = r0 + q4 + 4 * v, kk = k0c + m16;
-                if (ii < c && kk < c && ii >= kk) {
-                    const int64_t pk = d.coff + kk;
-                    unsafeAtomicAdd(Lp + cbase[pk] + rel[rbase[pk] + ii], -u[v]);
+        for (int e = 0; e < NG; ++e) mask_f(f[e]);
+        // row groups from K0 on: the columns' own groups first
+        for (int I0 = K0; I0 < ng; I0 += NG) {
+            const bool own = I0 == K0;
+            double fi[NG][NV];
+            uint32_t ro[NG][NG][4];
+#pragma unroll
+            for (int e = 0; e < NG; ++e) {
+                if (!own) load_f(min(I0 + e, ng - 1), fi[e]);
+#pragma unroll
+                for (int u = 0; u < NG; ++u)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int ii = min(max(16 * (I0 + e) + m, 16 * (K0 + u) + g + 4 * v), c - 1);
+                        if (!own || u <= e) ro[e][u][v] = (uint32_t)rel[cr[u][v].y + ii];
+                    }
+            }
+#pragma unroll
+            for (int e = 0; e < NG; ++e) {
+                if (own) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) fi[e][v] = f[e][v];
+                } else {
+                    mask_f(fi[e]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < NG; ++e) {
+                const int row = 16 * (I0 + e) + m;
+                // L_hat(I,:)^T = T F(I,:)^T
+                d4 h = {0, 0, 0, 0};
+#pragma unroll
+                for (int v = 0; v < NV; ++v) h = mfma(P[v], fi[e][v], h);
+                mfma_drain();
+                if (K0 == 0) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v)
+                        if (row < c && g + 4 * v < s) H[row + (int64_t)(g + 4 * v) * c] = h[v];
+                }
+#pragma unroll
+                for (int u = 0; u < NG; ++u) {
+                    if (own && u > e) continue;
+                    d4 x = {0, 0, 0, 0};
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) x = mfma(f[u][v], h[v], x);
+                    mfma_drain();
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int kk = 16 * (K0 + u) + g + 4 * v;
+                        if (row < c && row >= kk) unsafeAtomicAdd(Lp + cr[u][v].x + ro[e][u][v], -x[v]);
+                    }
                 }
             }
         }
-        wave_sync();
     }
 }
 
-__device__ void sb_invert(const BlockDesc d, double* __restrict__ Ap, const double* __restrict__ Hp,
-                          const double* __restrict__ Tp, const int64_t* __restrict__ cbase,
-                          const int64_t* __restrict__ rbase, const int32_t* __restrict__ rel, SbLds& S)
+template <int NG>
+__device__ __forceinline__ void sb_factor(const BlockDesc& d, double* Lp, double* Hp, double* Tp, const int64_t* cr2,
+                                          const int32_t* rel, unsigned long long* status, int require_spd)
 {
-    const int lane = threadIdx.x & 63;
+    if (d.s <= 4) sb_factor_n<NG, 1>(d, Lp, Hp, Tp, cr2, rel, status, require_spd);
+    else if (d.s <= 8) sb_factor_n<NG, 2>(d, Lp, Hp, Tp, cr2, rel, status, require_spd);
+    else sb_factor_n<NG, 4>(d, Lp, Hp, Tp, cr2, rel, status, require_spd);
+}
+
+// |C| <= 4 NC, or NC = 4 and any |C|, if kMany
+template <int NG, int NC, bool kMany>
+__device__ __forceinline__ void sb_invert_n(const BlockDesc d, double* __restrict__ Ap, const double* __restrict__ Hp,
+                                          const double* __restrict__ Tp, const int64_t* __restrict__ cr2,
+                                          const int32_t* __restrict__ rel)
+{
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
     const double* H = Hp + d.hoff;
     const double* T = Tp + d.woff;
     double* A = Ap + d.poff;
-    const int m16 = lane & 15, q4 = lane >> 4;
-    d4 p = {0, 0, 0, 0};  // P = L_hat^T X
-    for (int r0 = 0; r0 < c; r0 += 16) {
-        const int i = r0 + m16;
-        d4 acc = {0, 0, 0, 0};
-        for (int k0 = 0; k0 < c; k0 += 4) {
-            const int kk = k0 + q4;
-            double g = 0.0;
-            if (i < c && kk < c) {
-                const int64_t pc = d.coff + (i >= kk ? kk : i);
-                g = Ap[cbase[pc] + rel[rbase[pc] + (i >= kk ? i : kk)]];
+    const int ng = kMany ? (c + 15) >> 4 : min(c, 1);
+    double t[4];  // T(g + 4 v, m)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) t[v] = T[min(g + 4 * v, s - 1) + (int64_t)min(m, s - 1) * s];
+    // L_hat(16 K + g + 4 v, m), 0 past C and s
+    auto load_h = [&](int K, double (&h)[NC]) {
+#pragma unroll
+        for (int v = 0; v < NC; ++v) h[v] = H[min(16 * K + g + 4 * v, c - 1) + (int64_t)min(m, s - 1) * c];
+    };
+    auto mask_h = [&](int K, double (&h)[NC]) {
+#pragma unroll
+        for (int v = 0; v < NC; ++v) h[v] = 16 * K + g + 4 * v < c && m < s ? h[v] : 0.0;
+    };
+    auto map_at = [&](int p) { return *reinterpret_cast<const i64x2*>(cr2 + 2 * (d.coff + p)); };
+    d4 p = {0, 0, 0, 0}, pt = {0, 0, 0, 0};  // P = L_hat^T X and its transpose
+    for (int I0 = 0; I0 < ng; I0 += NG) {
+        i64x2 ci[NG];  // map entries of rows 16 (I0 + e) + m
+#pragma unroll
+        for (int e = 0; e < NG; ++e) ci[e] = map_at(min(16 * (I0 + e) + m, c - 1));
+        d4 x[NG];
+#pragma unroll
+        for (int e = 0; e < NG; ++e) x[e] = d4{0, 0, 0, 0};
+        double hi[NG][NC];
+        for (int K0 = 0; K0 < ng; K0 += NG) {
+            i64x2 ck[NG][NC];  // of columns 16 (K0 + u) + g + 4 v
+            double h[NG][NC];
+#pragma unroll
+            for (int u = 0; u < NG; ++u) {
+#pragma unroll
+                for (int v = 0; v < NC; ++v) ck[u][v] = map_at(min(16 * (K0 + u) + g + 4 * v, c - 1));
+                load_h(K0 + u, h[u]);
             }
-            const double b = (kk < c && m16 < s) ? H[kk + (int64_t)m16 * c] : 0.0;
-            acc = mfma(g, b, acc);
+            // G(i, k) = Ap[cbase[p] + rel[rbase[p] + q]], p = min(i, k), q = max(i, k)
+            uint32_t r[NG][NG][NC];
+#pragma unroll
+            for (int e = 0; e < NG; ++e)
+#pragma unroll
+                for (int u = 0; u < NG; ++u)
+#pragma unroll
+                    for (int v = 0; v < NC; ++v) {
+                        const int i = min(16 * (I0 + e) + m, c - 1), k = min(16 * (K0 + u) + g + 4 * v, c - 1);
+                        r[e][u][v] = (uint32_t)rel[(i >= k ? ck[u][v].y : ci[e].y) + max(i, k)];
+                    }
+            double a[NG][NG][NC];
+#pragma unroll
+            for (int e = 0; e < NG; ++e)
+#pragma unroll
+                for (int u = 0; u < NG; ++u)
+#pragma unroll
+                    for (int v = 0; v < NC; ++v) {
+                        const int i = min(16 * (I0 + e) + m, c - 1), k = min(16 * (K0 + u) + g + 4 * v, c - 1);
+                        a[e][u][v] = Ap[(i >= k ? ck[u][v].x : ci[e].x) + r[e][u][v]];
+                    }
+#pragma unroll
+            for (int u = 0; u < NG; ++u) mask_h(K0 + u, h[u]);
+            if (I0 == K0) {
+#pragma unroll
+                for (int u = 0; u < NG; ++u)
+#pragma unroll
+                    for (int v = 0; v < NC; ++v) hi[u][v] = h[u][v];
+            }
+#pragma unroll
+            for (int u = 0; u < NG; ++u)
+#pragma unroll
+                for (int v = 0; v < NC; ++v)
+#pragma unroll
+                    for (int e = 0; e < NG; ++e)
+                        x[e] = mfma(16 * (K0 + u) + g + 4 * v < c ? a[e][u][v] : 0.0, h[u][v], x[e]);
         }
         mfma_drain();
-        // acc[v] = (G L_hat)(r0 + q4 + 4v, m16): X = -acc
+        // x[e][v] = (G L_hat)(16 (I0 + e) + g + 4 v, m): X = -x
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = r0 + q4 + 4 * v;
-            if (row < c && m16 < s) A[s + row + (int64_t)m16 * ld] = -acc[v];
-        }
-        // P += L_hat(I,:)^T X(I,:): B(kk, n) = X(r0 + 4t + kk, n) is -acc[t] of this lane
+        for (int e = 0; e < NG; ++e) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int row = r0 + 4 * t + q4;
-            const double a = (row < c && m16 < s) ? H[row + (int64_t)m16 * c] : 0.0;
-            p = mfma(a, -acc[t], p);
+            for (int v = 0; v < NC; ++v) {
+                const int row = 16 * (I0 + e) + g + 4 * v;
+                if (row < c && m < s) A[s + row + (int64_t)m * ld] = -x[e][v];
+            }
+#pragma unroll
+            for (int v = 0; v < NC; ++v) {
+                p = mfma(hi[e][v], -x[e][v], p);
+                pt = mfma(-x[e][v], hi[e][v], pt);
+            }
         }
     }
     mfma_drain();
 #pragma unroll
-    for (int v = 0; v < 4; ++v) S.M[q4 + 4 * v][m16] = p[v];
-    wave_sync();
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = lane + 64 * q, ii = e & 15, jj = e >> 4;
-        if (ii < s && jj < s && ii >= jj)
-            A[ii + (int64_t)jj * ld] = 0.5 * ((T[ii + (int64_t)jj * s] - S.M[ii][jj]) + (T[jj + (int64_t)ii * s] - S.M[jj][ii]));
+    for (int v = 0; v < 4; ++v) {
+        const int ii = g + 4 * v;
+        if (ii < s && m <= ii) A[ii + (int64_t)m * ld] = t[v] - 0.5 * (p[v] + pt[v]);
     }
-    wave_sync();
+}
+
+template <int NG>
+__device__ __forceinline__ void sb_invert(const BlockDesc& d, double* Ap, const double* Hp, const double* Tp,
+                                          const int64_t* cr2, const int32_t* rel)
+{
+    if (d.c <= 8) sb_invert_n<1, 2, false>(d, Ap, Hp, Tp, cr2, rel);
+    else if (d.c <= 16) sb_invert_n<1, 4, false>(d, Ap, Hp, Tp, cr2, rel);
+    else sb_invert_n<NG, 4, true>(d, Ap, Hp, Tp, cr2, rel);
 }
 
 // Per-level launches of the small-block path: task q holds up to four block
 // ids (b, i0, j0, bn; -1 = none), one per wave.
 __device__ __forceinline__ int sb_block_of(const Task& t)
 {
-    const int w = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     return w == 0 ? t.b : w == 1 ? t.i0 : w == 2 ? t.j0 : t.bn;
 }
 
 __global__ __launch_bounds__(kThreads) void k_sb_factor(const Task* __restrict__ tasks,
                                                         const BlockDesc* __restrict__ blk, double* __restrict__ Lp,
                                                         double* __restrict__ Hp, double* __restrict__ Tp,
-                                                        const int64_t* __restrict__ cbase,
-                                                        const int64_t* __restrict__ rbase,
+                                                        const int64_t* __restrict__ cr2,
                                                         const int32_t* __restrict__ rel,
                                                         unsigned long long* __restrict__ status, int require_spd)
 {
-    __shared__ SbLds S[kThreads / 64];
     const int b = sb_block_of(tasks[blockIdx.x]);
-    if (b >= 0) sb_factor(blk[b], Lp, Hp, Tp, cbase, rbase, rel, status, require_spd, S[threadIdx.x >> 6]);
+    if (b >= 0) sb_factor<2>(blk[b], Lp, Hp, Tp, cr2, rel, status, require_spd);
 }
 
 __global__ __launch_bounds__(kThreads) void k_sb_invert(const Task* __restrict__ tasks,
                                                         const BlockDesc* __restrict__ blk, double* __restrict__ Ap,
                                                         const double* __restrict__ Hp, const double* __restrict__ Tp,
-                                                        const int64_t* __restrict__ cbase,
-                                                        const int64_t* __restrict__ rbase,
+                                                        const int64_t* __restrict__ cr2,
                                                         const int32_t* __restrict__ rel)
 {
-    __shared__ SbLds S[kThreads / 64];
     const int b = sb_block_of(tasks[blockIdx.x]);
-    if (b >= 0) sb_invert(blk[b], Ap, Hp, Tp, cbase, rbase, rel, S[threadIdx.x >> 6]);
+    if (b >= 0) sb_invert<2>(blk[b], Ap, Hp, Tp, cr2, rel);
 }
 
 // ===========================================================================
@@ -2252,7 +2356,6 @@ union PersistLds {
     GatherLds gather;
     SdiagLds sd;
     DiagLds<NB> diag;
-    SbLds sb[kThreads / 64];
 };
 
 struct QueueArgs {
@@ -2372,8 +2475,6 @@ template <int NB>
 __global__ __launch_bounds__(kThreads, NB < 8 ? 2 : 1) void k_persist_factor(const QueueArgs a, const BlockDesc* __restrict__ blk,
                                                              double* __restrict__ Lp, double* __restrict__ Wp,
                                                              double* __restrict__ Hp, double* __restrict__ Tp,
-                                                             const int64_t* __restrict__ cbase,
-                                                             const int64_t* __restrict__ rbase,
                                                              const int32_t* __restrict__ rel,
                                                              const int64_t* __restrict__ cr2)
 {
@@ -2389,7 +2490,7 @@ __global__ __launch_bounds__(kThreads, NB < 8 ? 2 : 1) void k_persist_factor(con
         if (op == qSbFactor) {
             const int b = sb_block_of(t);
             if (b >= 0)
-                sb_factor(blk[b], Lp, Hp, Tp, cbase, rbase, rel, a.status, a.require_spd, sm.sb[threadIdx.x >> 6]);
+                sb_factor_n<1, 4>(blk[b], Lp, Hp, Tp, cr2, rel, a.status, a.require_spd);
             __syncthreads();  // the LDS union is reused by the next task
             continue;
         }
@@ -2442,8 +2543,6 @@ template <int BNMAX>
 __global__ __launch_bounds__(kThreads, 2) void k_persist_invert(const QueueArgs a, const BlockDesc* __restrict__ blk,
                                                                 double* __restrict__ Ap, const double* __restrict__ Hp,
                                                                 const double* __restrict__ Tp,
-                                                                const int64_t* __restrict__ cbase,
-                                                                const int64_t* __restrict__ rbase,
                                                                 const int32_t* __restrict__ rel,
                                                                 const int64_t* __restrict__ cr2)
 {
@@ -2456,7 +2555,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_persist_invert(const QueueArgs 
         const int op = t.flags >> 8;
         if (op == qSbInvert) {
             const int b = sb_block_of(t);
-            if (b >= 0) sb_invert(blk[b], Ap, Hp, Tp, cbase, rbase, rel, sm.sb[threadIdx.x >> 6]);
+            if (b >= 0) sb_invert_n<1, 4, true>(blk[b], Ap, Hp, Tp, cr2, rel);
             __syncthreads();
             continue;
         }
@@ -2504,42 +2603,78 @@ __global__ __launch_bounds__(kThreads, 2) void k_persist_invert(const QueueArgs 
 // Levels made only of small blocks: no dependencies, so no queue head
 // either.  Wave g of W takes slots g, g + W, g + 2W, ... (slot = 4 task +
 // wave field) of the level's cost-ordered list, so every wave gets a like
-// mix; no atomics, no work-group barrier.
-__device__ __forceinline__ int slot_block(const QueueArgs& a, int64_t slot)
-{
-    const int32_t* ids = reinterpret_cast<const int32_t*>(a.q + slot / kSbPerTask);
-    return __builtin_amdgcn_readfirstlane(ids[slot % kSbPerTask]);
-}
+// mix; no atomics, no work-group barrier.  (A run of the plan's order per
+// XCD, for the locality of the ancestors, was 8 % slower.)  The id of the
+// block after the next and the next one's descriptor are loaded while a
+// block runs, which takes two of its five dependent loads off the chain.
+struct LightQueue {
+    const int32_t* ids;
+    const BlockDesc* blk;
+    int64_t nslots, step, slot;
+    int id0, id1;  // of this turn (uniform) and of the next
+    BlockDesc next;
 
-__global__ __launch_bounds__(kThreads) void k_light_factor(const QueueArgs a, const BlockDesc* __restrict__ blk,
+    __device__ __forceinline__ LightQueue(const QueueArgs& a, const BlockDesc* b)
+        : ids(reinterpret_cast<const int32_t*>(a.q)), blk(b), nslots(a.ntasks * kSbPerTask),
+          step((int64_t)gridDim.x * (kThreads / 64))
+    {
+        slot = (int64_t)blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        id1 = at(slot);
+        advance();
+    }
+    __device__ __forceinline__ int at(int64_t x) const
+    {
+        x = min(x, nslots - 1);
+        return ids[x / kSbPerTask * (int64_t)(sizeof(Task) / sizeof(int32_t)) + x % kSbPerTask];
+    }
+    __device__ __forceinline__ void advance()
+    {
+        id0 = __builtin_amdgcn_readfirstlane(id1);
+        id1 = at(slot + step);
+        next = blk[max(id0, 0)];
+    }
+    // the block of this turn into d; false: none in this slot
+    __device__ __forceinline__ bool take(BlockDesc& d)
+    {
+        const bool some = id0 >= 0;
+        d = next;
+        slot += step;
+        advance();
+        return some;
+    }
+    __device__ __forceinline__ bool more() const { return slot < nslots; }
+};
+
+// Levels of blocks with s <= 4 NV: fewer columns take fewer registers and
+// MFMA steps, and more waves per SIMD hide each other's loads (six for
+// NV = 1).
+template <int NV>
+__global__ __launch_bounds__(kThreads, NV == 1 ? 6 : 4) void k_light_factor(const QueueArgs a, const BlockDesc* __restrict__ blk,
                                                            double* __restrict__ Lp, double* __restrict__ Hp,
-                                                           double* __restrict__ Tp, const int64_t* __restrict__ cbase,
-                                                           const int64_t* __restrict__ rbase,
+                                                           double* __restrict__ Tp, const int64_t* __restrict__ cr2,
                                                            const int32_t* __restrict__ rel)
 {
-    __shared__ SbLds S[kThreads / 64];
-    const int64_t nslots = a.ntasks * kSbPerTask;
-    const int64_t nw = (int64_t)gridDim.x * (kThreads / 64);
-    for (int64_t slot = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); slot < nslots; slot += nw) {
-        const int b = slot_block(a, slot);
-        if (b >= 0) sb_factor(blk[b], Lp, Hp, Tp, cbase, rbase, rel, a.status, a.require_spd, S[threadIdx.x >> 6]);
+    LightQueue queue(a, blk);
+    while (queue.more()) {
+        BlockDesc d;
+        if (queue.take(d)) sb_factor_n<1, NV>(d, Lp, Hp, Tp, cr2, rel, a.status, a.require_spd);
     }
 }
 
-__global__ __launch_bounds__(kThreads) void k_light_invert(const QueueArgs a, const BlockDesc* __restrict__ blk,
+// Levels of blocks with |C| <= 4 NC, or any |C| if kMany (NC = 4): one piece
+// of G needs no loops and 50 registers instead of 100, eight waves per SIMD
+// instead of four (the leaves of the batch above: 168 -> 100 us).
+template <int NC, bool kMany>
+__global__ __launch_bounds__(kThreads, kMany ? 4 : 8) void k_light_invert(const QueueArgs a, const BlockDesc* __restrict__ blk,
                                                            double* __restrict__ Ap, const double* __restrict__ Hp,
                                                            const double* __restrict__ Tp,
-                                                           const int64_t* __restrict__ cbase,
-                                                           const int64_t* __restrict__ rbase,
-                                                           const int32_t* __restrict__ rel,
-                                                                const int64_t* __restrict__ cr2)
+                                                           const int64_t* __restrict__ cr2,
+                                                           const int32_t* __restrict__ rel)
 {
-    __shared__ SbLds S[kThreads / 64];
-    const int64_t nslots = a.ntasks * kSbPerTask;
-    const int64_t nw = (int64_t)gridDim.x * (kThreads / 64);
-    for (int64_t slot = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); slot < nslots; slot += nw) {
-        const int b = slot_block(a, slot);
-        if (b >= 0) sb_invert(blk[b], Ap, Hp, Tp, cbase, rbase, rel, S[threadIdx.x >> 6]);
+    LightQueue queue(a, blk);
+    while (queue.more()) {
+        BlockDesc d;
+        if (queue.take(d)) sb_invert_n<1, NC, kMany>(d, Ap, Hp, Tp, cr2, rel);
     }
 }
 
@@ -2978,8 +3113,8 @@ hipError_t launch_export_L(Prof* P, const DevPtrs& D, int64_t n, double* out, hi
 hipError_t launch_sb_factor(Prof* P, const DevPtrs& D, int64_t sb0, int64_t nsb, int require_spd, hipStream_t s)
 {
     if (nsb > 0)
-        launch(P, kSbFactor, k_sb_factor, dim3((unsigned)nsb), 0, s, D.t_sb + sb0, D.blocks, D.Lp, D.Hp, D.Tp, D.cbase,
-               D.rbase, D.rel, D.status, require_spd);
+        launch(P, kSbFactor, k_sb_factor, dim3((unsigned)nsb), 0, s, D.t_sb + sb0, D.blocks, D.Lp, D.Hp, D.Tp, D.cr2,
+               D.rel, D.status, require_spd);
     return hipGetLastError();
 }
 
@@ -2987,7 +3122,7 @@ hipError_t launch_sb_invert(Prof* P, const DevPtrs& D, int64_t sb0, int64_t nsb,
 {
     if (nsb > 0)
         launch(P, kSbInvert, k_sb_invert, dim3((unsigned)nsb), 0, s, D.t_sb + sb0, D.blocks, D.Ap, (const double*)D.Hp,
-               (const double*)D.Tp, D.cbase, D.rbase, D.rel);
+               (const double*)D.Tp, D.cr2, D.rel);
     return hipGetLastError();
 }
 
@@ -3065,9 +3200,9 @@ hipError_t launch_invert_level(Prof* P, const DevPtrs& D, int64_t gemm0, int64_t
 // selinv::PersistVariant
 hipError_t persist_occupancy(int occ[kNumVariants])
 {
-    const void* k[kNumVariants] = {(const void*)k_light_factor,       (const void*)k_persist_factor<2>,
+    const void* k[kNumVariants] = {(const void*)k_light_factor<1>, (const void*)k_light_factor<2>, (const void*)k_light_factor<4>,       (const void*)k_persist_factor<2>,
                                    (const void*)k_persist_factor<4>,  (const void*)k_persist_factor<8>,
-                                   (const void*)k_light_invert,       (const void*)k_persist_invert<32>,
+                                   (const void*)k_light_invert<2, false>, (const void*)k_light_invert<4, false>, (const void*)k_light_invert<4, true>,       (const void*)k_persist_invert<32>,
                                    (const void*)k_persist_invert<64>, (const void*)k_persist_invert<128>};
     hipError_t e = hipSuccess;
     for (int v = 0; v < kNumVariants && !e; v++) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(occ + v, k[v], kThreads, 0);
@@ -3088,15 +3223,17 @@ hipError_t launch_persist_factor(Prof* P, const DevPtrs& D, const Task* q, int64
     if (ntasks <= 0) return hipSuccess;
     const QueueArgs a{q, ntasks, head, done, D.status, require_spd, spin_limit};
     const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(grid, ntasks));
-#define SELINV_PF(K) launch(P, kQFactor, K, dim3(g), 0, s, a, D.blocks, D.Lp, D.Wp, D.Hp, D.Tp, D.cbase, D.rbase, D.rel, D.cr2)
+#define SELINV_PF(K) launch(P, kQFactor, K, dim3(g), 0, s, a, D.blocks, D.Lp, D.Wp, D.Hp, D.Tp, D.rel, D.cr2)
+#define SELINV_LF(K) launch(P, kQFactor, K, dim3(g), 0, s, a, D.blocks, D.Lp, D.Hp, D.Tp, D.cr2, D.rel)
     switch (variant) {
-        case kLightFactor:
-            launch(P, kQFactor, k_light_factor, dim3(g), 0, s, a, D.blocks, D.Lp, D.Hp, D.Tp, D.cbase, D.rbase, D.rel);
-            break;
+        case kLightFactor4: SELINV_LF(k_light_factor<1>); break;
+        case kLightFactor8: SELINV_LF(k_light_factor<2>); break;
+        case kLightFactor16: SELINV_LF(k_light_factor<4>); break;
         case kFactor32: SELINV_PF(k_persist_factor<2>); break;
         case kFactor64: SELINV_PF(k_persist_factor<4>); break;
         default: SELINV_PF(k_persist_factor<8>); break;
     }
+#undef SELINV_LF
 #undef SELINV_PF
     return hipGetLastError();
 }
@@ -3107,15 +3244,19 @@ hipError_t launch_persist_invert(Prof* P, const DevPtrs& D, const Task* q, int64
     if (ntasks <= 0) return hipSuccess;
     const QueueArgs a{q, ntasks, head, done, D.status, 0, spin_limit};
     const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(grid, ntasks));
-#define SELINV_PI(K)                                                                                              \
-    launch(P, kQInvert, K, dim3(g), 0, s, a, D.blocks, D.Ap, (const double*)D.Hp, (const double*)D.Tp, D.cbase, \
-           D.rbase, D.rel, D.cr2)
+#define SELINV_PI(K) \
+    launch(P, kQInvert, K, dim3(g), 0, s, a, D.blocks, D.Ap, (const double*)D.Hp, (const double*)D.Tp, D.rel, D.cr2)
+#define SELINV_LI(K) \
+    launch(P, kQInvert, K, dim3(g), 0, s, a, D.blocks, D.Ap, (const double*)D.Hp, (const double*)D.Tp, D.cr2, D.rel)
     switch (variant) {
-        case kLightInvert: SELINV_PI(k_light_invert); break;
+        case kLightInvert8: SELINV_LI((k_light_invert<2, false>)); break;
+        case kLightInvert16: SELINV_LI((k_light_invert<4, false>)); break;
+        case kLightInvert256: SELINV_LI((k_light_invert<4, true>)); break;
         case kInvert32: SELINV_PI(k_persist_invert<32>); break;
         case kInvert64: SELINV_PI(k_persist_invert<64>); break;
         default: SELINV_PI(k_persist_invert<128>); break;
     }
+#undef SELINV_LI
 #undef SELINV_PI
     return hipGetLastError();
 }

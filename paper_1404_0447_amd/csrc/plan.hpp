@@ -76,12 +76,14 @@ struct Sched {
 enum QOrder { qoPlan = 0, qoLpt = 1, qoRoundRobin = 2, qoTileLpt = 3, qoNumOrders };
 
 // Persistent kernel variants, chosen per level: only small blocks (light,
-// wave-granular), else bounded by the widest diagonal block (factor) or
-// output tile (inversion) of the level.
+// wave-granular; bounded by the largest s of the level, factor, or the
+// largest |C|, inversion), else bounded by the widest diagonal block
+// (factor) or output tile (inversion) of the level.
 enum PersistVariant {
-    kLightFactor = 0, kFactor32, kFactor64, kFactor128,
-    kLightInvert, kInvert32, kInvert64, kInvert128, kNumVariants
+    kLightFactor4 = 0, kLightFactor8, kLightFactor16, kFactor32, kFactor64, kFactor128,
+    kLightInvert8, kLightInvert16, kLightInvert256, kInvert32, kInvert64, kInvert128, kNumVariants
 };
+inline bool is_light(int v) { return v <= kLightFactor16 || (v >= kLightInvert8 && v <= kLightInvert256); }
 
 // Kernel kinds (same numbering as SELINV_K_* in selinv.h).
 enum Kind {
@@ -197,7 +199,7 @@ struct selinv_plan_s {
     void* graph_out = nullptr;
     hipStream_t cap_stream = nullptr;
     int n_cu = 0;                           // device of the bound workspace
-    int occ[selinv::kNumVariants] = {1, 1, 1, 1, 1, 1, 1, 1};  // resident work-groups per CU, per variant
+    int occ[selinv::kNumVariants] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1};  // resident work-groups per CU, per variant
     std::vector<uint8_t> q_var_fac, q_var_inv;                  // per level: the PersistVariant to launch
     std::string dev_arch;
     unsigned spin_limit = 1u << 22;         // polls of a dependency wait before it is abandoned

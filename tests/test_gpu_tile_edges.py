@@ -83,3 +83,31 @@ def test_dense_forward(n, cap, run):
     d = np.diag(ld).copy()
     np.fill_diagonal(ld, 1.0)
     assert np.abs(ld @ np.diag(d) @ ld.T - ap).max() <= 1e-12
+
+
+@pytest.mark.parametrize("run", ["levels", "persistent"])
+@pytest.mark.parametrize("n,cap", [(9, 2), (14, 3), (21, 4), (30, 5), (34, 7), (49, 8), (50, 9), (61, 12), (47, 15),
+                                   (64, 16), (65, 16), (272, 16), (271, 13)])
+def test_small_blocks(n, cap, run):
+    """Blocks of at most 16 columns, each whole on one wave; the rows below
+    them run through every count from 0 to n - cap that the chain has."""
+    import torch
+    a, m = _dense(n, n)
+    p = _plan(m, max_super=cap, exec_cap=cap)
+    v = torch.as_tensor(m.vals, device="cuda")
+    if run == "levels":
+        p.factor(v)
+        sel = p.invert()
+    else:
+        p.set_schedule(small_s=16)
+        sel = p.run(v)
+    p.sync_status()
+    cp, ri, perm = p.pattern()
+    cols = np.repeat(np.arange(n), np.diff(cp))
+    ap = a[np.ix_(perm, perm)]
+    assert np.abs(sel.cpu().numpy() - np.linalg.inv(ap)[ri, cols]).max() <= 1e-12
+    ld = np.zeros((n, n))
+    ld[ri, cols] = p.factor_values().cpu().numpy()
+    d = np.diag(ld).copy()
+    np.fill_diagonal(ld, 1.0)
+    assert np.abs(ld @ np.diag(d) @ ld.T - ap).max() <= 1e-12
