@@ -111,3 +111,21 @@ def test_small_blocks(n, cap, run):
     d = np.diag(ld).copy()
     np.fill_diagonal(ld, 1.0)
     assert np.abs(ld @ np.diag(d) @ ld.T - ap).max() <= 1e-12
+
+
+@pytest.mark.parametrize("n,cap", [(1, 64), (2, 64), (15, 64), (16, 64), (17, 64), (31, 64), (33, 64), (63, 64), (64, 64),
+                                   (65, 64), (90, 17), (129, 32), (250, 49), (333, 64), (777, 64)])
+def test_dense_complex(n, cap):
+    """Selected inverse of complex symmetric chains: diagonal 1 + i / 2."""
+    import torch
+    a, m = _dense(n, n)
+    b, mb = _dense(n, n + 1)
+    z = a + 0.5j * b
+    p = _plan(m, max_super=cap, exec_cap=cap, complex_values=True)
+    p.factor_complex(torch.as_tensor(m.vals + 0.5j * mb.vals, device="cuda"))
+    sel = p.invert_complex()
+    p.sync_status()
+    cp, ri, perm = p.pattern()
+    cols = np.repeat(np.arange(n), np.diff(cp))
+    x = np.linalg.inv(z[np.ix_(perm, perm)])
+    assert np.abs(sel.cpu().numpy() - x[ri, cols]).max() <= 1e-12
