@@ -476,6 +476,70 @@ __global__ __launch_bounds__(kThreads) void k_zdiag(const Task* __restrict__ tas
     }
 }
 
+// One 16 x 16 tile per wave, 4 NS entries of contraction from 0: a wave has
+// every operand load in flight at once, straight into MFMA form, and needs no
+// LDS and no barrier.  Rows ra.. of a and rb.. of b (entry k of row r at
+// p[r + k ld], 0 past the contraction); element (g + 4 v, m) in register v.
+// `under` runs between the loads and the products.  For launches of few
+// tiles, where a tile's time is its latency: a 64-wide tile spends 7 us on
+// the matrix unit of one CU (s = 64), a quarter of it on a CU of its own 1.8.
+// The products are those of zdense, in its order.
+template <int NS, class AF>
+__device__ __forceinline__ void zwave_n(const ZOperand& a, int ra, const ZOperand& b, int rb, zd4& re, zd4& im,
+                                        AF& under)
+{
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    z2 x[NS], y[NS];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+        x[t] = zbuffer(a, (uint32_t)(ra + m) * 16u + (uint32_t)(4 * t + g) * a.ld16, 0);
+        y[t] = zbuffer(b, (uint32_t)(rb + m) * 16u + (uint32_t)(4 * t + g) * b.ld16, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    under();
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+        re = zmfma(x[t].x, y[t].x, re);
+        im = zmfma(x[t].x, y[t].y, im);
+        re = zmfma(-x[t].y, y[t].y, re);
+        im = zmfma(x[t].y, y[t].x, im);
+    }
+    zdrain();
+}
+template <class AF>
+__device__ __forceinline__ void zwave(const ZOperand& a, int ra, const ZOperand& b, int rb, int s, zd4& re, zd4& im,
+                                      AF under)
+{
+    if (s <= 16) zwave_n<4>(a, ra, b, rb, re, im, under);
+    else if (s <= 32) zwave_n<8>(a, ra, b, rb, re, im, under);
+    else zwave_n<kZMaxS / 4>(a, ra, b, rb, re, im, under);
+}
+
+// L_hat(C,K) rows [r0, r0+64) = F(C,K) T_K: four work-groups per task, a
+// wave per 16 x 16 tile
+__global__ __launch_bounds__(kThreads, 2) void k_zpanel_few(const Task* __restrict__ tasks,
+                                                            const BlockDesc* __restrict__ blk,
+                                                            const double* __restrict__ Lp, double* __restrict__ Hp,
+                                                            const double* __restrict__ Tp)
+{
+    const Task tk = tasks[blockIdx.x >> 2];
+    const BlockDesc d = blk[tk.b];
+    const int s = d.s, c = d.c, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int i0 = tk.i0 + 16 * wave, j0 = 16 * (blockIdx.x & 3);
+    if (i0 >= c || j0 >= s) return;
+    const int64_t ld = (int64_t)s + c;
+    zd4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    zwave(zoperand(Tp, d.woff, (int64_t)s * s, s), j0, zoperand(Lp, d.poff + s, (int64_t)(s - 1) * ld + c, ld), i0, s,
+          re, im, ZNoHook());
+    const int i = i0 + (lane & 15);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int j = j0 + (lane >> 4) + 4 * v;
+        if (i < c && j < s) zstore(Hp, d.hoff + i + (int64_t)j * c, z2{re[v], im[v]});
+    }
+}
+
 // L_hat(C,K) rows [r0, r0+64) = F(C,K) T_K
 __global__ __launch_bounds__(kThreads) void k_zpanel(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                      const double* __restrict__ Lp, double* __restrict__ Hp,
@@ -502,12 +566,11 @@ __global__ __launch_bounds__(kThreads) void k_zpanel(const Task* __restrict__ ta
 // ancestor panels; the tasks of one launch touch disjoint entries.  The tile
 // is formed as F(k0.., :) L_hat(i0.., :)^T, so that sixteen lanes hold
 // sixteen consecutive rows of one target column, a contiguous run of its
-// panel instead of sixteen
-// columns: 11.1 -> 10.0 ms of the 32-pole batch; its read-modify-write of the
-// targets alone is about half of that.  The scatter targets do not depend on the product:
-// their (cbase, rbase) pairs are loaded before the products and the rel
-// entries under them, and the epilogue reads every target before it writes
-// the first.
+// panel instead of sixteen columns: 11.1 -> 10.0 ms of the 32-pole batch; its
+// read-modify-write of the targets alone is about half of that.  The scatter
+// targets do not depend on the product: their (cbase, rbase) pairs are loaded
+// before the products and the rel entries under them, and the epilogue reads
+// every target before it writes the first.
 __global__ __launch_bounds__(kThreads, 2) void k_zschur(const Task* __restrict__ tasks, const BlockDesc* __restrict__ blk,
                                                         double* __restrict__ Lp, const double* __restrict__ Hp,
                                                         const int64_t* __restrict__ cr2, const int32_t* __restrict__ rel)
@@ -560,6 +623,44 @@ __global__ __launch_bounds__(kThreads, 2) void k_zschur(const Task* __restrict__
             for (int v = 0; v < 4; ++v)
                 if (full || (row_of(n) < c && row_of(n) >= col_of(m, v)))
                     zstore(Lp, cr[m][v].x + ro[m][n][v], old[m][n][v] - z2{acc.re[m][n][v], acc.im[m][n][v]});
+}
+
+// The same update, four work-groups per task (a 32 x 32 quarter each), a wave
+// per 16 x 16 tile, with every target read before the products end.
+__global__ __launch_bounds__(kThreads, 2) void k_zschur_few(const Task* __restrict__ tasks,
+                                                            const BlockDesc* __restrict__ blk, double* __restrict__ Lp,
+                                                            const double* __restrict__ Hp,
+                                                            const int64_t* __restrict__ cr2,
+                                                            const int32_t* __restrict__ rel)
+{
+    typedef int64_t i64v2 __attribute__((ext_vector_type(2)));
+    const Task tk = tasks[blockIdx.x >> 2];
+    const BlockDesc d = blk[tk.b];
+    const int s = d.s, c = d.c, q = blockIdx.x & 3, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int i0 = tk.i0 + 32 * (q >> 1) + 16 * (wave >> 1), k0 = tk.j0 + 32 * (q & 1) + 16 * (wave & 1);
+    if (i0 >= c || k0 >= c || i0 + 15 < k0) return;
+    const int64_t ld = (int64_t)s + c;
+    const int row = i0 + (lane & 15);
+    auto col_of = [&](int v) { return k0 + (lane >> 4) + 4 * v; };
+    i64v2 cr[4];
+    uint32_t ro[4];
+    z2 old[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) cr[v] = *reinterpret_cast<const i64v2*>(cr2 + 2 * (d.coff + min(col_of(v), c - 1)));
+    __builtin_amdgcn_sched_barrier(0);
+    auto targets = [&]() {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ro[v] = (uint32_t)rel[cr[v].y + min(max(row, col_of(v)), c - 1)];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) old[v] = zload(Lp, cr[v].x + ro[v]);
+    };
+    zd4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    zwave(zoperand(Lp, d.poff + s, (int64_t)(s - 1) * ld + c, ld), k0, zoperand(Hp, d.hoff, (int64_t)s * c, c), i0, s,
+          re, im, targets);
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        if (row < c && row >= col_of(v)) zstore(Lp, cr[v].x + ro[v], old[v] - z2{re[v], im[v]});
 }
 
 // Ainv(C,K) rows [r0, r0+64) = -G L_hat with G = Ainv(C,C) gathered from the
@@ -933,18 +1034,31 @@ hipError_t launch_zexport(const double* Ap, const int64_t* off, int64_t n, doubl
     return hipGetLastError();
 }
 
+// Launches of at most this many tiles take the wave-per-16 x 16 kernels (s =
+// 64, old > new us): panel 27 tiles 12 > 6, 104 13 > 9, 160 equal, 256
+// 16 < 19; Schur 15 tiles 13 > 5, 91 14 > 9, 192 15 > 12, 320 25 > 20, 480
+// 29 < 32 (they load each operand four times as often).  One pole of
+// n = 8,000, factor + inversion: 4.36 -> 3.49 ms.
+constexpr int64_t kZFewPanel = 160, kZFewSchur = 384;
+
 hipError_t launch_zfactor_level(const DevPtrs& D, int64_t diag0, int64_t ndiag, int64_t panel0, int64_t npanel,
                                 const int64_t* schur_cuts, int ncuts, hipStream_t s)
 {
     if (ndiag > 0)
         hipLaunchKernelGGL(k_zdiag, dim3((unsigned)ndiag), dim3(kThreads), 0, s, D.t_ldlt + diag0, D.blocks, D.Lp,
                            D.Tp, D.status);
-    if (npanel > 0)
+    if (npanel > 0 && npanel <= kZFewPanel)
+        hipLaunchKernelGGL(k_zpanel_few, dim3((unsigned)(4 * npanel)), dim3(kThreads), 0, s, D.t_panel + panel0,
+                           D.blocks, (const double*)D.Lp, D.Hp, (const double*)D.Tp);
+    else if (npanel > 0)
         hipLaunchKernelGGL(k_zpanel, dim3((unsigned)npanel), dim3(kThreads), 0, s, D.t_panel + panel0, D.blocks,
                            (const double*)D.Lp, D.Hp, (const double*)D.Tp);
     for (int g = 0; g + 1 < ncuts; g++) {
         const int64_t n = schur_cuts[g + 1] - schur_cuts[g];
-        if (n > 0)
+        if (n > 0 && n <= kZFewSchur)
+            hipLaunchKernelGGL(k_zschur_few, dim3((unsigned)(4 * n)), dim3(kThreads), 0, s, D.t_schur + schur_cuts[g],
+                               D.blocks, D.Lp, (const double*)D.Hp, D.cr2, D.rel);
+        else if (n > 0)
             hipLaunchKernelGGL(k_zschur, dim3((unsigned)n), dim3(kThreads), 0, s, D.t_schur + schur_cuts[g], D.blocks,
                                D.Lp, (const double*)D.Hp, D.cr2, D.rel);
     }
