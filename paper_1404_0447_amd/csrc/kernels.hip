@@ -160,7 +160,7 @@ __global__ void k_export_L(const BlockDesc* __restrict__ blk, const int32_t* __r
 // 64 x BN MFMA tiles, four waves: BN >= 64 -> 2 x 2 waves of 32 x BN/2, else
 // 4 x 1 waves of 16 x BN; contractions in chunks of 16.
 // ---------------------------------------------------------------------------
-constexpr int TBM = 64, TBK = 16, TPAD = 4;
+constexpr int TBM = 64, TBK = 16;
 
 template <int BN>
 struct TileShape {
@@ -189,93 +189,6 @@ __device__ __forceinline__ void tile_epilogue_t(const d4 (&acc)[2][4], F f)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 f(wm0 + mt * 16 + (lane & 15), wn0 + nt * 16 + (lane >> 4) + 4 * v, acc[mt][nt][v]);
-}
-
-struct GemmLds {
-    double A[2][TBK][TBM + TPAD];
-    double B[2][TBK][128 + TPAD];
-};
-
-// ---------------------------------------------------------------------------
-// acc += A(64 x K) B(K x BN) for a contraction of at most NCH chunks of 16
-// (NCH <= 8: at most 128), for levels with few tiles, where a tile's time is
-// its latency: every chunk's loads are issued before the first product, so
-// the global-memory latency is paid once instead of once per chunk.  The
-// loads of all NCH chunks are unconditional (past the contraction the
-// address callbacks addrA(k0, kk, ii, ok) / addrB(k0, kk, j, ok) return an
-// in-bounds stand-in and a false mask), which
-// keeps them in one straight run: with a branch per chunk the wait before
-// the first product would have to cover every path, i.e. all loads.  A read
-// along i, B along j (kBJ: B(k, j) contiguous in j) or along k, operands
-// swapped when kT; masks kept as
-// bits.  BN <= 64 (at most 8 values per thread a chunk).
-// ---------------------------------------------------------------------------
-template <int BN, int NCH, bool kBJ, bool kT, class FA, class FB, class FH>
-__device__ __forceinline__ void tile_mma_deep(GemmLds& L, int Kb, int Ke, d4 (&acc)[2][4], FA addrA, FB addrB,
-                                              FH afterPrologue)
-{
-    static_assert(BN <= 64 && NCH * TBK <= kDeepK, "at most 8 chunks of 8 values in registers");
-    using SH = TileShape<BN>;
-    constexpr int NB = BN / 16;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm0 = (wave % SH::WM) * (TBM / SH::WM), wn0 = (wave / SH::WM) * (BN / SH::WN);
-    const int nch = Ke > Kb ? (Ke - Kb + TBK - 1) / TBK : 0;
-    double va[NCH][4], vb[NCH][NB];
-    uint32_t oka = 0, okb = 0;  // bit 4 ch + q (A), NB ch + q (B)
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-        const int k0 = Kb + ch * TBK;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + q * kThreads;
-            bool ok;
-            va[ch][q] = *addrA(k0, e >> 6, e & 63, ok);
-            oka |= (uint32_t)ok << (4 * ch + q);
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int e = tid + q * kThreads;
-            const int kk = kBJ ? e / BN : (e & 15), j = kBJ ? e % BN : (e >> 4);
-            bool ok;
-            vb[ch][q] = *addrB(k0, kk, j, ok);
-            okb |= (uint32_t)ok << (NB * ch + q);
-        }
-    }
-    afterPrologue();
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-        if (ch >= nch) break;
-        const int buf = ch & 1;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + q * kThreads;
-            L.A[buf][e >> 6][e & 63] = (oka >> (4 * ch + q)) & 1 ? va[ch][q] : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int e = tid + q * kThreads;
-            const int kk = kBJ ? e / BN : (e & 15), j = kBJ ? e % BN : (e >> 4);
-            L.B[buf][kk][j] = (okb >> (NB * ch + q)) & 1 ? vb[ch][q] : 0.0;
-        }
-        // chunk ch - 1 was read from the other buffer before every wave
-        // passed the previous barrier; this buffer was last read two chunks ago
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < TBK / 4; ++ks) {
-            const int kr = ks * 4 + (lane >> 4);
-            double a[SH::MT], b[SH::NT];
-#pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt) a[mt] = L.A[buf][kr][wm0 + mt * 16 + (lane & 15)];
-#pragma unroll
-            for (int nt = 0; nt < SH::NT; ++nt) b[nt] = L.B[buf][kr][wn0 + nt * 16 + (lane & 15)];
-#pragma unroll
-            for (int mt = 0; mt < SH::MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < SH::NT; ++nt)
-                    acc[mt][nt] = kT ? mfma(b[nt], a[mt], acc[mt][nt]) : mfma(a[mt], b[nt], acc[mt][nt]);
-        }
-    }
-    mfma_drain();
 }
 
 #define SELINV_BN_DISPATCH(bn, CALL) \
@@ -836,11 +749,6 @@ __device__ __forceinline__ void dense_mma(LDS& L, const Operand& opA, const Oper
 // Factor panel (Algorithm 1 step 2, fused into the factorization):
 // L_hat(C,B) = F(C,B) T for rows [i0, i0+64), columns [j0, j0+BN).
 // ---------------------------------------------------------------------------
-union DeepLds {
-    GemmLds g;
-    GatherLds d;
-};
-
 // L_hat(i, j) = sum over k of F(i, k) T(j, k): T is symmetric, so both
 // operands lie along their rows
 template <int BN, class LDS>
@@ -853,36 +761,14 @@ __device__ __forceinline__ void panel_product(LDS& L, const Task& t, const Block
                                       operand(T + t.j0, (int64_t)s * s - t.j0, s), 0, s, acc, [] {});
 }
 
-template <int BN, bool kDeep = false, class LDS>
+template <int BN, class LDS>
 __device__ __forceinline__ void panel_task(LDS& L, const Task t, const BlockDesc d, const double* __restrict__ Lp,
                            double* __restrict__ Hp, const double* __restrict__ Tp)
 {
     const int s = d.s, c = d.c;
-    const int64_t ld = (int64_t)s + c;
     const int r0 = t.i0, n0 = t.j0;
     d4 acc[2][4] = {};
-    const double* F = Lp + d.poff + s;
-    const double* T = Tp + d.woff;
-    if constexpr (kDeep) {
-        auto addrA = [&](int k0, int kk, int ii, bool& ok) -> const double* {
-            const int i = r0 + ii, k = k0 + kk;
-            ok = i < c && k < s;
-            return ok ? F + i + (int64_t)k * ld : F;
-        };
-        auto addrB = [&](int k0, int kk, int j, bool& ok) -> const double* {
-            const int k = k0 + kk, jj = n0 + j;
-            ok = k < s && jj < s;
-            return ok ? T + k + (int64_t)jj * s : T;
-        };
-        // chunks of 16 the contraction s needs: 1, 2, 4 or 8 (s <= 128)
-        if (s <= 16) tile_mma_deep<BN, 1, false, true>(L.g, 0, s, acc, addrA, addrB, [] {});
-        else if (s <= 32) tile_mma_deep<BN, 2, false, true>(L.g, 0, s, acc, addrA, addrB, [] {});
-        else if (s <= 64) tile_mma_deep<BN, 4, false, true>(L.g, 0, s, acc, addrA, addrB, [] {});
-        else if (s <= kDeepK) tile_mma_deep<BN, 8, false, true>(L.g, 0, s, acc, addrA, addrB, [] {});
-        else panel_product<BN>(L.d, t, d, F, T, acc);
-    } else {
-        panel_product<BN>(L, t, d, F, T, acc);
-    }
+    panel_product<BN>(L, t, d, Lp + d.poff + s, Tp + d.woff, acc);
     tile_epilogue_t<BN>(acc, [&](int i, int j, double v) {
         const int ii = r0 + i, jj = n0 + j;
         if (ii < c && jj < s) Hp[d.hoff + ii + (int64_t)jj * c] = v;
@@ -901,20 +787,64 @@ __global__ __launch_bounds__(kThreads) void k_panel(const Task* __restrict__ tas
 #undef SELINV_CALL
 }
 
-// levels with few panel tiles (width <= 64 each): the contraction (s <= 128)
-// loaded up front
-__global__ __launch_bounds__(kThreads) void k_panel_deep(const Task* __restrict__ tasks,
-                                                         const BlockDesc* __restrict__ blk,
-                                                         const double* __restrict__ Lp, double* __restrict__ Hp,
-                                                         const double* __restrict__ Tp)
+// ---------------------------------------------------------------------------
+// Levels of few tiles, where a tile's time is its latency: one 16 x 16 tile
+// per wave, with every operand load of the contraction (s <= kDeepK) in
+// flight at once, straight into MFMA form; no LDS and no barrier.  Rows ra..
+// of a and rb.. of b (entry k of row r at p[r + k ld], 0 past the
+// contraction); element (g + 4 v, m) in register v.  `under` runs between
+// the loads and the products.  With a 64 x 64 tile per work-group, its chunks
+// through LDS (4 us on the matrix unit of one CU at s = 128, and eight
+// barriers), the panel and Schur launches of a 301 x 257 grid took 8.2 and
+// 9.3 us on average, now 5.4 and 6.0; of a 40^3 grid 12.2 and 11.2, now 8.0
+// and 8.9.
+// ---------------------------------------------------------------------------
+template <int NS, class AF>
+__device__ __forceinline__ d4 wave_mma_n(const Operand& a, int ra, const Operand& b, int rb, AF& under)
 {
-    __shared__ DeepLds L;
-    const Task t = tasks[blockIdx.x];
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    double x[NS], y[NS];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+        x[t] = buffer_f64(a.rsrc, (uint32_t)(ra + m) * 8u + (uint32_t)(4 * t + g) * a.ld8, 0);
+        y[t] = buffer_f64(b.rsrc, (uint32_t)(rb + m) * 8u + (uint32_t)(4 * t + g) * b.ld8, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    under();
+    d4 acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int t = 0; t < NS; ++t) acc = mfma(x[t], y[t], acc);
+    mfma_drain();
+    return acc;
+}
+template <class AF>
+__device__ __forceinline__ d4 wave_mma(const Operand& a, int ra, const Operand& b, int rb, int s, AF under)
+{
+    if (s <= 16) return wave_mma_n<4>(a, ra, b, rb, under);
+    if (s <= 32) return wave_mma_n<8>(a, ra, b, rb, under);
+    if (s <= 64) return wave_mma_n<16>(a, ra, b, rb, under);
+    return wave_mma_n<kDeepK / 4>(a, ra, b, rb, under);
+}
+
+// four work-groups per task, each 16 columns; a wave 16 rows
+__global__ __launch_bounds__(kThreads, 2) void k_panel_few(const Task* __restrict__ tasks,
+                                                           const BlockDesc* __restrict__ blk,
+                                                           const double* __restrict__ Lp, double* __restrict__ Hp,
+                                                           const double* __restrict__ Tp)
+{
+    const Task t = tasks[blockIdx.x >> 2];
     const BlockDesc d = blk[t.b];
-    switch (t.bn) {
-        case 16: panel_task<16, true>(L, t, d, Lp, Hp, Tp); break;
-        case 32: panel_task<32, true>(L, t, d, Lp, Hp, Tp); break;
-        default: panel_task<64, true>(L, t, d, Lp, Hp, Tp); break;
+    const int s = d.s, c = d.c, lane = threadIdx.x & 63, jq = 16 * (blockIdx.x & 3);
+    const int i0 = t.i0 + 16 * __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), j0 = t.j0 + jq;
+    if (i0 >= c || j0 >= s || jq >= t.bn) return;
+    const int64_t ld = (int64_t)s + c;
+    const d4 acc = wave_mma(operand(Tp + d.woff, (int64_t)s * s, s), j0,
+                            operand(Lp + d.poff + s, (int64_t)(s - 1) * ld + c, ld), i0, s, [] {});
+    const int i = i0 + (lane & 15);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int j = j0 + (lane >> 4) + 4 * v;
+        if (i < c && j < s) Hp[d.hoff + i + (int64_t)j * c] = acc[v];
     }
 }
 
@@ -1049,46 +979,21 @@ __device__ __forceinline__ void scatter_update(const Task& t, const BlockDesc& d
     }
 }
 
-template <bool kDeep = false, class LDS>
+template <class LDS>
 __device__ __forceinline__ void schur_task(LDS& L, const Task t, const BlockDesc d, double* __restrict__ Lp,
                                            const double* __restrict__ Hp, const int64_t* __restrict__ cr2,
                                            const int32_t* __restrict__ rel)
 {
     const int s = d.s, c = d.c;
     const int64_t ld = (int64_t)s + c;
-    const int i0 = t.i0, k0c = t.j0;
-    const double* H = Hp + d.hoff;
-    const double* F = Lp + d.poff + s;
-    auto product = [&](d4(&acc)[2][4], auto prefetch) {
-        if constexpr (kDeep) {
-            // A(kk, t) = F(k0 + kk, t): contiguous along the tile rows
-            auto addrA = [&](int t0, int tt, int kk, bool& ok) -> const double* {
-                const int k = k0c + kk, col = t0 + tt;
-                ok = k < c && col < s;
-                return ok ? F + k + (int64_t)col * ld : F;
-            };
-            // B(t, ii) = L_hat(i0 + ii, t): contiguous in ii
-            auto addrB = [&](int t0, int tt, int ii, bool& ok) -> const double* {
-                const int i = i0 + ii, k = t0 + tt;
-                ok = i < c && k < s;
-                return ok ? H + i + (int64_t)k * c : H;
-            };
-            if (s <= 16) tile_mma_deep<64, 1, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
-            else if (s <= 32) tile_mma_deep<64, 2, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
-            else if (s <= 64) tile_mma_deep<64, 4, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
-            else if (s <= kDeepK) tile_mma_deep<64, 8, true, false>(L.g, 0, s, acc, addrA, addrB, prefetch);
-        }
-        auto dense = [&](auto& W) {
-            dense_mma<64, false, false, false>(W, operand(F + k0c, (int64_t)(s - 1) * ld + c - k0c, ld),
-                                               operand(H + i0, (int64_t)s * c - i0, c), 0, s, acc, prefetch);
-        };
-        if constexpr (kDeep) {
-            if (s > kDeepK) dense(L.d);
-        } else {
-            dense(L);
-        }
-    };
-    scatter_update(t, d, Lp, cr2, rel, product, [](int, int, double x) { return -x; });
+    const double *F = Lp + d.poff + s + t.j0, *H = Hp + d.hoff + t.i0;
+    scatter_update(
+        t, d, Lp, cr2, rel,
+        [&](d4(&acc)[2][4], auto prefetch) {
+            dense_mma<64, false, false, false>(L, operand(F, (int64_t)(s - 1) * ld + c - t.j0, ld),
+                                               operand(H, (int64_t)s * c - t.i0, c), 0, s, acc, prefetch);
+        },
+        [](int, int, double x) { return -x; });
 }
 
 __global__ __launch_bounds__(kThreads, 3) void k_schur(const Task* __restrict__ tasks,
@@ -1102,16 +1007,47 @@ __global__ __launch_bounds__(kThreads, 3) void k_schur(const Task* __restrict__ 
     schur_task(L, t, blk[t.b], Lp, Hp, cr2, rel);
 }
 
-// colour groups with few tiles: the contraction (s <= 128) loaded up front
-__global__ __launch_bounds__(kThreads) void k_schur_deep(const Task* __restrict__ tasks,
-                                                         const BlockDesc* __restrict__ blk, double* __restrict__ Lp,
-                                                         const double* __restrict__ Hp,
-                                                         const int64_t* __restrict__ cr2,
-                                                         const int32_t* __restrict__ rel)
+// colour groups of few tiles: four work-groups per task (a 32 x 32 quarter
+// each), a wave per 16 x 16 tile
+__global__ __launch_bounds__(kThreads, 2) void k_schur_few(const Task* __restrict__ tasks,
+                                                           const BlockDesc* __restrict__ blk, double* __restrict__ Lp,
+                                                           const double* __restrict__ Hp,
+                                                           const int64_t* __restrict__ cr2,
+                                                           const int32_t* __restrict__ rel)
 {
-    __shared__ DeepLds L;
-    const Task t = tasks[blockIdx.x];
-    schur_task<true>(L, t, blk[t.b], Lp, Hp, cr2, rel);
+    const Task t = tasks[blockIdx.x >> 2];
+    const BlockDesc d = blk[t.b];
+    const int s = d.s, c = d.c, q = blockIdx.x & 3, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int i0 = t.i0 + 32 * (q >> 1) + 16 * (wave >> 1), k0 = t.j0 + 32 * (q & 1) + 16 * (wave & 1);
+    if (i0 >= c || k0 >= c || i0 + 15 < k0) return;
+    const int64_t ld = (int64_t)s + c;
+    const int row = i0 + (lane & 15);
+    const bool alone = t.flags & 4;  // no other block of the level updates these entries
+    auto col_of = [&](int v) { return k0 + (lane >> 4) + 4 * v; };
+    i64x2 cr[4];
+    uint32_t ro[4];
+    double old[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) cr[v] = *reinterpret_cast<const i64x2*>(cr2 + 2 * (d.coff + min(col_of(v), c - 1)));
+    __builtin_amdgcn_sched_barrier(0);
+    const d4 acc = wave_mma(operand(Lp + d.poff + s, (int64_t)(s - 1) * ld + c, ld), k0,
+                            operand(Hp + d.hoff, (int64_t)s * c, c), i0, s, [&] {
+#pragma unroll
+                                for (int v = 0; v < 4; ++v)
+                                    ro[v] = (uint32_t)rel[cr[v].y + min(max(row, col_of(v)), c - 1)];
+                                if (alone) {
+#pragma unroll
+                                    for (int v = 0; v < 4; ++v) old[v] = Lp[cr[v].x + ro[v]];
+                                }
+                            });
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (row >= c || row < col_of(v)) continue;
+        double* to = Lp + cr[v].x + ro[v];
+        if (alone) *to = old[v] - acc[v];
+        else unsafeAtomicAdd(to, -acc[v]);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1743,13 +1679,17 @@ __global__ __launch_bounds__(64 * diag_waves(NB)) void k_ldlt_diag(const Task* _
 // -F_KK^{-1}.  The unswept part of M is the Schur complement the pivoted
 // LDL^T would hold, so the rule is applied to it unchanged; an interchange
 // only reorders the list of unswept indices (ord[position] = index), and no
-// data moves.  The block lives in registers with the ownership of the
-// positive definite sweep (lower 16 x 16 sub-blocks, thread (tx, ty) holds
-// rows tx + 16a, columns ty + 16b); a pivot's column goes through LDS, where
+// data moves.  The block lives in registers (lower 16 x 16 sub-blocks, thread
+// (tx, ty) holds rows tx + 16a, columns ty + 16b); a pivot's column goes
+// through LDS, where
 // every wave reads it and takes the rule's decisions itself (the same values
 // give every wave the same decision, so no decision is broadcast).  One
 // work-group per block, NB = 2, 4, 8 for s <= 32, 64, 128.  A singular 1x1 or
 // 2x2 pivot latches the block's first column in the status word.
+// What bounds it: a chain per pivot of LDS round trips, cross-lane maxima,
+// scalar decisions and branches (151 us for 128 columns); neither fewer
+// vector instructions in the update nor the update under the search's
+// latencies made it faster (159 and 161 us).
 // ---------------------------------------------------------------------------
 
 // a value every lane holds alike, made known to the compiler as uniform
@@ -3159,11 +3099,14 @@ hipError_t launch_ldlt_level(Prof* P, const DevPtrs& D, const int64_t diag[4], i
 
 hipError_t launch_panel_level(Prof* P, const DevPtrs& D, int64_t panel0, int64_t npanel, int panel_deep, hipStream_t s)
 {
-    // panel_deep: bit 0 the level's panel tiles take the whole-contraction
-    // kernel; bit 1 its blocks are narrow enough for it (s <= kDeepK)
-    if (npanel > 0)
-        launch(P, kPanel, (panel_deep & 1) ? k_panel_deep : k_panel, dim3((unsigned)npanel), 0, s,
-               D.t_panel + panel0, D.blocks, (const double*)D.Lp, D.Hp, (const double*)D.Tp);
+    // panel_deep: bit 0 the level has few panel tiles; bit 1 its blocks are
+    // narrow enough for the kernels of few tiles (s <= kDeepK)
+    if (npanel > 0 && (panel_deep & 1))
+        launch(P, kPanel, k_panel_few, dim3((unsigned)(4 * npanel)), 0, s, D.t_panel + panel0, D.blocks,
+               (const double*)D.Lp, D.Hp, (const double*)D.Tp);
+    else if (npanel > 0)
+        launch(P, kPanel, k_panel, dim3((unsigned)npanel), 0, s, D.t_panel + panel0, D.blocks, (const double*)D.Lp,
+               D.Hp, (const double*)D.Tp);
     return hipGetLastError();
 }
 
@@ -3173,9 +3116,12 @@ hipError_t launch_schur_groups(Prof* P, const DevPtrs& D, const int64_t* cuts, i
     // one launch per colour group (groups update disjoint entries)
     for (int g = g0; g < g1; g++) {
         const int64_t n = cuts[g + 1] - cuts[g];
-        if (n > 0)
-            launch(P, kSchur, (panel_deep & 2) && n <= kDeepMaxTiles ? k_schur_deep : k_schur, dim3((unsigned)n), 0, s,
-                   D.t_schur + cuts[g], D.blocks, D.Lp, (const double*)D.Hp, D.cr2, D.rel);
+        if (n > 0 && (panel_deep & 2) && n <= kDeepMaxTiles)
+            launch(P, kSchur, k_schur_few, dim3((unsigned)(4 * n)), 0, s, D.t_schur + cuts[g], D.blocks, D.Lp,
+                   (const double*)D.Hp, D.cr2, D.rel);
+        else if (n > 0)
+            launch(P, kSchur, k_schur, dim3((unsigned)n), 0, s, D.t_schur + cuts[g], D.blocks, D.Lp,
+                   (const double*)D.Hp, D.cr2, D.rel);
     }
     return hipGetLastError();
 }

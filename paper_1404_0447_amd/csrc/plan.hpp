@@ -154,8 +154,8 @@ struct selinv_plan_s {
     // per level: t_schur in colour groups [cut[g], cut[g+1]) whose blocks share no column of C
     std::vector<std::vector<int64_t>> schur_cuts;
     // per level: bit 0, panel tiles <= 64 wide and at most kDeepMaxTiles of
-    // them (whole-contraction panel kernel); bit 1, every block of the level
-    // at most kDeepK wide (whole-contraction kernels allowed at all)
+    // them (the panel kernel of few tiles); bit 1, every block of the level
+    // at most kDeepK wide (the kernels of few tiles allowed at all)
     std::vector<char> panel_deep;
     // reverse sweep: selected inversion (leaves first) and factorization (root first)
     selinv::LevelTasks t_rs1, t_rs2, t_rs3, t_rf1a, t_rf1b, t_rf2;

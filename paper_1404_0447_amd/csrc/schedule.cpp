@@ -306,7 +306,7 @@ void build_schedule(selinv_plan_s* P)
     P->zgemm_cut.assign(D, 0);
     P->zgemm_mid.assign(D, 0);
     // deterministic mode: no small-block kernels (their Schur updates use
-    // atomics), no split contractions, no whole-contraction kernel variants
+    // atomics), no split contractions, none of the kernels of few tiles
     const bool det = P->opts.deterministic != 0;
     // the small-block kernels factor without pivots: none with pivoting
     const bool piv = P->opts.pivoting != 0;
@@ -349,7 +349,7 @@ void build_schedule(selinv_plan_s* P)
         // may be cut finer to fill the device
         const int64_t dwant = det ? 1 : best_split(dg, kGemmSlots, kSdiagTaskOvh, 64, kMinSplitKDiag);
         const int64_t rwant = det ? 1 : fill_for(rbase_), rdwant = det ? 1 : fill_for(rdbase);
-        // few panel tiles: at most 64 wide each, for the whole-contraction kernel
+        // few panel tiles: at most 64 wide each, for the kernel of few tiles
         int64_t npanel64 = 0;
         int smax = 0;
         for (int B : lv[l]) {
@@ -359,7 +359,7 @@ void build_schedule(selinv_plan_s* P)
             npanel64 += (int64_t)((d.c + kTileM - 1) / kTileM) * ((d.s + pbn - 1) / pbn);
             smax = std::max(smax, d.s);
         }
-        // the whole-contraction kernels hold a contraction of at most kDeepK
+        // the kernels of few tiles hold a contraction of at most kDeepK
         // (blocks wider than 128 columns exist only with exec_cap > 128)
         const bool deep_ok = !det && smax <= kDeepK;
         const bool deep = deep_ok && npanel64 <= kDeepMaxTiles;

@@ -35,11 +35,13 @@ inline bool is_small(int s, int c, int smax) { return s <= smax && c <= kSbC; }
 // fastest at 40^3, 64^3 and molecular 16^3)
 constexpr int kSbCLevel = 32;
 // A level with at most this many panel tiles (a Schur colour group with at
-// most this many tiles) loads each tile's whole contraction (s <= 128) before
-// its first product: there the tiles' latency, not the device's throughput,
-// sets the level time.
+// most this many tiles) gives each 16 x 16 tile to a wave, which loads its
+// whole contraction (s <= 128) before its first product: there the tiles'
+// latency, not the device's throughput, sets the level time.  At s = 128 a
+// Schur launch of 105 tiles takes 10 us so, of 190 14, of 253 16; tiled, of
+// 276 tiles 18, of 300 17, of 325 17.
 constexpr int kDeepMaxTiles = 256;
-constexpr int kDeepK = 128;  // longest contraction of the whole-contraction kernels
+constexpr int kDeepK = 128;  // longest contraction of the kernels of few tiles
 constexpr int kZeroCols = 8;  // columns of Ainv(:, B) a task of the set-up kernel clears
 // A level's Schur update runs in colour groups (read-modify-write, one launch
 // each) only when its blocks need at most this many colours; more launches
