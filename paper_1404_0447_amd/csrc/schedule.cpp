@@ -344,7 +344,11 @@ void build_schedule(selinv_plan_s* P)
             // off-diagonal tile
             dg.push_back({(int64_t)nd * nd, d.c, kDiagTile64});
         }
-        const int64_t want = det ? 1 : best_split(gg, kGemmSlots, kGemmTaskOvh, 64);
+        // shorter pieces where even those leave every work-group a CU of its own
+        int64_t few = 0;
+        for (const TileGroup& g : gg) few += g.count * split_for(g.c, g.c, kMinSplitKFew);
+        const int mink = few <= kGemmSlots / 2 ? kMinSplitKFew : kMinSplitK;
+        const int64_t want = det ? 1 : best_split(gg, kGemmSlots, kGemmTaskOvh, 64, mink);
         // a block has only nd (nd + 1) / 2 diagonal pairs: their contraction
         // may be cut finer to fill the device
         const int64_t dwant = det ? 1 : best_split(dg, kGemmSlots, kSdiagTaskOvh, 64, kMinSplitKDiag);
@@ -405,7 +409,7 @@ void build_schedule(selinv_plan_s* P)
             // forward, tiled path
             // contractions over C are split into pieces of >= kMinSplitK rows
             // when a level has too few tiles to fill the device
-            const int split = split_for(want, c);
+            const int split = split_for(want, c, mink);
             const int dsplit = split_for(dwant, c, kMinSplitKDiag);
             const int nd64 = (s + kDiagTile64 - 1) / kDiagTile64;
             // Ainv(B,B) accumulates (from T) when a contraction is split or

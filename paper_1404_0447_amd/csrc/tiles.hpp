@@ -56,10 +56,15 @@ constexpr int kFillTiles = 1024;
 // target (256 CUs x 2); the per-level split is sized for them
 constexpr long kGemmSlots = 512;
 // fixed cost of one work-group of the split contractions, in 16-deep chunks
-// (swept over 3..12 at 64^3: 6 fastest)
+// (swept over 3, 6, 10 at 64^3: gather-GEMM 18.3, 18.1, 18.2 ms)
 constexpr double kGemmTaskOvh = 6.0;
 constexpr double kSdiagTaskOvh = 8.0;  // smaller epilogue (half a 64 x 64 tile)
 constexpr int kMinSplitK = 128;  // rows of C per split piece, at least
+// the same in a level that even so has at most a work-group per CU (kGemmSlots
+// / 2), where a piece's length is its time: gather-GEMM of a 301 x 257 grid
+// 202 -> 164 us, of the indefinite 12^3 matrix 820 -> 777, of 40^3 1.82 ->
+// 1.78 ms; 32 rows 181, 771 us, 1.78 ms.  With 64 everywhere 40^3 took 1.83.
+constexpr int kMinSplitKFew = 64;
 constexpr int kMinSplitKDiag = 64;  // the same for the diagonal tile pairs
 
 // output-column tile of a block of width s: 16, 32, 64 or 128
