@@ -237,9 +237,9 @@ static void push_sb_groups(const std::vector<int>& small, int op, std::vector<Ta
 // Complex plans (deterministic schedule: every gather-GEMM tile and
 // diagonal-step task contracts over all of C): a level with fewer than
 // kZSplitFill / 2 tasks of one kind cuts each task's contraction into
-// pieces of at least kZSplitRows rows (half that in a level of fewer than
-// kZSplitFewTasks tasks; boundaries on 16-row chunks), about
-// kZSplitFill pieces in all.  A piece (flags bit 5) writes its partial
+// pieces of at least kZSplitRows rows, about kZSplitFill pieces in all (of
+// kZSplitFewRows and kZSplitFewFill in a level of fewer than kZSplitFewTasks
+// tasks; boundaries on 16-row chunks).  A piece (flags bit 5) writes its partial
 // product over its rows of C to scratch slot `pad`; after the pieces, one
 // task per split task (same block and tile origin, bn = pieces, kb = first
 // slot, flags bit 6) sums them in piece order and writes the result.
@@ -253,9 +253,9 @@ static int64_t zsplit_level(const selinv_plan_s* P, LevelTasks& lt, int l, int64
     const int64_t t0 = lt.off[l], n = (int64_t)t.size() - t0;
     mid = cut = (int64_t)t.size();
     if (n <= 0 || n >= kZSplitFill / 2) return 0;
-    const int want = (int)((kZSplitFill + n - 1) / n);
-    // levels with very few tasks (a single pole's) take shorter pieces
-    const int rows = n < kZSplitFewTasks ? kZSplitRows / 2 : kZSplitRows;
+    const bool few = n < kZSplitFewTasks;
+    const int want = (int)(((few ? kZSplitFewFill : kZSplitFill) + n - 1) / n);
+    const int rows = few ? kZSplitFewRows : kZSplitRows;
     std::vector<Task> whole, pieces, sums;
     int64_t slot = 0;
     for (int64_t q = t0; q < (int64_t)t.size(); q++) {

@@ -17,11 +17,16 @@ constexpr int kZMaxS = 64;       // widest block of the complex path (one 64-wid
 // writes its 64 x 64 complex partial product to a scratch slot of
 // kZSlotDoubles doubles.
 constexpr int kZSplitFill = 2048;
-constexpr int kZSplitRows = 64;
-// levels with fewer tasks than this (those of a single pole) cut pieces of
-// kZSplitRows / 2 rows: one pole 5.85 -> 5.67 ms, while 32-row pieces in the
-// batch's larger levels cost more in sums than they gained
-constexpr int kZSplitFewTasks = 64;
+constexpr int kZSplitRows = 128;
+// levels with fewer tasks than this (those of a single pole) cut shorter
+// pieces and fewer of them: there a piece's length is its time, while in the
+// larger levels of a batch the pieces' sums cost more than they gain.
+// Measured (one pole, 32 poles; ms): 64 rows (32 below 64 tasks) and a fill of
+// 2,048 everywhere 3.51, 30.3; 128 and 64 rows 3.78, 30.0; 32 rows below 128
+// tasks and a fill of 768 everywhere 3.40, 30.5.
+constexpr int kZSplitFewTasks = 128;
+constexpr int kZSplitFewRows = 32;
+constexpr int kZSplitFewFill = 768;
 constexpr size_t kZSlotDoubles = 2 * (size_t)kZMaxS * kZMaxS;
 
 // small blocks run whole on one wave (all phases, 16 x 16 MFMA tiles)
