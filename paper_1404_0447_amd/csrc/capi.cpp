@@ -358,13 +358,12 @@ hipError_t factor_levels(selinv_plan_s* P, const DevPtrs& D, const double* d_val
     if (!e) e = launch_fill(prof, kAssemble, D.Lp, P->arena, 0.0, s);
     if (!e) e = launch_scatter_set(prof, kAssemble, d_valsA, D.asm_off, P->nnzA, D.Lp, s);
     const int spd = P->opts.require_spd ? 1 : 0;
-    const int deep_ok = P->opts.deterministic ? 0 : 3;
     for (int l = P->exec.depth - 1; l >= 0 && !e; l--) {
         const auto& q = P->t_sb.off;
         const auto& b = P->t_panel.off;
         const auto& a = P->t_ldlt.off;
         const auto& cut = P->schur_cuts[l];
-        const int deep = P->panel_deep[l] & deep_ok;
+        const int deep = P->panel_deep[l];
         const int64_t dg[4] = {a[l], P->ldlt_cut[2 * l], P->ldlt_cut[2 * l + 1], a[l + 1]};
         e = launch_sb_factor(prof, D, q[l], q[l + 1] - q[l], spd, s);
         if (!e) e = P->opts.pivoting ? launch_ldlt_bk(prof, D, dg, s)

@@ -59,7 +59,8 @@ hipError_t launch_ldlt_bk(Prof* P, const DevPtrs& D, const int64_t diag[4], hipS
 // diag[0..3]: the level's diagonal-block tasks for s <= 32, <= 64 and wider
 hipError_t launch_ldlt_level(Prof* P, const DevPtrs& D, const int64_t diag[4], int require_spd, hipStream_t s);
 // panel_deep bit 0: panel kernel of few tiles; bit 1: Schur kernel of few tiles
-// allowed for small groups (0 in the deterministic mode)
+// allowed for small groups (their sums are the tiled kernels', entry by entry
+// in the same order, so the deterministic mode takes them too)
 hipError_t launch_panel_level(Prof* P, const DevPtrs& D, int64_t panel0, int64_t npanel, int panel_deep, hipStream_t s);
 // Schur colour groups [g0, g1) of a level, cuts as in schur_cuts
 hipError_t launch_schur_groups(Prof* P, const DevPtrs& D, const int64_t* cuts, int g0, int g1, int panel_deep,

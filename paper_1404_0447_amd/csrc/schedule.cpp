@@ -306,7 +306,7 @@ void build_schedule(selinv_plan_s* P)
     P->zgemm_cut.assign(D, 0);
     P->zgemm_mid.assign(D, 0);
     // deterministic mode: no small-block kernels (their Schur updates use
-    // atomics), no split contractions, none of the kernels of few tiles
+    // atomics), no split contractions
     const bool det = P->opts.deterministic != 0;
     // the small-block kernels factor without pivots: none with pivoting
     const bool piv = P->opts.pivoting != 0;
@@ -365,7 +365,7 @@ void build_schedule(selinv_plan_s* P)
         }
         // the kernels of few tiles hold a contraction of at most kDeepK
         // (blocks wider than 128 columns exist only with exec_cap > 128)
-        const bool deep_ok = !det && smax <= kDeepK;
+        const bool deep_ok = smax <= kDeepK;
         const bool deep = deep_ok && npanel64 <= kDeepMaxTiles;
         P->panel_deep[l] = (char)((deep ? 1 : 0) | (deep_ok ? 2 : 0));
         for (int B : lv[l]) {

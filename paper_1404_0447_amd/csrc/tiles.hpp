@@ -9,7 +9,7 @@ constexpr int kTileM = 64;       // rows of an MFMA output tile (gather-GEMM, pa
 constexpr int kSchurTile = 64;   // edge of a Schur-update tile (lower c x c)
 constexpr int kDiagTile = 32;    // edge of a diagonal-block tile (pairs (I,J), I >= J)
 constexpr int kDiagTile64 = 64;  // the same on the per-level path (pipelined MFMA tile)
-constexpr int kLdsDiagMax = 128; // diagonal blocks swept in registers up to this width
+constexpr int kLdsDiagMax = 128; // diagonal blocks inverted in LDS and registers up to this width
 constexpr int kZMaxS = 64;       // widest block of the complex path (one 64-wide tile per diagonal step)
 // Complex gather-GEMM and diagonal step: a level with fewer than
 // kZSplitFill / 2 tasks cuts each task's contraction over C into pieces of
