@@ -1305,38 +1305,96 @@ __device__ __forceinline__ double recip(double d)
 }
 
 // ---------------------------------------------------------------------------
-// Diagonal block, s <= 16 NB (NB = 2, 4, 8): L_BB, D and T = F_BB^{-1} by
-// symmetric Gauss-Jordan sweeps over pivot blocks of 16 columns.  Sweeping
-// block p, with C(R) = M(R, p) (16 x 16 for every block row R) and
-// Q = M(p, p)^{-1}:
-//   M(I, J) -= (C(I) Q) C(J)^T  (I, J != p),  M(R, p) = C(R) Q,  M(p, p) = -Q;
-// after the last block M = -F_BB^{-1} = -T.  M's lower 16 x 16 tiles live in
-// LDS; the products run on MFMA.
+// Diagonal block, s <= 16 NB (NB = 2, 4, 8): L_BB, D and T = F_BB^{-1} by the
+// symmetric sweep of one pivot after the other,
+//   M(i, k) -= c_i c_k / d,  M(i, j) = M(j, i) = c_i / d,  M(j, j) = -1 / d
+// (pivot j, c = M(:, j), d = c_j), after which M = -F_BB^{-1}, arranged by
+// pivot blocks of 16 columns.  Block p is factored in one wave's registers
+// (ldl16).  For every block row R, with C(R) = M(R, p), and C(p) = -I,
+//   Y(R) = C(R) L_pp^{-T} by substitution, column after column, and
+//   l(R) = Y(R) D_p^{-1}: what each pivot finds in the rows and its multipliers;
+//   M(I, J) = M'(I, J) - l(I) Y(J)^T for every tile, with M' = M outside row
+// and column p and 0 in them.  M's lower 16 x 16 tiles live in the registers of
+// the waves that update them, by MFMA; a tile goes to LDS when its column is
+// the next step's.
+// These are the scalar sweep's operations in its order.  An explicit
+// Q = M(p, p)^{-1} (C(R) Q for l(R) L_pp^{-1}) would square the condition
+// number of the pivot block; and the pivot blocks have to be exactly
+// symmetric, or L D L^T no longer gives F_BB back to rounding.  Largest error
+// of T, relative, SPD of condition 1e8, 24 columns: the scalar sweep 3e-10,
+// this 4e-10, with Q 3e-6; Gaussian kernel of condition 5e7, 128 columns:
+// 9e-10, 4e-10, no digit.
 //
 // What bounds it is the chain of s dependent pivots.  So wave 0 does nothing
-// but that chain: it updates the next pivot block, inverts it in its own
-// registers (gj16: the pivot column and row go between lanes by row
-// broadcasts and row swaps, no LDS and no barrier; about 220 cycles a pivot,
-// against about 1,000 when each pivot's column went through LDS behind a
-// barrier) and stores -Q, while the other waves update the other tiles and
-// form L_BB.  A block step has two barriers: first all waves form
-// N(R) = -C(R) Q from the published tiles, then the updates run.
-// One block of 128 columns: 61 -> 33 us, of 64: 20 -> 14 us (launch
-// included); 32 columns take about 8 us either way.
+// but that chain: it updates the next pivot block, factors it (the pivot column
+// and row go between lanes by row broadcasts and row swaps, no LDS and no
+// barrier) and publishes the factors, while the other waves update the tiles
+// and write L_BB.  A block step has two barriers: first all waves form Y(R) and
+// l(R) from the published tiles, then the updates run.  (With every tile in
+// LDS, its reads and writes took longer than the chain: 33 us for 128 columns.)
+// One block of 128 columns: 31.9 us (61 when each pivot's column went through
+// LDS behind a barrier), of 64: 14.5 us (20; launch included).
 //
-// L_BB(R, p) = C(R) Q L_pp = C(R) L_pp^{-T} D_p^{-1} needs one more product a
-// tile and is off the pivot chain.  Rows and columns past s hold the
-// identity: their pivots are 1 and they touch nothing else.
+// Rows and columns past s hold the identity and are not swept.
 // ---------------------------------------------------------------------------
-constexpr int kDiagPad = 18;  // 16 doubles a row and 16 bytes: every row 16-byte aligned, operand reads conflict-free
+// doubles from row to row: of M's tiles, read and written 8 bytes a lane, and of
+// C, N and the pivot block's factors, read 16 bytes a lane (every row aligned
+// to that); either is free of bank conflicts
+constexpr int kTilePad = 17, kDiagPad = 18;
 template <int NB>
 struct alignas(16) DiagLds {
-    double M[NB * (NB + 1) / 2][16][kDiagPad];  // tile (I, J), I >= J, at I (I + 1) / 2 + J
-    double C[16 * NB][kDiagPad];
-    double N[16 * NB][kDiagPad];
-    double Lb[2][16][kDiagPad];  // -L_pp
-    double D[2][16];
+    double M[NB * (NB + 1) / 2][16][kTilePad];  // published tile (I, J), I >= J, at I (I + 1) / 2 + J
+    double C[16 * NB][kDiagPad];  // Y(R)
+    double N[16 * NB][kDiagPad];  // -l(R)
+    double Lb[2][16][kDiagPad];   // -L_pp below its diagonal, else 0
+    double D[2][16], inv[2][16];  // D_p and its reciprocal
 };
+
+// the power of two s with |d| s in [1, 4), from d's exponent bits (integer
+// operations: frexp and ldexp run at a quarter of the rate)
+__device__ __forceinline__ double pow2_scale(double d)
+{
+    return __hiloint2double(max(0x7FE00000 - (__double2hiint(d) & 0x7FF00000), 0x00100000), 0);
+}
+// 1 / f: one third-order step from the hardware's estimate
+__device__ __forceinline__ double recip3(double f)
+{
+    const double y = __builtin_amdgcn_rcp(f), h = fma(-f, y, 1.0);
+    return fma(y, fma(h, h, h), y);
+}
+
+// Elimination of a symmetric 16 x 16 block, lane (m, g) holding row m, columns
+// g + 4 v.  The part not yet eliminated stays symmetric to the last bit: an
+// entry's update c_i c_k / d is formed as (c_i c_k) / d, the same for (k, i),
+// and c_i is scaled by d's exponent beforehand so that the product neither
+// overflows nor underflows where the update would not.  Rows from n on hold
+// the identity; pivots from the next multiple of 4 on are skipped.
+//
+// What bounds it is issue: a lone wave issues an instruction per 4 cycles
+// (5 where it is 8 bytes long, 16 for a reciprocal, 8 for a row swap), and no
+// result is later than that.
+
+// X(., j): column j as pivot j finds it (d_j in row j), and what has been left
+// of the rows above.  P is used up.
+__device__ __forceinline__ void ldl16(double (&P)[4], double (&X)[4], const int g, const int n)
+{
+    double c = row_copy<0>(P[0]);  // column j in every lane (m, .)
+    StaticFor<0, 4>::run([&](auto vc) {
+        constexpr int vj = decltype(vc)::value;
+        if (4 * vj >= n) return;  // uniform
+        StaticFor<4 * vj, 4 * vj + 4>::run([&](auto jc) {
+            constexpr int j = decltype(jc)::value, j1 = j < 15 ? j + 1 : 15;
+            const double d = row_lane<j>(c), s = pow2_scale(d), r = recip3(d * s), u = c * s;
+            // the next column, broadcast before its update
+            const double next = row_copy<(j1 & 3)>(P[j1 >> 2]);
+            const double cn = fma(-(u * row_lane<j1>(c)), r, next);
+#pragma unroll
+            for (int v = j1 >> 2; v < 4; ++v) P[v] = fma(-(u * row_lane<j>(P[v])), r, P[v]);
+            X[vj] = g == (j & 3) ? c : X[vj];
+            c = cn;
+        });
+    });
+}
 
 // Gauss-Jordan inversion of a symmetric 16 x 16 block, lane (m, g) holding
 // row m, columns g + 4 v.  Pivot j: l = column j / d_j; every row m != j
@@ -1372,6 +1430,35 @@ __device__ __forceinline__ void gj16(double (&P)[NV], double (&L)[NV], double& d
     for (int v = 0; v < NV; ++v) P[v] *= im;
 }
 
+// one wave's LDS writes before its own reads of other lanes' values
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Y = C L^{-T} for a unit lower triangular L and 16 rows, lane (m, g) holding
+// rows g + 4 v, column m: column j, final, leaves the columns right of it.
+// lb: -L(m, j), 0 for m <= j.  Each step multiplies a value broadcast within
+// the rows of 16 lanes in the instruction itself; four independent ones follow
+// each other, which keeps the wait states between a write and its broadcast.
+__device__ __forceinline__ void substitute16(double (&x)[4], const double (&lb)[16])
+{
+#define SELINV_FMAC(V, J) "v_fmac_f64_dpp %" #V ", %" #V ", %[l" #J "] row_newbcast:" #J " row_mask:0xf bank_mask:0xf\n\t"
+#define SELINV_STEP(J) SELINV_FMAC(0, J) SELINV_FMAC(1, J) SELINV_FMAC(2, J) SELINV_FMAC(3, J)
+    asm volatile("s_nop 1\n\t"
+        SELINV_STEP(0) SELINV_STEP(1) SELINV_STEP(2) SELINV_STEP(3) SELINV_STEP(4)
+        SELINV_STEP(5) SELINV_STEP(6) SELINV_STEP(7) SELINV_STEP(8) SELINV_STEP(9)
+        SELINV_STEP(10) SELINV_STEP(11) SELINV_STEP(12) SELINV_STEP(13) SELINV_STEP(14)
+        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3])
+        : [l0] "v"(lb[0]), [l1] "v"(lb[1]), [l2] "v"(lb[2]), [l3] "v"(lb[3]), [l4] "v"(lb[4]), [l5] "v"(lb[5]),
+          [l6] "v"(lb[6]), [l7] "v"(lb[7]), [l8] "v"(lb[8]), [l9] "v"(lb[9]), [l10] "v"(lb[10]), [l11] "v"(lb[11]),
+          [l12] "v"(lb[12]), [l13] "v"(lb[13]), [l14] "v"(lb[14]));
+#undef SELINV_STEP
+#undef SELINV_FMAC
+}
+
 // NW waves work on the block.  Lane (m, g) = (l % 16, l / 16) holds entry (m, g + 4 v) of a 16 x 16 block in
 // register v: the form of both MFMA operands (k = g + 4 v in step v) and,
 // with the product formed transposed, of its result.
@@ -1380,11 +1467,10 @@ __device__ __forceinline__ void ldlt_blocks(const BlockDesc d, double* __restric
                                             unsigned long long* __restrict__ status, int require_spd, DiagLds<NB>& S)
 {
     // tile waves: all but wave 0, and but wave 4 of 8, which shares its SIMD
-    // and forms L_BB
+    // and writes L_BB.  Every wave substitutes rows, wave 0 one
     constexpr int NK = NW == 8 ? 6 : NW - 1;
     constexpr int NT = NB * (NB + 1) / 2, NL = (NT + NK - 1) / NK;
-    constexpr int kGroup = NB < 8 ? 1 : 3;  // tiles updated together: independent MFMA chains
-    constexpr int kRows = NB == 8 && NK < 6 ? 2 : 1;      // rows of N a tile wave forms together
+    constexpr int kRows = (NB - 1 + NW - 2) / (NW - 1);  // rows a wave substitutes, interleaved
     const int s = d.s, nb = (s + 15) >> 4;
     const int64_t ld = (int64_t)d.s + d.c;
     double* F = Lp + d.poff;
@@ -1403,20 +1489,30 @@ __device__ __forceinline__ void ldlt_blocks(const BlockDesc d, double* __restric
         I = __builtin_popcountll(kStarts & ((2ull << t) - 1));
         J = t - tile(I, 0);
     };
-    double Q[4];
-    // invert the pivot block P of step p; -Q, -L_pp and D to LDS
+    // factor the pivot block P of step p
     auto pivots = [&](int p, const d4& P) {
-        double L[4] = {0.0, 0.0, 0.0, 0.0}, dm = 1.0;
+        const int buf = p & 1;
+        double Q[4], C[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) Q[v] = P[v];
-        gj16(Q, L, dm, m, g);
+        for (int v = 0; v < 4; ++v) {
+            Q[v] = P[v];
+            C[v] = m == g + 4 * v ? 1.0 : 0.0;
+        }
+        ldl16(Q, C, g, s - 16 * p);
+        double dm = C[0];
+#pragma unroll
+        for (int v = 1; v < 4; ++v) dm = m >> 2 == v ? C[v] : dm;
+        const double sc = pow2_scale(dm), im = sc * recip3(dm * sc);
+        if (g == (m & 3)) {
+            S.D[buf][m] = dm;
+            S.inv[buf][m] = im;
+        }
+        wave_sync();
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int k = g + 4 * v;
-            S.M[tile(p, p)][m][k] = -Q[v];
-            S.Lb[p & 1][m][k] = m > k ? -L[v] : (m == k ? -1.0 : 0.0);
+            S.Lb[buf][m][k] = m > k ? -C[v] * S.inv[buf][k] : 0.0;
         }
-        if (g == 0) S.D[p & 1][m] = dm;
     };
     // F(i, j) of tile (I, J), the identity past s
     auto load_tile = [&](int I, int J) {
@@ -1430,163 +1526,114 @@ __device__ __forceinline__ void ldlt_blocks(const BlockDesc d, double* __restric
         }
         return x;
     };
-    if (tiles) {
-        d4 x[NL];
-        const int nt = nb * (nb + 1) / 2;
+    d4 P = {0, 0, 0, 0};  // the chain's next pivot block
+    // this wave's tiles, every NK-th
+    const int nt = nb * (nb + 1) / 2;
+    d4 x[NL];
+    int I[NL], J[NL];
 #pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            int I, J;
-            tile_of(min(1 + u * NK + wk, nt - 1), I, J);
-            x[u] = load_tile(I, J);
-        }
-#pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            const int t = 1 + u * NK + wk;
-            if (t < nt) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) S.M[t][m][g + 4 * v] = x[u][v];
-            }
-        }
+    for (int u = 0; u < NL; ++u) {
+        tile_of(min(u * NK + wk, nt - 1), I[u], J[u]);
+        if (tiles) x[u] = load_tile(I[u], J[u]);
     }
-    if (chain) pivots(0, load_tile(0, 0));
-    __syncthreads();
-    for (int p = 0; p < nb; ++p) {
+    if (chain) P = load_tile(0, 0);
+    // step -1 only factors the first pivot block
+    for (int p = -1; p < nb; ++p) {
         const int buf = p & 1;
         const bool more = p + 1 < nb;
-        // C(R), N(R)^T = -Q C(R)^T and M(R, p) = -N(R), rows R[0 .. n)
-        auto rows_of = [&](const double (&nQ)[4], const int* R, const bool* live, auto n, d4* acc, double (*c)[4]) {
-            constexpr int kN = decltype(n)::value;
+        // Y(R) and -l(R), rows R = p + 1 (wave 0), p + 2, .. cyclically to p.
+        // Lane (m, g) holds rows g + 4 v, column m, so that a column reaches
+        // the lanes right of it by a broadcast within rows of 16 lanes.
+        if (p >= 0 && wave < nb) {
+            const int step = chain ? nb : NW - 1;
+            int R[kRows];
+            double x[kRows][4], lb[16];
 #pragma unroll
-            for (int e = 0; e < kN; ++e) {
+            for (int j = 0; j < 16; j += 2) {
+                const d2 q = *reinterpret_cast<const d2*>(&S.Lb[buf][m][j]);
+                lb[j] = q.x;
+                lb[j + 1] = q.y;
+            }
+            const double inv = S.inv[buf][m];
+#pragma unroll
+            for (int e = 0; e < kRows; ++e) {
+                const int r = min(wave + e * step, nb - 1);
+                R[e] = p + 1 + r < nb ? p + 1 + r : p + 1 + r - nb;
                 const double* src = S.M[tile(max(R[e], p), min(R[e], p))][0];
-                if (R[e] > p) {
+                const int mk = R[e] > p ? 1 : kTilePad, gk = R[e] > p ? kTilePad : 1;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) c[e][v] = src[m * kDiagPad + g + 4 * v];
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) c[e][v] = src[(g + 4 * v) * kDiagPad + m];
+                for (int v = 0; v < 4; ++v) {
+                    const double c = src[m * mk + (g + 4 * v) * gk];
+                    x[e][v] = R[e] != p ? c : m == g + 4 * v ? -1.0 : 0.0;
                 }
             }
+            StaticFor<0, kRows>::run([&](auto ec) {
+                constexpr int e = decltype(ec)::value;
+                if (e == 0 || wave + e * step < nb) substitute16(x[e], lb);  // uniform
+            });
 #pragma unroll
-            for (int e = 0; e < kN; ++e) acc[e] = d4{0.0, 0.0, 0.0, 0.0};
+            for (int e = 0; e < kRows; ++e)
+                if (wave + e * step < nb) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-#pragma unroll
-                for (int e = 0; e < kN; ++e) acc[e] = mfma(nQ[v], c[e][v], acc[e]);
-#pragma unroll
-            for (int e = 0; e < kN; ++e)
-                if (live[e]) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) S.C[16 * R[e] + m][g + 4 * v] = c[e][v];
-                }
-            mfma_drain();
-#pragma unroll
-            for (int e = 0; e < kN; ++e)
-                if (live[e]) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) S.N[16 * R[e] + m][g + 4 * v] = acc[e][v];
-                    double* dst = S.M[tile(max(R[e], p), min(R[e], p))][0];
-                    if (R[e] > p) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) dst[m * kDiagPad + g + 4 * v] = -acc[e][v];
-                    } else {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) dst[(g + 4 * v) * kDiagPad + m] = -acc[e][v];
+                    for (int v = 0; v < 4; ++v) {
+                        S.C[16 * R[e] + g + 4 * v][m] = x[e][v];
+                        S.N[16 * R[e] + g + 4 * v][m] = -(x[e][v] * inv);
                     }
                 }
-        };
-        d4 P = {0, 0, 0, 0};
-        if (chain && more) {
-            // row p + 1, and the next pivot block with it: its update needs
-            // nothing from the other waves
-            const double nQ[4] = {-Q[0], -Q[1], -Q[2], -Q[3]};
-            const int R[1] = {p + 1};
-            const bool live[1] = {true};
-            d4 acc[1];
-            double c[1][4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) P[v] = S.M[tile(p + 1, p + 1)][m][g + 4 * v];
-            rows_of(nQ, R, live, std::integral_constant<int, 1>{}, acc, c);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) P = mfma(c[0][v], acc[0][v], P);
-            mfma_drain();
         }
-        if (tiles) {
-            double nQ[4];
+        if (chain && more && p >= 0) {
+            // the next pivot block: its update needs nothing from the other
+            // waves.  Its upper entries are the lower ones: exactly symmetric
+            double(*tp)[kTilePad] = S.M[tile(p + 1, p + 1)];
+            wave_sync();
+            double y[4], n[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) nQ[v] = S.M[tile(p, p)][m][g + 4 * v];
-            // p + 2, p + 3, .. cyclically, without p
-            for (int r0 = 1 + wk; r0 < nb - 1; r0 += kRows * NK) {
-                int R[kRows];
-                bool live[kRows];
-                d4 acc[kRows];
-                double c[kRows][4];
-#pragma unroll
-                for (int e = 0; e < kRows; ++e) {
-                    const int r = min(r0 + e * NK, nb - 2);
-                    live[e] = r0 + e * NK < nb - 1;
-                    R[e] = p + 1 + r < nb ? p + 1 + r : p + 1 + r - nb;
-                }
-                rows_of(nQ, R, live, std::integral_constant<int, kRows>{}, acc, c);
+            for (int v = 0; v < 4; ++v) {
+                P[v] = tp[m][g + 4 * v];
+                y[v] = S.C[16 * (p + 1) + m][g + 4 * v];
+                n[v] = S.N[16 * (p + 1) + m][g + 4 * v];
             }
-        }
-        if (chain && !more && nb > 1) {
-            // the last step has no row p + 1: wave 0 takes the first of the others
-            const double nQ[4] = {-Q[0], -Q[1], -Q[2], -Q[3]};
-            const int R[1] = {0};
-            const bool live[1] = {true};
-            d4 acc[1];
-            double c[1][4];
-            rows_of(nQ, R, live, std::integral_constant<int, 1>{}, acc, c);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) P = mfma(y[v], n[v], P);
+            mfma_drain();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) tp[m][g + 4 * v] = P[v];
+            wave_sync();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) P[v] = tp[max(m, g + 4 * v)][min(m, g + 4 * v)];
         }
         __syncthreads();
         if (tiles) {
-            // M(I, J) += N(I) C(J)^T over the tiles outside row and column p
-            // and the next pivot block
-            const int nt = nb * (nb - 1) / 2;
-            for (int t0 = wk; t0 < nt; t0 += kGroup * NK) {
-                d4 x[kGroup];
-                d2 a[kGroup][2], b[kGroup][2];  // contraction index 4 g + t in step t
-                double(*tp[kGroup])[kDiagPad];
-                bool live[kGroup];
+            // M(I, J) = M'(I, J) - l(I) Y(J)^T
+            if (p >= 0) {
 #pragma unroll
-                for (int e = 0; e < kGroup; ++e) {
-                    int I, J;
-                    const int t = t0 + e * NK;
-                    tile_of(min(t, nt - 1), I, J);
-                    I += I >= p;
-                    J += J >= p;
-                    live[e] = t < nt && !(I == p + 1 && J == p + 1);
-                    tp[e] = S.M[tile(I, J)];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) x[e][v] = tp[e][m][g + 4 * v];
+                for (int u = 0; u < NL; ++u) {
+                    if (u * NK + wk >= nt) break;  // uniform
+                    d2 a[2], b[2];  // contraction index 4 g + t in step t
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
-                        a[e][h] = *reinterpret_cast<const d2*>(&S.C[16 * J + m][4 * g + 2 * h]);
-                        b[e][h] = *reinterpret_cast<const d2*>(&S.N[16 * I + m][4 * g + 2 * h]);
+                        a[h] = *reinterpret_cast<const d2*>(&S.C[16 * J[u] + m][4 * g + 2 * h]);
+                        b[h] = *reinterpret_cast<const d2*>(&S.N[16 * I[u] + m][4 * g + 2 * h]);
                     }
+                    if (I[u] == p || J[u] == p) x[u] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int w = 0; w < 2; ++w) x[u] = mfma(a[h][w], b[h][w], x[u]);
                 }
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w)
-#pragma unroll
-                        for (int e = 0; e < kGroup; ++e) x[e] = mfma(a[e][h][w], b[e][h][w], x[e]);
                 mfma_drain();
-#pragma unroll
-                for (int e = 0; e < kGroup; ++e)
-                    if (live[e]) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) tp[e][m][g + 4 * v] = x[e][v];
-                    }
             }
-        }
-        if (lower) {
-            // L_BB(R, p) = N(R) (-L_pp) below the pivot block, L_pp and D in it
-            const double* lb = &S.Lb[buf][0][0];
-            double a[4];
+            // what the next step reads: the rows' tiles of its column, and
+            // for wave 0 the pivot block after it (the next one is its own)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) a[v] = lb[(g + 4 * v) * kDiagPad + m];
+            for (int u = 0; u < NL; ++u)
+                if (u * NK + wk < nt && ((I[u] == p + 1) != (J[u] == p + 1) || (I[u] == J[u] && I[u] == p + 2))) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) S.M[u * NK + wk][m][g + 4 * v] = x[u][v];
+                }
+        }
+        if (lower && p >= 0) {
+            // L_BB(R, p) = l(R) below the pivot block, L_pp and D in it
             double* Fp = F + m + (int64_t)(16 * p + g) * ld;
             if (l0 == 0) {
                 const double dm = S.D[buf][m];
@@ -1595,27 +1642,17 @@ __device__ __forceinline__ void ldlt_blocks(const BlockDesc d, double* __restric
                     atomicMin(status, (unsigned long long)(d.first + row));
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const double x = m == g + 4 * v ? dm : -lb[m * kDiagPad + g + 4 * v];
+                    const double x = m == g + 4 * v ? dm : -S.Lb[buf][m][g + 4 * v];
                     if (row < s && m >= g + 4 * v) Fp[16 * p + (int64_t)(4 * v) * ld] = x;
                 }
             }
-            for (int R = p + 1 + l0; R < nb; R += 2 * lstep) {
-                const int R2 = min(R + lstep, nb - 1);
-                d4 x = {0, 0, 0, 0}, y = {0, 0, 0, 0};
+            for (int R = p + 1 + l0; R < nb; R += lstep) {
+                double x[4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    x = mfma(a[v], S.N[16 * R + m][g + 4 * v], x);
-                    y = mfma(a[v], S.N[16 * R2 + m][g + 4 * v], y);
-                }
-                mfma_drain();
-                // a repeated last row writes the same values twice
+                for (int v = 0; v < 4; ++v) x[v] = -S.N[16 * R + m][g + 4 * v];
                 if (16 * R + m < s) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) Fp[16 * R + (int64_t)(4 * v) * ld] = x[v];
-                }
-                if (16 * R2 + m < s) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) Fp[16 * R2 + (int64_t)(4 * v) * ld] = y[v];
                 }
             }
         }
@@ -1623,7 +1660,35 @@ __device__ __forceinline__ void ldlt_blocks(const BlockDesc d, double* __restric
         __syncthreads();
     }
     // T = -M, made exactly symmetric from the lower triangle
-    for (int t = wave; t < nb * (nb + 1) / 2; t += NW) {
+    if constexpr (NB == 2) {
+        // three tiles at most: their transposes straight to their columns
+        // (32 columns 8.3 us, through LDS 8.6; 128 columns 34.3 and 31.8)
+        if (tiles) {
+#pragma unroll
+            for (int u = 0; u < NL; ++u) {
+                double* Tl = T + 16 * I[u] + m + (int64_t)(16 * J[u] + g) * s;
+                double* Tu = T + 16 * J[u] + g + (int64_t)(16 * I[u] + m) * s;
+                const bool row = u * NK + wk < nt && 16 * I[u] + m < s;
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (row && (I[u] != J[u] || g + 4 * v <= m)) {
+                        Tl[(int64_t)(4 * v) * s] = -x[u][v];
+                        Tu[4 * v] = -x[u][v];
+                    }
+            }
+        }
+        return;
+    }
+    if (tiles) {
+#pragma unroll
+        for (int u = 0; u < NL; ++u)
+            if (u * NK + wk < nt) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) S.M[u * NK + wk][m][g + 4 * v] = x[u][v];
+            }
+    }
+    __syncthreads();
+    for (int t = wave; t < nt; t += NW) {
         int I, J;
         tile_of(t, I, J);
         double lo[4], up[4];  // entries (m, k) and (k, m), k = g + 4 v

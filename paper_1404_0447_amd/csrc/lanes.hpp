@@ -33,21 +33,19 @@ __device__ __forceinline__ double row_lane(double x)
     return __longlong_as_double(__builtin_amdgcn_update_dpp(0ll, __double_as_longlong(x), 0x150 + J, 0xF, 0xF, true));
 }
 
-// row G (of the wave's four rows of 16 lanes) in every row: halves, then
-// neighbouring rows swapped between two copies
-template <int G>
-__device__ __forceinline__ unsigned row_copy32(unsigned x)
-{
-    const auto a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    const unsigned y = (G & 2) ? a[1] : a[0];
-    const auto b = __builtin_amdgcn_permlane16_swap(y, y, false, false);
-    return (G & 1) ? b[1] : b[0];
-}
+// row G (of the wave's four rows of 16 lanes) of x in every row.  Rows of the
+// two halves h, l of x side by side: swapping neighbouring rows gives
+// (h0 l0 h2 l2) and (h1 l1 h3 l3); swapping halves with a copy (hG lG hG lG);
+// swapping rows with a copy every h and every l.
 template <int G>
 __device__ __forceinline__ double row_copy(double x)
 {
-    return __hiloint2double((int)row_copy32<G>((unsigned)__double2hiint(x)),
-                            (int)row_copy32<G>((unsigned)__double2loint(x)));
+    const auto a = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(x), (unsigned)__double2loint(x), false, false);
+    const unsigned y = a[G & 1];
+    const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    const unsigned z = b[G >> 1];
+    const auto c = __builtin_amdgcn_permlane16_swap(z, z, false, false);
+    return __hiloint2double((int)c[0], (int)c[1]);
 }
 
 }  // namespace selinv
