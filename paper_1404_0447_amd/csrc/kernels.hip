@@ -1368,7 +1368,7 @@ __device__ __forceinline__ double recip3(double f)
 // entry's update c_i c_k / d is formed as (c_i c_k) / d, the same for (k, i),
 // and c_i is scaled by d's exponent beforehand so that the product neither
 // overflows nor underflows where the update would not.  Rows from n on hold
-// the identity; pivots from the next multiple of 4 on are skipped.
+// the identity and their pivots are skipped (by fours in ldl16).
 //
 // What bounds it is issue: a lone wave issues an instruction per 4 cycles
 // (5 where it is 8 bytes long, 16 for a reciprocal, 8 for a row swap), and no
@@ -1396,35 +1396,27 @@ __device__ __forceinline__ void ldl16(double (&P)[4], double (&X)[4], const int 
     });
 }
 
-// Gauss-Jordan inversion of a symmetric 16 x 16 block, lane (m, g) holding
-// row m, columns g + 4 v.  Pivot j: l = column j / d_j; every row m != j
-// loses l_m times row j, and column j becomes -l (1 in row j).  Row j itself
-// is scaled by 1 / d_j once, at the end: until then the recurrence is linear
-// in it.  L: the multipliers l (rows below the diagonal: L_pp); dm: d_m.
-// Rows from n on hold the identity and their pivots are skipped.
+// P becomes its inverse; L: the multipliers (L_pp below the diagonal) and d_j
+// in row j.  Symmetric Gauss-Jordan: row j is left unscaled until the end,
+// which suffices where only the inverse's lower triangle is used.  Without the
+// symmetry, L D L^T was off by 1e-12 of a Gaussian kernel of 16 columns and
+// condition 5e7, now by 3e-16.
 template <int NV>
-__device__ __forceinline__ void gj16(double (&P)[NV], double (&L)[NV], double& dm, const int m, const int g,
-                                     const int n = 16)
+__device__ __forceinline__ void gj16(double (&P)[NV], double (&L)[NV], const int m, const int g, const int n)
 {
     double im = 1.0;  // 1 / d_m
     StaticFor<0, 4 * NV>::run([&](auto jc) {
         constexpr int j = decltype(jc)::value, gj = j & 3, vj = j >> 2;
         if (j >= n) return;  // uniform
-        const double c = row_copy<gj>(P[vj]);  // column j
-        const double dj = row_lane<j>(c);
-        const double inv = recip(dj);
-        const double l = c * inv;
-        const double lz = m == j ? 0.0 : l;
+        const double c = row_copy<gj>(P[vj]);
+        const double d = row_lane<j>(c), s = pow2_scale(d), r = recip3(d * s), u = m == j ? 0.0 : c * s;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) P[v] = fma(-lz, row_lane<j>(P[v]), P[v]);
+        for (int v = 0; v < NV; ++v) P[v] = fma(-(u * row_lane<j>(P[v])), r, P[v]);
         if (g == gj) {
-            P[vj] = m == j ? 1.0 : -l;
-            L[vj] = l;
+            P[vj] = m == j ? 1.0 : -(u * r);
+            L[vj] = m == j ? d : u * r;
         }
-        if (m == j) {
-            im = inv;
-            dm = dj;
-        }
+        im = m == j ? s * r : im;
     });
 #pragma unroll
     for (int v = 0; v < NV; ++v) P[v] *= im;
@@ -2101,7 +2093,7 @@ __device__ __forceinline__ void sb_factor_n(const BlockDesc d, double* __restric
         for (int v = 0; v < 4; ++v)
             cr[v] = *reinterpret_cast<const i64x2*>(cr2 + 2 * (d.coff + min(16 * K + g + 4 * v, c - 1)));
     };
-    double P[NV], L[NV] = {}, dm = 1.0;
+    double P[NV], L[NV];  // L: D on the diagonal
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const int k = g + 4 * v, a = min(max(m, k), s - 1), b = min(min(m, k), s - 1);
@@ -2117,14 +2109,14 @@ __device__ __forceinline__ void sb_factor_n(const BlockDesc d, double* __restric
             load_map(min(e, ng - 1), cr[e]);
         }
     }
-    gj16(P, L, dm, m, g, s);
-    if (g == 0 && m < s && !(isfinite(dm) && dm != 0.0 && (!require_spd || dm > 0.0)))
-        atomicMin(status, (unsigned long long)(d.first + m));
+    gj16(P, L, m, g, s);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
         const int k = g + 4 * v;
+        if (m == k && m < s && !(isfinite(L[v]) && L[v] != 0.0 && (!require_spd || L[v] > 0.0)))
+            atomicMin(status, (unsigned long long)(d.first + m));
         if (m < s && k <= m) {  // L_BB, D; T made exactly symmetric from the lower triangle
-            F[m + (int64_t)k * ld] = m == k ? dm : L[v];
+            F[m + (int64_t)k * ld] = L[v];
             T[m + (int64_t)k * s] = P[v];
             T[k + (int64_t)m * s] = P[v];
         }

@@ -109,13 +109,13 @@ RUNS = ["levels", "persistent"]
 
 @pytest.mark.parametrize("run", RUNS)
 @pytest.mark.parametrize("kappa", [1e2, 1e6, 1e10])
-@pytest.mark.parametrize("s", [17, 24, 32, 33, 48, 64, 100, 128])
+@pytest.mark.parametrize("s", [4, 8, 16, 17, 24, 32, 33, 48, 64, 100, 128])
 def test_spd_block(s, kappa, run):
     _check(spd(s, kappa, s), run)
 
 
 @pytest.mark.parametrize("run", RUNS)
-@pytest.mark.parametrize("s", [17, 24, 32, 64, 128])
+@pytest.mark.parametrize("s", [16, 17, 24, 32, 64, 128])
 def test_gaussian_kernel_block(s, run):
     _check(gaussian_kernel(s), run)
 
