@@ -1350,19 +1350,6 @@ struct alignas(16) DiagLds {
     double D[2][16], inv[2][16];  // D_p and its reciprocal
 };
 
-// the power of two s with |d| s in [1, 4), from d's exponent bits (integer
-// operations: frexp and ldexp run at a quarter of the rate)
-__device__ __forceinline__ double pow2_scale(double d)
-{
-    return __hiloint2double(max(0x7FE00000 - (__double2hiint(d) & 0x7FF00000), 0x00100000), 0);
-}
-// 1 / f: one third-order step from the hardware's estimate
-__device__ __forceinline__ double recip3(double f)
-{
-    const double y = __builtin_amdgcn_rcp(f), h = fma(-f, y, 1.0);
-    return fma(y, fma(h, h, h), y);
-}
-
 // Elimination of a symmetric 16 x 16 block, lane (m, g) holding row m, columns
 // g + 4 v.  The part not yet eliminated stays symmetric to the last bit: an
 // entry's update c_i c_k / d is formed as (c_i c_k) / d, the same for (k, i),
@@ -1420,14 +1407,6 @@ __device__ __forceinline__ void gj16(double (&P)[NV], double (&L)[NV], const int
     });
 #pragma unroll
     for (int v = 0; v < NV; ++v) P[v] *= im;
-}
-
-// one wave's LDS writes before its own reads of other lanes' values
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Y = C L^{-T} for a unit lower triangular L and 16 rows, lane (m, g) holding

@@ -48,4 +48,24 @@ __device__ __forceinline__ double row_copy(double x)
     return __hiloint2double((int)c[0], (int)c[1]);
 }
 
+// the power of two s with |d| s in [1, 4), from d's exponent bits; 2^1023 for 0
+__device__ __forceinline__ double pow2_scale(double d)
+{
+    return __hiloint2double(max(0x7FE00000 - (__double2hiint(d) & 0x7FF00000), 0x00100000), 0);
+}
+// 1 / f: one third-order step from the hardware's estimate
+__device__ __forceinline__ double recip3(double f)
+{
+    const double y = __builtin_amdgcn_rcp(f), h = fma(-f, y, 1.0);
+    return fma(y, fma(h, h, h), y);
+}
+
+// one wave's LDS writes before its own reads of other lanes' values
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace selinv

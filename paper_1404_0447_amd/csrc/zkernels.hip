@@ -239,68 +239,120 @@ __device__ __forceinline__ void zvisit(const ZAcc& acc, F f)
 __device__ __forceinline__ z2 zload(const double* p, int64_t e) { return *reinterpret_cast<const z2*>(p + 2 * e); }
 __device__ __forceinline__ void zstore(double* p, int64_t e, z2 v) { *reinterpret_cast<z2*>(p + 2 * e) = v; }
 
-// 1 / b: the hardware reciprocal of |b|^2 refined by two Newton steps
-// (each doubles the correct bits of the ~23-bit estimate), then b's
-// conjugate scaled by it
-__device__ __forceinline__ z2 zrecip(z2 b)
+// 1 / d = s inv: the power of two s is taken from d's larger part, so that
+// |d s|^2 is in [1, 32)
+__device__ __forceinline__ z2 zrecip(z2 d, double& s)
 {
-    const double den = b.x * b.x + b.y * b.y;
-    double r = __builtin_amdgcn_rcp(den);
-    r = fma(r, fma(-den, r, 1.0), r);
-    r = fma(r, fma(-den, r, 1.0), r);
-    return z2{b.x * r, -b.y * r};
+    s = pow2_scale(fmax(fabs(d.x), fabs(d.y)));
+    const z2 f = d * s;
+    const double r = recip3(fma(f.x, f.x, f.y * f.y));
+    return z2{f.x * r, -(f.y * r)};
 }
 
 // ---------------------------------------------------------------------------
-// Diagonal block, s <= 64: T_K = F_KK^{-1} by symmetric Gauss-Jordan sweeps
-// over pivot blocks of 16 columns, natural order, plain (not conjugate)
-// products.  Sweeping block p, with C(R) = M(R, p) and Q = M(p, p)^{-1}:
-//   M(I, J) -= (C(I) Q) C(J)^T  (I, J != p),  M(R, p) = C(R) Q,  M(p, p) = -Q;
-// after the last block M = -F_KK^{-1} = -T_K; only T leaves the kernel.
+// Diagonal block, s <= 64: T_K = F_KK^{-1} by the symmetric sweep of one pivot
+// after the other, natural order, plain (not conjugate) products, arranged by
+// pivot blocks of 16 columns.  Block p is factored in one wave's registers
+// (zldl16: M(p, p) = L_p D_p L_p^T).  For every block row R, with C(R) = M(R, p),
+// and C(p) = -I, Y(R) = C(R) L_p^{-T} by substitution, column after column, and
+// l(R) = Y(R) D_p^{-1}; then M(I, J) = M'(I, J) - l(I) Y(J)^T for every tile,
+// with M' = M outside row and column p and 0 in them.  After the last block
+// M = -F_KK^{-1} = -T_K; only T leaves the kernel.
+// These are the scalar sweep's operations in its order: no block is inverted on
+// the way, so a nearly singular pivot block costs what it costs pivot by pivot.
+// Complex symmetric, 64 columns, leading 16 x 16 block with an eigenvalue
+// 1e-4 of its diagonal (1e-6), largest relative error of T in the median:
+// scalar sweep 2e-12 (1e-10), this 1e-11 (6e-10), with the blocks' inverses
+// 8e-9 (6e-5).
 //
-// What bounds it is the chain of s dependent pivots: wave 0 inverts the pivot
-// blocks in its own registers (zgj16: lane broadcasts, no LDS, no barrier)
-// while the other three waves update the tiles of M, which live in LDS, with
-// MFMA products.  A block of 64 columns: 24 us against 50 us when every
-// pivot's column went through LDS behind a barrier (one pole: 5.2 -> 4.3 ms).  Rows and columns past s
-// hold the identity.  A zero or non-finite pivot latches its column.
+// What bounds it is the chain of s dependent pivots: wave 0 factors the pivot
+// blocks in its own registers (lane broadcasts, no LDS, no barrier) while the
+// other three waves update the tiles of M, which stay in their registers, with
+// MFMA products; the tiles of the next step's column go through LDS.  A block
+// of 64 columns: 24 us against 50 us when every pivot's column went through
+// LDS behind a barrier.  Rows and columns past s hold the identity.  A zero or
+// non-finite pivot latches its column.
 // ---------------------------------------------------------------------------
 // 16 complex entries a row and 16 bytes: conflict-free operand reads
 constexpr int kZDiagPad = 17;
 constexpr int kZNB = kZT / 16, kZNT = kZNB * (kZNB + 1) / 2;
 struct ZDiagLds {
-    z2 M[kZNT][16][kZDiagPad];  // tile (I, J), I >= J, at I (I + 1) / 2 + J
-    z2 C[kZT][kZDiagPad], N[kZT][kZDiagPad];
+    z2 M[kZNB][16][kZDiagPad];               // C(R) of the next step
+    z2 P[16][kZDiagPad];                     // the pivot block after it
+    z2 C[kZT][kZDiagPad], N[kZT][kZDiagPad]; // Y(R), -l(R)
+    z2 Lb[2][16][kZDiagPad];                 // -L_p below its diagonal, else 0
+    z2 inv[2][16];                           // 1 / D_p
 };
 
-// Gauss-Jordan inversion of a symmetric 16 x 16 block, lane (m, g) holding
-// row m, columns g + 4 v.  Pivot j: l = column j / d_j; every row m != j
-// loses l_m times row j, and column j becomes -l (1 in row j).  Row j itself
-// is scaled by 1 / d_j once, at the end.  dm: d_m.
-__device__ __forceinline__ void zgj16(z2 (&P)[4], z2& dm, const int m, const int g)
+// Elimination of a symmetric 16 x 16 block, lane (m, g) holding row m, columns
+// g + 4 v; X(., j): column j as pivot j finds it (d_j in row j), and what has
+// been left of the rows above.  P is used up.  The part not yet eliminated
+// stays symmetric to the last bit: c_i c_k is formed first, its imaginary part
+// from two rounded products, alike for (i, k) and (k, i).  Rows from n on hold
+// the identity; pivots from the next multiple of 4 on are skipped.
+__device__ __forceinline__ void zldl16(z2 (&P)[4], z2 (&X)[4], const int g, const int n)
 {
-    z2 im = {0.0, 0.0};  // 1 / d_m
-    StaticFor<0, 16>::run([&](auto jc) {
-        constexpr int j = decltype(jc)::value, gj = j & 3, vj = j >> 2;
-        const z2 c = {row_copy<gj>(P[vj].x), row_copy<gj>(P[vj].y)};  // column j
-        const z2 dj = {row_lane<j>(c.x), row_lane<j>(c.y)};
-        const z2 inv = zrecip(dj);
-        const z2 l = zmul(c, inv);
-        const z2 lz = m == j ? z2{0.0, 0.0} : l;
+    auto column = [](auto jc, const z2& p) {
+        constexpr int G = decltype(jc)::value & 3;
+        return z2{row_copy<G>(p.x), row_copy<G>(p.y)};
+    };
+    z2 c = column(std::integral_constant<int, 0>{}, P[0]);  // column j in every lane (m, .)
+    StaticFor<0, 4>::run([&](auto vc) {
+        constexpr int vj = decltype(vc)::value;
+        if (4 * vj >= n) return;  // uniform
+        StaticFor<4 * vj, 4 * vj + 4>::run([&](auto jc) {
+            constexpr int j = decltype(jc)::value, j1 = j < 15 ? j + 1 : 15;
+            double s;
+            const z2 inv = zrecip(z2{row_lane<j>(c.x), row_lane<j>(c.y)}, s), u = c * s;
+            auto less = [&](z2 p, z2 b) {  // p - (u b) inv
+#pragma clang fp contract(off)
+                const double re = fma(-u.y, b.y, u.x * b.x), im = u.x * b.y + u.y * b.x;
+                return z2{fma(-re, inv.x, fma(im, inv.y, p.x)), fma(-re, inv.y, fma(-im, inv.x, p.y))};
+            };
+            // the next column, broadcast before its update
+            const z2 next = column(std::integral_constant<int, j1>{}, P[j1 >> 2]);
+            const z2 cn = less(next, z2{row_lane<j1>(c.x), row_lane<j1>(c.y)});
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const z2 r = {row_lane<j>(P[v].x), row_lane<j>(P[v].y)};
-            P[v].x = fma(lz.y, r.y, fma(-lz.x, r.x, P[v].x));
-            P[v].y = fma(-lz.y, r.x, fma(-lz.x, r.y, P[v].y));
-        }
-        if (g == gj) P[vj] = m == j ? z2{1.0, 0.0} : -l;
-        if (m == j) {
-            im = inv;
-            dm = dj;
-        }
+            for (int v = j1 >> 2; v < 4; ++v) P[v] = less(P[v], z2{row_lane<j>(P[v].x), row_lane<j>(P[v].y)});
+            if (g == (j & 3)) X[vj] = c;
+            c = cn;
+        });
     });
+}
+
+// Y = C L^{-T} for a unit lower triangular L and 16 rows, lane (m, g) holding
+// rows g + 4 v, column m.  lb: -L(m, j), 0 for m <= j.  Broadcasts within the
+// rows of 16 lanes in the instruction itself, at least three other
+// instructions after the write of what they read.
+__device__ __forceinline__ void zsubstitute16(z2 (&x)[4], const z2 (&lb)[16])
+{
+    double r[4], i[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) P[v] = zmul(P[v], im);
+    for (int v = 0; v < 4; ++v) r[v] = x[v].x, i[v] = x[v].y;
+#define SELINV_FMAC(D, S, L, J) "v_fmac_f64_dpp %" #D ", " S ", %[" L "] row_newbcast:" #J " row_mask:0xf bank_mask:0xf\n\t"
+#define SELINV_STEP(J) \
+    SELINV_FMAC(0, "%0", "x" #J, J) SELINV_FMAC(1, "%1", "x" #J, J) SELINV_FMAC(2, "%2", "x" #J, J) SELINV_FMAC(3, "%3", "x" #J, J) \
+    SELINV_FMAC(4, "%4", "x" #J, J) SELINV_FMAC(5, "%5", "x" #J, J) SELINV_FMAC(6, "%6", "x" #J, J) SELINV_FMAC(7, "%7", "x" #J, J) \
+    SELINV_FMAC(0, "-%4", "y" #J, J) SELINV_FMAC(1, "-%5", "y" #J, J) SELINV_FMAC(2, "-%6", "y" #J, J) SELINV_FMAC(3, "-%7", "y" #J, J) \
+    SELINV_FMAC(4, "%0", "y" #J, J) SELINV_FMAC(5, "%1", "y" #J, J) SELINV_FMAC(6, "%2", "y" #J, J) SELINV_FMAC(7, "%3", "y" #J, J)
+#define SELINV_ROWS "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(i[0]), "+v"(i[1]), "+v"(i[2]), "+v"(i[3])
+#define SELINV_LB(J) [x##J] "v"(lb[J].x), [y##J] "v"(lb[J].y)
+    asm volatile("s_nop 1\n\t" SELINV_STEP(0) SELINV_STEP(1) SELINV_STEP(2) SELINV_STEP(3) SELINV_STEP(4) SELINV_STEP(5)
+                     SELINV_STEP(6) SELINV_STEP(7)
+                 : SELINV_ROWS
+                 : SELINV_LB(0), SELINV_LB(1), SELINV_LB(2), SELINV_LB(3), SELINV_LB(4), SELINV_LB(5), SELINV_LB(6),
+                   SELINV_LB(7));
+    asm volatile("s_nop 1\n\t" SELINV_STEP(8) SELINV_STEP(9) SELINV_STEP(10) SELINV_STEP(11) SELINV_STEP(12) SELINV_STEP(13)
+                     SELINV_STEP(14)
+                 : SELINV_ROWS
+                 : SELINV_LB(8), SELINV_LB(9), SELINV_LB(10), SELINV_LB(11), SELINV_LB(12), SELINV_LB(13),
+                   SELINV_LB(14));
+#undef SELINV_LB
+#undef SELINV_ROWS
+#undef SELINV_STEP
+#undef SELINV_FMAC
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = z2{r[v], i[v]};
 }
 
 // (re, im) += a b, 16 x 16 blocks as lane (m, g) holds them: entry
@@ -327,24 +379,36 @@ __global__ __launch_bounds__(kThreads) void k_zdiag(const Task* __restrict__ tas
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const bool chain = wave == 0;
-    constexpr int NK = kThreads / 64 - 1;  // tile waves
-    const int wk = wave - 1;
-    auto tile = [](int I, int J) { return (int)((unsigned)(I * (I + 1)) >> 1) + J; };
-    auto tile_of = [&](int t, int& I, int& J) {  // row by row: rows 1 .. 3 start at tiles 1, 3, 6
-        I = __builtin_popcount((1u << 1 | 1u << 3 | 1u << 6) & ((2u << t) - 1));
-        J = t - tile(I, 0);
-    };
-    z2 Q[4];
-    // invert the pivot block P of step p and store -Q
+    constexpr int NK = kThreads / 64 - 1, NL = (kZNT + NK - 1) / NK;  // tile waves, tiles of each
+    static_assert(kThreads / 64 >= kZNB, "a block row for every wave");
+    const int wk = chain ? 0 : wave - 1;
+    // factor the pivot block P of step p
     auto pivots = [&](int p, const z2 (&P)[4]) {
-        z2 dm = {1.0, 0.0};
+        const int buf = p & 1;
+        z2 Q[4], C[4];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) Q[v] = P[v];
-        zgj16(Q, dm, m, g);
+        for (int v = 0; v < 4; ++v) {
+            Q[v] = P[v];
+            C[v] = z2{m == g + 4 * v ? 1.0 : 0.0, 0.0};
+        }
+        zldl16(Q, C, g, s - 16 * p);
+        z2 dm = C[0];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) S.M[tile(p, p)][m][g + 4 * v] = -Q[v];
-        if (g == 0 && 16 * p + m < s && !((dm.x != 0.0 || dm.y != 0.0) && isfinite(dm.x) && isfinite(dm.y)))
-            atomicMin(status, (unsigned long long)(d.first + 16 * p + m));
+        for (int v = 1; v < 4; ++v)
+            if (m >> 2 == v) dm = C[v];
+        double sc;
+        const z2 im = zrecip(dm, sc);
+        if (g == (m & 3)) {
+            S.inv[buf][m] = im * sc;
+            if (16 * p + m < s && !((dm.x != 0.0 || dm.y != 0.0) && isfinite(dm.x) && isfinite(dm.y)))
+                atomicMin(status, (unsigned long long)(d.first + 16 * p + m));
+        }
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int k = g + 4 * v;
+            S.Lb[buf][m][k] = m > k ? -zmul(C[v], S.inv[buf][k]) : z2{0.0, 0.0};
+        }
     };
     // F(i, j) of tile (I, J), the identity past s
     auto load_tile = [&](int I, int J, z2 (&x)[4]) {
@@ -356,123 +420,119 @@ __global__ __launch_bounds__(kThreads) void k_zdiag(const Task* __restrict__ tas
             x[v] = i < s && j < s ? f : z2{i == j ? 1.0 : 0.0, 0.0};
         }
     };
-    if (chain) {
-        z2 P[4];
-        load_tile(0, 0, P);
-        pivots(0, P);
-    } else {
-        constexpr int NL = (kZNT - 1 + NK - 1) / NK;
-        z2 x[NL][4];
-        const int nt = nb * (nb + 1) / 2;
+    // this wave's tiles, every NK-th, as real and imaginary parts
+    const int nt = nb * (nb + 1) / 2;
+    zd4 re[NL], im[NL];
+    int I[NL], J[NL];
+    z2 P[4];  // the chain's next pivot block
 #pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            int I, J;
-            tile_of(min(1 + u * NK + wk, nt - 1), I, J);
-            load_tile(I, J, x[u]);
-        }
+    for (int u = 0; u < NL; ++u) {
+        // row by row: rows 1 .. 3 start at tiles 1, 3, 6
+        const int t = min(u * NK + wk, nt - 1);
+        I[u] = __builtin_popcount((1u << 1 | 1u << 3 | 1u << 6) & ((2u << t) - 1));
+        J[u] = t - (int)((unsigned)(I[u] * (I[u] + 1)) >> 1);
+        if (!chain) {
+            z2 x[4];
+            load_tile(I[u], J[u], x);
 #pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            const int t = 1 + u * NK + wk;
-            if (t < nt) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) S.M[t][m][g + 4 * v] = x[u][v];
-            }
+            for (int v = 0; v < 4; ++v) re[u][v] = x[v].x, im[u][v] = x[v].y;
         }
     }
-    __syncthreads();
-    for (int p = 0; p < nb; ++p) {
+    if (chain) load_tile(0, 0, P);
+    // step -1 only factors the first pivot block
+    for (int p = -1; p < nb; ++p) {
+        const int buf = p & 1;
         const bool more = p + 1 < nb;
-        // C(R), N(R)^T = -Q C(R)^T and M(R, p) = -N(R), row R
-        auto row = [&](const z2 (&nQ)[4], int R, z2 (&c)[4], z2 (&n)[4]) {
-            z2* tp = &S.M[tile(max(R, p), min(R, p))][0][0];
-            if (R > p) {
+        // Y(R) and -l(R), rows R = p + 1 (wave 0), p + 2, .. cyclically to p;
+        // lane (m, g) holds rows g + 4 v, column m
+        if (p >= 0 && wave < nb) {
+            const int R = p + 1 + wave < nb ? p + 1 + wave : p + 1 + wave - nb;
+            z2 x[4], lb[16];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) c[v] = tp[m * kZDiagPad + g + 4 * v];
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) c[v] = tp[(g + 4 * v) * kZDiagPad + m];
-            }
-            zd4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
-            zblock_mma(nQ, c, re, im);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) S.C[16 * R + m][g + 4 * v] = c[v];
-            zdrain();
+            for (int j = 0; j < 15; ++j) lb[j] = S.Lb[buf][m][j];
+            const z2 inv = S.inv[buf][m];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                n[v] = z2{re[v], im[v]};
-                S.N[16 * R + m][g + 4 * v] = n[v];
+                const z2 c = S.M[R][g + 4 * v][m];
+                x[v] = R != p ? c : z2{m == g + 4 * v ? -1.0 : 0.0, 0.0};
             }
-            if (R > p) {
+            zsubstitute16(x, lb);
 #pragma unroll
-                for (int v = 0; v < 4; ++v) tp[m * kZDiagPad + g + 4 * v] = -n[v];
-            } else {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) tp[(g + 4 * v) * kZDiagPad + m] = -n[v];
+            for (int v = 0; v < 4; ++v) {
+                S.C[16 * R + g + 4 * v][m] = x[v];
+                S.N[16 * R + g + 4 * v][m] = -zmul(x[v], inv);
             }
-        };
-        z2 nQ[4], c[4], n[4], P[4];
+        }
+        if (chain && more && p >= 0) {
+            // the next pivot block: its update needs nothing from the other
+            // waves.  Its upper entries are the lower ones: exactly symmetric
+            wave_sync();
+            z2 y[4], n[4];
+            zd4 pr, pi;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) nQ[v] = chain ? -Q[v] : S.M[tile(p, p)][m][g + 4 * v];
-        if (chain) {
-            // row p + 1, and the next pivot block with it (the last step has
-            // no such row: then row 0)
-            if (more) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) P[v] = S.M[tile(p + 1, p + 1)][m][g + 4 * v];
+            for (int v = 0; v < 4; ++v) {
+                const z2 x = S.P[m][g + 4 * v];
+                pr[v] = x.x, pi[v] = x.y;
+                y[v] = S.C[16 * (p + 1) + m][g + 4 * v];
+                n[v] = S.N[16 * (p + 1) + m][g + 4 * v];
             }
-            if (nb > 1) row(nQ, more ? p + 1 : 0, c, n);
-            if (more) {
-                zd4 re = {P[0].x, P[1].x, P[2].x, P[3].x}, im = {P[0].y, P[1].y, P[2].y, P[3].y};
-                zblock_mma(c, n, re, im);
-                zdrain();
+            zblock_mma(y, n, pr, pi);
+            zdrain();
 #pragma unroll
-                for (int v = 0; v < 4; ++v) P[v] = z2{re[v], im[v]};
-            }
-        } else {
-            // p + 2, p + 3, .. cyclically, without p
-            const int r = 1 + wk, R = p + 1 + r < nb ? p + 1 + r : p + 1 + r - nb;
-            if (r < nb - 1) row(nQ, R, c, n);
+            for (int v = 0; v < 4; ++v) S.P[m][g + 4 * v] = z2{pr[v], pi[v]};
+            wave_sync();
+#pragma unroll
+            for (int v = 0; v < 4; ++v) P[v] = S.P[max(m, g + 4 * v)][min(m, g + 4 * v)];
         }
         __syncthreads();
-        if (chain) {
-            if (more) pivots(p + 1, P);
-        } else {
-            // M(I, J) += N(I) C(J)^T over the tiles outside row and column p
-            // and the next pivot block
-            const int nt = nb * (nb - 1) / 2;
-            for (int t = wk; t < nt; t += NK) {
-                int I, J;
-                tile_of(t, I, J);
-                I += I >= p;
-                J += J >= p;
-                if (I == p + 1 && J == p + 1) continue;
-                z2(*tp)[kZDiagPad] = S.M[tile(I, J)];
-                z2 a[4], b[4], x[4];
+        if (!chain) {
+            // M(I, J) = M'(I, J) - l(I) Y(J)^T
+            if (p >= 0) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    x[v] = tp[m][g + 4 * v];
-                    a[v] = S.C[16 * J + m][g + 4 * v];
-                    b[v] = S.N[16 * I + m][g + 4 * v];
+                for (int u = 0; u < NL; ++u) {
+                    if (u * NK + wk >= nt) break;  // uniform
+                    z2 a[4], b[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        a[v] = S.C[16 * J[u] + m][g + 4 * v];
+                        b[v] = S.N[16 * I[u] + m][g + 4 * v];
+                    }
+                    if (I[u] == p || J[u] == p) re[u] = im[u] = zd4{0.0, 0.0, 0.0, 0.0};
+                    zblock_mma(a, b, re[u], im[u]);
                 }
-                zd4 re = {x[0].x, x[1].x, x[2].x, x[3].x}, im = {x[0].y, x[1].y, x[2].y, x[3].y};
-                zblock_mma(a, b, re, im);
                 zdrain();
+            }
+            // what the next step reads: the rows' tiles of its column, and
+            // for wave 0 the pivot block after it (the next one is its own)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) tp[m][g + 4 * v] = z2{re[v], im[v]};
+            for (int u = 0; u < NL; ++u) {
+                if (u * NK + wk >= nt) break;  // uniform
+                const bool col = J[u] == p + 1, row = I[u] == p + 1;
+                z2* to = I[u] == J[u] ? S.P[0] : S.M[col ? I[u] : J[u]][0];
+                if (I[u] == J[u] ? I[u] == p + 2 : col) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) to[m * kZDiagPad + g + 4 * v] = z2{re[u][v], im[u][v]};
+                } else if (I[u] != J[u] && row) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) to[(g + 4 * v) * kZDiagPad + m] = z2{re[u][v], im[u][v]};
+                }
             }
         }
+        if (chain && more) pivots(p + 1, P);
         __syncthreads();
     }
     // T = -M, made exactly symmetric from the lower triangle
-    for (int t = wave; t < nb * (nb + 1) / 2; t += kThreads / 64) {
-        int I, J;
-        tile_of(t, I, J);
+    if (!chain) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int k = g + 4 * v, i = 16 * I + m, j = 16 * J + k, i2 = 16 * I + k, j2 = 16 * J + m;
-            if (i < s && j <= i) zstore(Tp, d.woff + i + (int64_t)j * s, -S.M[t][m][k]);
-            if (i2 < s && j2 < i2) zstore(Tp, d.woff + j2 + (int64_t)i2 * s, -S.M[t][k][m]);
-        }
+        for (int u = 0; u < NL; ++u)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * I[u] + m, j = 16 * J[u] + g + 4 * v;
+                if (u * NK + wk < nt && i < s && j <= i) {
+                    zstore(Tp, d.woff + i + (int64_t)j * s, -z2{re[u][v], im[u][v]});
+                    zstore(Tp, d.woff + j + (int64_t)i * s, -z2{re[u][v], im[u][v]});
+                }
+            }
     }
 }
 

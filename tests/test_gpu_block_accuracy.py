@@ -143,3 +143,46 @@ def test_gradient(s):
     acols, arows = np.triu_indices(s)
     ref = np.where(arows == acols, 0.5, 1.0) * d[arows, acols]
     assert np.abs(g - ref).max() <= 4 * 2 * U * np.linalg.cond(a) * np.abs(ref).max()
+
+
+def nearly_singular_complex(s, kappa, seed):
+    """Complex symmetric, shifted so close to an eigenvalue of its leading
+    16 x 16 block that 1 / kappa of it is left."""
+    rng = np.random.default_rng(seed)
+    a = rng.standard_normal((s, s)) + 1j * rng.standard_normal((s, s))
+    a = 0.5 * (a + a.T)
+    lam = np.linalg.eigvals(a[:16, :16])
+    return a - lam[np.argmax(np.abs(lam))] * (1.0 - 1.0 / kappa) * np.eye(s)
+
+
+def _check_complex(a):
+    """Complex products carry an error of up to 2 sqrt(2) times a real one's."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1404_0447_amd import selinv as S
+    s = len(a)
+    m = _matrix(a)
+    p = S.Plan.from_matrix(m, complex_values=True).bind()
+    p.factor_complex(torch.as_tensor(m.vals, device="cuda"))
+    sel = p.invert_complex()
+    p.sync_status()
+    cp, ri, perm = p.pattern()
+    cols = np.repeat(np.arange(s), np.diff(cp))
+    ap = a[np.ix_(perm, perm)]
+    x = _inverse(ap)
+    bar = 2 * np.sqrt(2) * 2 * U * np.linalg.cond(ap) * _growth(ap)
+    assert np.abs(sel.cpu().numpy() - x[ri, cols]).max() <= bar * np.abs(x).max()
+
+
+@pytest.mark.parametrize("kappa", [1e2, 1e4, 1e6])
+@pytest.mark.parametrize("s", [16, 17, 32, 33, 48, 64])
+def test_complex_nearly_singular_leading_block(s, kappa):
+    _check_complex(nearly_singular_complex(s, kappa, s))
+
+
+@pytest.mark.parametrize("eta", [1.0, 0.1, 0.01])
+@pytest.mark.parametrize("s", [17, 33, 64])
+def test_complex_near_the_real_axis(s, eta):
+    """H + i eta, the matrices of poles next to the spectrum."""
+    _check_complex(indefinite(s, 1e2, s) + 1j * eta * np.eye(s))
