@@ -3156,7 +3156,7 @@ hipError_t launch_schur_groups(Prof* P, const DevPtrs& D, const int64_t* cuts, i
     // one launch per colour group (groups update disjoint entries)
     for (int g = g0; g < g1; g++) {
         const int64_t n = cuts[g + 1] - cuts[g];
-        if (n > 0 && (panel_deep & 2) && n <= kDeepMaxTiles)
+        if (n > 0 && (panel_deep & 2) && n <= kFewSchurTiles)
             launch(P, kSchur, k_schur_few, dim3((unsigned)(4 * n)), 0, s, D.t_schur + cuts[g], D.blocks, D.Lp,
                    (const double*)D.Hp, D.cr2, D.rel);
         else if (n > 0)

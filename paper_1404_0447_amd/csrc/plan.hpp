@@ -153,8 +153,8 @@ struct selinv_plan_s {
     std::vector<int64_t> ldlt_cut;     // per level: t_ldlt splits into s <= 32 | <= 64 | wider at 2l, 2l+1
     // per level: t_schur in colour groups [cut[g], cut[g+1]) whose blocks share no column of C
     std::vector<std::vector<int64_t>> schur_cuts;
-    // per level: bit 0, panel tiles <= 64 wide and at most kDeepMaxTiles of
-    // them (the panel kernel of few tiles); bit 1, every block of the level
+    // per level: bit 0, panel tiles <= 64 wide and few of them
+    // (the panel kernel of few tiles); bit 1, every block of the level
     // at most kDeepK wide (the kernels of few tiles allowed at all)
     std::vector<char> panel_deep;
     // reverse sweep: selected inversion (leaves first) and factorization (root first)

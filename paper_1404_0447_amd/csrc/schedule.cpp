@@ -366,7 +366,7 @@ void build_schedule(selinv_plan_s* P)
         // the kernels of few tiles hold a contraction of at most kDeepK
         // (blocks wider than 128 columns exist only with exec_cap > 128)
         const bool deep_ok = smax <= kDeepK;
-        const bool deep = deep_ok && npanel64 <= kDeepMaxTiles;
+        const bool deep = deep_ok && npanel64 <= (smax <= 64 ? kFewPanelTiles : kFewPanelTilesWide);
         P->panel_deep[l] = (char)((deep ? 1 : 0) | (deep_ok ? 2 : 0));
         for (int B : lv[l]) {
             const BlockDesc& d = P->blocks[B];

@@ -21,9 +21,12 @@ constexpr int kZSplitRows = 128;
 // levels with fewer tasks than this (those of a single pole) cut shorter
 // pieces and fewer of them: there a piece's length is its time, while in the
 // larger levels of a batch the pieces' sums cost more than they gain.
-// Measured (one pole, 32 poles; ms): 64 rows (32 below 64 tasks) and a fill of
-// 2,048 everywhere 3.51, 30.3; 128 and 64 rows 3.78, 30.0; 32 rows below 128
-// tasks and a fill of 768 everywhere 3.40, 30.5.
+// Measured, ms, these constants against 64 rows (32 below 64 tasks) and a fill
+// of 2,048 everywhere: n = 8,000, 1 pole 3.34 and 3.43, 2 4.49 and 4.48, 4 6.44
+// and 6.43, 8 10.17 and 10.17, 16 17.19 and 17.30, 32 29.93 and 30.10; n = 1,728,
+// 1 pole 1.02 and 1.02, 4 1.18 and 1.30, 8 1.60 and 1.58, 16 2.18 and 2.12, 32
+// 3.17 and 3.13; n = 1,372, 1 pole 0.71 and 0.70, 4 0.77 and 0.81, 8 0.94 and
+// 0.97, 16 1.28 and 1.30, 32 1.89 and 1.96.
 constexpr int kZSplitFewTasks = 128;
 constexpr int kZSplitFewRows = 32;
 constexpr int kZSplitFewFill = 768;
@@ -39,13 +42,26 @@ inline bool is_small(int s, int c, int smax) { return s <= smax && c <= kSbC; }
 // kernels spread them over many more work-groups (swept over 0..256: 32
 // fastest at 40^3, 64^3 and molecular 16^3)
 constexpr int kSbCLevel = 32;
-// A level with at most this many panel tiles (a Schur colour group with at
-// most this many tiles) gives each 16 x 16 tile to a wave, which loads its
-// whole contraction (s <= 128) before its first product: there the tiles'
-// latency, not the device's throughput, sets the level time.  At s = 128 a
-// Schur launch of 105 tiles takes 10 us so, of 190 14, of 253 16; tiled, of
-// 276 tiles 18, of 300 17, of 325 17.
-constexpr int kDeepMaxTiles = 256;
+// A level with few panel tiles (a Schur colour group with few tiles) gives
+// each 16 x 16 tile to a wave, which loads its whole contraction (s <= 128)
+// before its first product: there the tiles' latency, not the device's
+// throughput, sets the level time.  Measured, us, few-tile kernel < or >
+// tiled kernel at the same number of 64-wide tiles (a: batches of dense chains
+// of that s; b: the 40^3 grid, c: the molecular 16^3 matrix, where s is mostly
+// 128):
+//   Schur  s = 16  144 6.5 = 6.5, 192 7.1 > 6.6, 240 8.2 > 7.0 (a)
+//          s = 32  132 7.1 = 7.2, 168 8.5 > 8.2, 224 10.2 > 8.6 (a)
+//          s = 64  120 6.4 < 8.6, 168 9.7 < 10.7, 192 10.2 > 9.3 (a)
+//          s = 128 120 9.0 < 11.8, 144 12.3 > 11.6, 224 16.1 > 13.1 (a);
+//                  120 10.8 < 12.6, 153 13.7 = 13.6, 231 16.4 > 14.6 (b);
+//                  136 12.5 = 12.4, 171 13.5 > 13.2, 253 16.6 > 13.3 (c)
+//   panel  s = 16  96 3.8 = 3.6, 160 4.3 > 3.7; s = 32  144 4.6 = 4.8, 192 5.4
+//          > 4.9; s = 64  144 7.1 < 7.4, 192 7.6 < 8.2, 220 8.8 > 8.5 (a)
+//          s = 128, against tiles of 128 columns: 128 9.3 < 16.7, 230 15.1 <
+//          17.3, 298 17.8 = 17.8, 326 19.9 > 17.8 (b); 247 10.8 < 16.3 (c)
+constexpr int kFewSchurTiles = 160;
+constexpr int kFewPanelTiles = 160;      // of blocks at most 64 wide
+constexpr int kFewPanelTilesWide = 256;  // of wider ones
 constexpr int kDeepK = 128;  // longest contraction of the kernels of few tiles
 constexpr int kZeroCols = 8;  // columns of Ainv(:, B) a task of the set-up kernel clears
 // A level's Schur update runs in colour groups (read-modify-write, one launch

@@ -1094,11 +1094,20 @@ hipError_t launch_zexport(const double* Ap, const int64_t* off, int64_t n, doubl
     return hipGetLastError();
 }
 
-// Launches of at most this many tiles take the wave-per-16 x 16 kernels (s =
-// 64, old > new us): panel 27 tiles 12 > 6, 104 13 > 9, 160 equal, 256
-// 16 < 19; Schur 15 tiles 13 > 5, 91 14 > 9, 192 15 > 12, 320 25 > 20, 480
-// 29 < 32 (they load each operand four times as often).  One pole of
-// n = 8,000, factor + inversion: 4.36 -> 3.49 ms.
+// Launches of at most this many tiles take the wave-per-16 x 16 kernels (they
+// load each operand four times as often).  Measured, us, these < or > the
+// 64-wide tiles at the same number of tiles (a: batches of dense chains of
+// that s; b: poles of n = 8,000, s mostly 64):
+//   panel  s = 16  144 5.1 < 5.5, 192 6.1 = 6.0, 220 7.7 > 6.2; s = 32  160
+//          8.6 = 8.8, 192 9.1 < 9.4, 220 11.2 > 9.7; s = 64  160 14.4 < 14.9,
+//          192 15.2 < 15.7, 220 18.6 > 16.4 (a); 132 12.8 < 13.5, 168 13.5 =
+//          13.5, 212 16.0 > 15.1 (b); past 256, where the 64-wide tiles no
+//          longer have a CU each, 264 18.1 < 22.1, 384 22.8 = 23.1 (b)
+//   Schur  s = 16  360 13.1 < 14.5, 480 15.3 = 15.5; s = 32  360 15.1 < 18.2,
+//          480 19.4 < 20.3; s = 64  360 23.8 < 26.2, 440 27.8 = 28.1, 480 30.5
+//          > 29.1 (a); 376 21.4 < 25.0, 476 26.9 < 28.7 (b)
+// Without a limit 8 poles take 9.8 ms instead of 10.2, but 32 poles 30.5
+// instead of 29.9.  One pole with 64-wide tiles alone: 4.36 instead of 3.49.
 constexpr int64_t kZFewPanel = 160, kZFewSchur = 384;
 
 hipError_t launch_zfactor_level(const DevPtrs& D, int64_t diag0, int64_t ndiag, int64_t panel0, int64_t npanel,
