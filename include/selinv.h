@@ -266,7 +266,7 @@ selinv_status selinv_get_symbolic(selinv_plan p, int32_t* parent, int32_t* xsupe
 /* Kernel kinds reported by the timing calls below. */
 enum {
     SELINV_K_ASSEMBLE = 0, /* zero the factor arena, scatter A into it            */
-    SELINV_K_LDLT = 1,     /* diagonal block LDL^T, W = L_KK^{-1}, T_K           */
+    SELINV_K_LDLT = 1,     /* diagonal block LDL^T and T_K = F_KK^{-1}           */
     SELINV_K_PANEL = 2,    /* L(C,K) and the normalised L_hat(C,K)               */
     SELINV_K_SCHUR = 3,    /* Schur update added into ancestor panels            */
     SELINV_K_GEMM = 4,     /* Ainv(C,K) = -Ainv(C,C) L_hat(C,K), gathered        */
@@ -311,7 +311,7 @@ selinv_status selinv_get_arena(selinv_plan p, int32_t which, double* d_out, int6
 /* Execution blocks (host copies, nblocks entries each; any may be NULL):
  * first column, width s, |C|, priority level, and the offsets (in doubles)
  * of the block's (s+c) x s panel, its c x s L_hat block and its s x s
- * W / T blocks; crow_off[b] indexes the rows C(b) in the order returned by
+ * scratch / T blocks; crow_off[b] indexes the rows C(b) in the order returned by
  * selinv_get_exec_rows. */
 selinv_status selinv_get_blocks(selinv_plan p, int32_t* first, int32_t* s, int32_t* c, int32_t* level,
                                 int64_t* poff, int64_t* hoff, int64_t* woff, int64_t* crow_off);

@@ -260,16 +260,16 @@ selinv_status resolve_opts(const selinv_opts* opts, selinv_opts& o)
     if (o.deterministic != 0 && o.deterministic != 1) return fail(SELINV_EINVAL, "deterministic must be 0 or 1");
     if (o.checkpoint_every < 1) o.checkpoint_every = 1;
     if (o.max_super <= 0) o.max_super = 128;
-    // execution blocks default to <= 128 columns (the width the register
-    // sweep of the diagonal block holds); the L pattern does not depend on
-    // the partition, only the reported fundamental supernodes use max_super
+    // execution blocks default to <= 128 columns (the width the diagonal
+    // block's kernel holds in LDS and registers); the L pattern does not depend
+    // on the partition, only the reported fundamental supernodes use max_super
     if (o.exec_cap <= 0) o.exec_cap = std::min(o.max_super, (int32_t)kLdsDiagMax);
     if (o.max_super > 256 || o.exec_cap > 256)
         return fail(SELINV_EUNSUPPORTED, "supernode width cap above 256 is not supported");
     if (o.complex_values) {
-        // the complex kernels hold a whole diagonal block in registers (four
-        // 16-row sub-blocks) and one 64 x 64 output tile per diagonal step, and
-        // add without atomics: blocks of at most 64 columns, deterministic schedule
+        // the complex kernels hold a diagonal block of four 16-column pivot
+        // blocks and one 64 x 64 output tile per diagonal step, and add without
+        // atomics: blocks of at most 64 columns, deterministic schedule
         o.exec_cap = std::min(o.exec_cap, (int32_t)kZMaxS);
         o.deterministic = 1;
     }

@@ -9,7 +9,8 @@
 //       F(C,B) L_BB^{-T} D^{-1} and is formed only on export).
 //   Ap  same layout, holds the selected entries of A^{-1}.
 //   Hp  L_hat(C,B) = L(C,B) L_BB^{-1} = F(C,B) T, c x s column-major (ld c).
-//   Wp  W = L_BB^{-1} (s x s); Tp  T = L_BB^{-T} D_B^{-1} L_BB^{-1} (s x s).
+//   Tp  T = F_BB^{-1} (s x s); Wp  scratch (s x s): L_BB^{-1} of a block wider
+//       than 128 columns while its T is formed, not written for the others.
 // Block index maps: for position r of C(B), cbase[r] is the arena offset of
 // column C[r] inside its owning block J, and rel[rbase[r] + i] the row of
 // C[i] (i >= r's segment start) inside rows(J).  So the entry
@@ -241,8 +242,11 @@ __device__ __forceinline__ void tile_epilogue_t(const d4 (&acc)[2][4], F f)
 // chunk n+3, of B of chunk n+2, of the rel entries of chunk n+4 and of the
 // (cbase, rbase) pairs of chunk n+5 are issued: A, which comes from HBM, has
 // two iterations of MFMAs to arrive, the others one.  One barrier per chunk.
-// Byte offsets inside a block's panel and C's maps are 32-bit: a |C| that
-// exceeds them (4 million) would need a 16 TB inverse.
+// Byte offsets inside a block's panel and C's maps are 32-bit, here and at the
+// buffer descriptors below, so s (s + |C|) doubles have to stay below 4 GiB.
+// With s <= 256 that holds to |C| of 2.09 million.  No plan gets there: C x C
+// lies in the ancestors' panels, |C|^2 / 2 doubles, 17.6 TB at that size, and
+// the 288 GB of a card end at a |C| of 270,000.
 constexpr int kGatherRow = 16 * (int)sizeof(double);  // bytes of one LDS row
 // byte offset of contraction entry k of a row: entries 8 t + g and 8 t + 4 + g
 // (g < 4) share slot 4 t + g
@@ -1242,8 +1246,8 @@ __global__ __launch_bounds__(kThreads) void k_sdiag64(const Task* __restrict__ t
 }
 
 // ---------------------------------------------------------------------------
-// Factor, diagonal block wider than the register sweeps hold (s > 128, only
-// with exec_cap above 128), on global memory: right-looking LDL^T without
+// Factor, diagonal block wider than the kernels below hold (s > 128, only with
+// exec_cap above 128), on global memory: right-looking LDL^T without
 // pivoting in place of F_BB, then W = L_BB^{-1} column by column (forward
 // substitution, one thread a column) and T = W^T D^{-1} W.  A pivot that is
 // zero, not finite, or (require_spd) not positive is latched as the smallest
@@ -1294,8 +1298,8 @@ __device__ void ldlt_global(const BlockDesc d, double* __restrict__ Lp, double* 
     }
 }
 
-// 1 / d: hardware reciprocal and two Newton steps (each squares the relative
-// error; the first estimate is good to about 2^-26)
+// 1 / d: hardware reciprocal (within 2^-24) and two Newton steps, each of which
+// squares the relative error
 __device__ __forceinline__ double recip(double d)
 {
     double inv = __builtin_amdgcn_rcp(d);
@@ -1728,7 +1732,9 @@ __global__ __launch_bounds__(64 * diag_waves(NB)) void k_ldlt_diag(const Task* _
 // What bounds it: a chain per pivot of LDS round trips, cross-lane maxima,
 // scalar decisions and branches (151 us for 128 columns); neither fewer
 // vector instructions in the update nor the update under the search's
-// latencies made it faster (159 and 161 us).
+// latencies made it faster (159 and 161 us).  Not tried: panels of 16 pivots
+// whose columns are brought up to date as they are searched, with the rest of
+// the block updated once a panel; the pivots would be the same.
 // ---------------------------------------------------------------------------
 
 // a value every lane holds alike, made known to the compiler as uniform

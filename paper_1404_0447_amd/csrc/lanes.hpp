@@ -53,7 +53,8 @@ __device__ __forceinline__ double pow2_scale(double d)
 {
     return __hiloint2double(max(0x7FE00000 - (__double2hiint(d) & 0x7FF00000), 0x00100000), 0);
 }
-// 1 / f: one third-order step from the hardware's estimate
+// 1 / f: one third-order step from the hardware's estimate, which is within
+// 2^-24 of it (measured over [1, 4): the result within 2^-53)
 __device__ __forceinline__ double recip3(double f)
 {
     const double y = __builtin_amdgcn_rcp(f), h = fma(-f, y, 1.0);

@@ -30,7 +30,7 @@ struct Partition {
 struct BlockDesc {
     int64_t poff;   // panel (s+c) x s, column-major, ld = s + c  (L and Ainv arenas)
     int64_t hoff;   // L_hat(C,K), c x s column-major, ld = c
-    int64_t woff;   // s x s blocks: W = L_KK^{-1} and T = L_KK^{-T} D^{-1} L_KK^{-1}
+    int64_t woff;   // s x s blocks: T = F_KK^{-1}, and the scratch beside it
     int64_t coff;   // offset into the per-position arrays (crow, cbase, rbase)
     int32_t first, s, c, level;
 };
