@@ -249,6 +249,21 @@ __device__ __forceinline__ z2 zrecip(z2 d, double& s)
     return z2{f.x * r, -(f.y * r)};
 }
 
+// 1 / d to about half a unit in the last place of its size: a Newton step from
+// zrecip, with the residual 1 - f inv of the scaled f from exact products.
+// These are D^{-1}'s entries, which a diagonally dominant block's inverse has
+// on its diagonal.
+__device__ __forceinline__ z2 zrecip_refined(z2 d)
+{
+#pragma clang fp contract(off)
+    double s;
+    const z2 i = zrecip(d, s), f = d * s;
+    const double p = f.x * i.x, q = f.y * i.x;
+    const double ex = fma(f.y, i.y, 1.0 - p) - fma(f.x, i.x, -p);
+    const double ey = -(fma(f.x, i.y, q) + fma(f.y, i.x, -q));
+    return z2{fma(i.x, ex, fma(-i.y, ey, i.x)), fma(i.x, ey, fma(i.y, ex, i.y))} * s;
+}
+
 // ---------------------------------------------------------------------------
 // Diagonal block, s <= 64: T_K = F_KK^{-1} by the symmetric sweep of one pivot
 // after the other, natural order, plain (not conjugate) products, arranged by
@@ -304,10 +319,10 @@ __device__ __forceinline__ void zldl16(z2 (&P)[4], z2 (&X)[4], const int g, cons
             constexpr int j = decltype(jc)::value, j1 = j < 15 ? j + 1 : 15;
             double s;
             const z2 inv = zrecip(z2{row_lane<j>(c.x), row_lane<j>(c.y)}, s), u = c * s;
-            auto less = [&](z2 p, z2 b) {  // p - (u b) inv
+            auto less = [&](z2 p, z2 b) {  // p - (u b) inv, one rounding at p's size
 #pragma clang fp contract(off)
                 const double re = fma(-u.y, b.y, u.x * b.x), im = u.x * b.y + u.y * b.x;
-                return z2{fma(-re, inv.x, fma(im, inv.y, p.x)), fma(-re, inv.y, fma(-im, inv.x, p.y))};
+                return z2{p.x - fma(-im, inv.y, re * inv.x), p.y - fma(im, inv.x, re * inv.y)};
             };
             // the next column, broadcast before its update
             const z2 next = column(std::integral_constant<int, j1>{}, P[j1 >> 2]);
@@ -356,11 +371,12 @@ __device__ __forceinline__ void zsubstitute16(z2 (&x)[4], const z2 (&lb)[16])
 }
 
 // (re, im) += a b, 16 x 16 blocks as lane (m, g) holds them: entry
-// (m, g + 4 v) of a, and of b transposed, in register v
+// (m, g + 4 v) of a, and of b transposed, in register v.  The last pivots
+// first: in row and column p the sums grow towards the earlier ones.
 __device__ __forceinline__ void zblock_mma(const z2 (&a)[4], const z2 (&b)[4], zd4& re, zd4& im)
 {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 3; v >= 0; --v) {
         re = zmfma(a[v].x, b[v].x, re);
         im = zmfma(a[v].x, b[v].y, im);
         re = zmfma(-a[v].y, b[v].y, re);
@@ -396,10 +412,9 @@ __global__ __launch_bounds__(kThreads) void k_zdiag(const Task* __restrict__ tas
 #pragma unroll
         for (int v = 1; v < 4; ++v)
             if (m >> 2 == v) dm = C[v];
-        double sc;
-        const z2 im = zrecip(dm, sc);
+        const z2 im = zrecip_refined(dm);
         if (g == (m & 3)) {
-            S.inv[buf][m] = im * sc;
+            S.inv[buf][m] = im;
             if (16 * p + m < s && !((dm.x != 0.0 || dm.y != 0.0) && isfinite(dm.x) && isfinite(dm.y)))
                 atomicMin(status, (unsigned long long)(d.first + 16 * p + m));
         }
@@ -467,40 +482,51 @@ __global__ __launch_bounds__(kThreads) void k_zdiag(const Task* __restrict__ tas
             // the next pivot block: its update needs nothing from the other
             // waves.  Its upper entries are the lower ones: exactly symmetric
             wave_sync();
-            z2 y[4], n[4];
-            zd4 pr, pi;
+            z2 x[4], y[4], n[4];
+            zd4 pr = {0, 0, 0, 0}, pi = {0, 0, 0, 0};
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const z2 x = S.P[m][g + 4 * v];
-                pr[v] = x.x, pi[v] = x.y;
+                x[v] = S.P[m][g + 4 * v];
                 y[v] = S.C[16 * (p + 1) + m][g + 4 * v];
                 n[v] = S.N[16 * (p + 1) + m][g + 4 * v];
             }
             zblock_mma(y, n, pr, pi);
             zdrain();
 #pragma unroll
-            for (int v = 0; v < 4; ++v) S.P[m][g + 4 * v] = z2{pr[v], pi[v]};
+            for (int v = 0; v < 4; ++v) S.P[m][g + 4 * v] = x[v] + z2{pr[v], pi[v]};
             wave_sync();
 #pragma unroll
             for (int v = 0; v < 4; ++v) P[v] = S.P[max(m, g + 4 * v)][min(m, g + 4 * v)];
         }
         __syncthreads();
         if (!chain) {
-            // M(I, J) = M'(I, J) - l(I) Y(J)^T
+            // M(I, J) = M'(I, J) - l(I) Y(J)^T, the product summed by itself:
+            // into M it would round twice a pivot at M's size, where the
+            // scalar sweep rounds once (T's error on the blocks of a 4^3-atom
+            // pencil 3.8e-16 instead of 1.9e-16; the scalar sweep's 2.9e-16)
             if (p >= 0) {
 #pragma unroll
-                for (int u = 0; u < NL; ++u) {
-                    if (u * NK + wk >= nt) break;  // uniform
-                    z2 a[4], b[4];
+                for (int u0 = 0; u0 < NL; u0 += 2) {
+                    if (u0 * NK + wk >= nt) break;  // uniform
+                    zd4 ar[2] = {}, ai[2] = {};
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        a[v] = S.C[16 * J[u] + m][g + 4 * v];
-                        b[v] = S.N[16 * I[u] + m][g + 4 * v];
+                    for (int u = u0; u < min(u0 + 2, NL); ++u) {
+                        z2 a[4], b[4];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            a[v] = S.C[16 * J[u] + m][g + 4 * v];
+                            b[v] = S.N[16 * I[u] + m][g + 4 * v];
+                        }
+                        zblock_mma(a, b, ar[u - u0], ai[u - u0]);
                     }
-                    if (I[u] == p || J[u] == p) re[u] = im[u] = zd4{0.0, 0.0, 0.0, 0.0};
-                    zblock_mma(a, b, re[u], im[u]);
+                    zdrain();
+#pragma unroll
+                    for (int u = u0; u < min(u0 + 2, NL); ++u) {
+                        const bool zero = I[u] == p || J[u] == p;  // uniform
+                        re[u] = zero ? ar[u - u0] : re[u] + ar[u - u0];
+                        im[u] = zero ? ai[u - u0] : im[u] + ai[u - u0];
+                    }
                 }
-                zdrain();
             }
             // what the next step reads: the rows' tiles of its column, and
             // for wave 0 the pivot block after it (the next one is its own)

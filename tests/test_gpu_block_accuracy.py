@@ -186,3 +186,36 @@ def test_complex_nearly_singular_leading_block(s, kappa):
 def test_complex_near_the_real_axis(s, eta):
     """H + i eta, the matrices of poles next to the spectrum."""
     _check_complex(indefinite(s, 1e2, s) + 1j * eta * np.eye(s))
+
+
+@pytest.mark.parametrize("s", [8, 16, 32, 48, 64])
+def test_complex_roundings_per_pivot(s):
+    """Each pivot's update rounds an entry once, at the entry's size.
+
+    Diagonally dominant blocks H + i eta: every pivot changes the diagonal,
+    which makes up the norm, by a small part of itself, so a rounding is
+    uniform and independent of the others: 2 U / sqrt(12) of the binade's
+    floor, over mantissas drawn log-uniformly sqrt(0.75 / (2 ln 2)) of that,
+    0.425 U in all.  s pivots add up to 0.425 U sqrt(s); with two roundings a
+    pivot it is 0.60 U sqrt(s).  The bar lies midway."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1404_0447_amd import selinv as S
+    rng, errors = np.random.default_rng(s), []
+    for _ in range(24):
+        h = rng.standard_normal((s, s))
+        a = 0.5 * (h + h.T) + 1j * 4 * np.sqrt(s) * 2.0 ** rng.uniform() * np.eye(s)
+        m = _matrix(a)
+        p = S.Plan.from_matrix(m, complex_values=True).bind()
+        p.factor_complex(torch.as_tensor(m.vals, device="cuda"))
+        sel = p.invert_complex().cpu().numpy()
+        p.sync_status()
+        _, ri, perm = p.pattern()
+        assert len(ri) == s * (s + 1) // 2
+        x = np.zeros((s, s), np.clongdouble)
+        cols = np.repeat(np.arange(s), np.arange(s, 0, -1))
+        x[ri, cols] = x[cols, ri] = sel
+        ref = _inverse(a[np.ix_(perm, perm)])
+        errors.append(np.sqrt((np.abs(x - ref) ** 2).sum() / (np.abs(ref) ** 2).sum()))
+    assert np.mean(errors) <= 0.51 * U * np.sqrt(s)
