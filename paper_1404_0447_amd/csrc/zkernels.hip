@@ -277,14 +277,14 @@ __device__ __forceinline__ z2 zrecip_refined(z2 d)
 // the way, so a nearly singular pivot block costs what it costs pivot by pivot.
 // Complex symmetric, 64 columns, leading 16 x 16 block with an eigenvalue
 // 1e-4 of its diagonal (1e-6), largest relative error of T in the median:
-// scalar sweep 2e-12 (1e-10), this 1e-11 (6e-10), with the blocks' inverses
-// 8e-9 (6e-5).
+// scalar sweep 1.6e-12 (1.3e-10), this 3.4e-12 (3.7e-10), with the blocks'
+// inverses 8e-9 (6e-5).
 //
 // What bounds it is the chain of s dependent pivots: wave 0 factors the pivot
 // blocks in its own registers (lane broadcasts, no LDS, no barrier) while the
 // other three waves update the tiles of M, which stay in their registers, with
 // MFMA products; the tiles of the next step's column go through LDS.  A block
-// of 64 columns: 24 us against 50 us when every pivot's column went through
+// of 64 columns: 25 us against 50 us when every pivot's column went through
 // LDS behind a barrier.  Rows and columns past s hold the identity.  A zero or
 // non-finite pivot latches its column.
 // ---------------------------------------------------------------------------
@@ -371,12 +371,11 @@ __device__ __forceinline__ void zsubstitute16(z2 (&x)[4], const z2 (&lb)[16])
 }
 
 // (re, im) += a b, 16 x 16 blocks as lane (m, g) holds them: entry
-// (m, g + 4 v) of a, and of b transposed, in register v.  The last pivots
-// first: in row and column p the sums grow towards the earlier ones.
+// (m, g + 4 v) of a, and of b transposed, in register v
 __device__ __forceinline__ void zblock_mma(const z2 (&a)[4], const z2 (&b)[4], zd4& re, zd4& im)
 {
 #pragma unroll
-    for (int v = 3; v >= 0; --v) {
+    for (int v = 0; v < 4; ++v) {
         re = zmfma(a[v].x, b[v].x, re);
         im = zmfma(a[v].x, b[v].y, im);
         re = zmfma(-a[v].y, b[v].y, re);
@@ -503,7 +502,11 @@ __global__ __launch_bounds__(kThreads) void k_zdiag(const Task* __restrict__ tas
             // M(I, J) = M'(I, J) - l(I) Y(J)^T, the product summed by itself:
             // into M it would round twice a pivot at M's size, where the
             // scalar sweep rounds once (T's error on the blocks of a 4^3-atom
-            // pencil 3.8e-16 instead of 1.9e-16; the scalar sweep's 2.9e-16)
+            // pencil 3.8e-16 instead of 1.9e-16; the scalar sweep's 2.9e-16).
+            // In row and column p the sum takes the last pivot first: pivots
+            // i .. 15 add to a diagonal entry (i, i), and its own, 1 / d_i, is
+            // the large one.  The other tiles take the pivots as they come: a
+            // small last pivot makes the large term, and comes last.
             if (p >= 0) {
 #pragma unroll
                 for (int u0 = 0; u0 < NL; u0 += 2) {
@@ -512,10 +515,11 @@ __global__ __launch_bounds__(kThreads) void k_zdiag(const Task* __restrict__ tas
 #pragma unroll
                     for (int u = u0; u < min(u0 + 2, NL); ++u) {
                         z2 a[4], b[4];
+                        const int r = I[u] == p || J[u] == p ? 3 : 0;
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            a[v] = S.C[16 * J[u] + m][g + 4 * v];
-                            b[v] = S.N[16 * I[u] + m][g + 4 * v];
+                            a[v] = S.C[16 * J[u] + m][g + 4 * (v ^ r)];
+                            b[v] = S.N[16 * I[u] + m][g + 4 * (v ^ r)];
                         }
                         zblock_mma(a, b, ar[u - u0], ai[u - u0]);
                     }
