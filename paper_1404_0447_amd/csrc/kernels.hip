@@ -1325,9 +1325,9 @@ __device__ __forceinline__ double recip(double d)
 // Q = M(p, p)^{-1} (C(R) Q for l(R) L_pp^{-1}) would square the condition
 // number of the pivot block; and the pivot blocks have to be exactly
 // symmetric, or L D L^T no longer gives F_BB back to rounding.  Largest error
-// of T, relative, SPD of condition 1e8, 24 columns: the scalar sweep 3e-10,
-// this 4e-10, with Q 3e-6; Gaussian kernel of condition 5e7, 128 columns:
-// 9e-10, 4e-10, no digit.
+// of T, relative, SPD of condition 1e8, 24 columns (median of 15): the scalar
+// sweep 2.0e-10, this 2.3e-10, with Q 5e-6; Gaussian kernel of condition 5e7,
+// 128 columns: 7.6e-10, 7.3e-10, no digit.
 //
 // What bounds it is the chain of s dependent pivots.  So wave 0 does nothing
 // but that chain: it updates the next pivot block, factors it (the pivot column
